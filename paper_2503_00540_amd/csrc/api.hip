@@ -15,6 +15,9 @@ struct rekv_ctx {
     int device;
     void* ws;             // workspace: split-KV partials, or pooled questions + scores
     size_t ws_bytes;
+    uint32_t* tickets;    // arrival counters of split attention launches, zero between launches
+    int ticket_slot;      // their slot of the static pool, -1: an allocation of its own
+    bool tickets_used;    // a launch has been given them
     void* scratch;        // this device's copy of the static scratch array
     hipStream_t side;     // host<->device copies of offloaded KV
     hipEvent_t ev_main;   // recorded on the caller's stream, waited on by the side stream
@@ -31,6 +34,12 @@ struct rekv_ctx {
 constexpr size_t NOALLOC_SCRATCH_BYTES = (size_t)33 << 20;
 static __device__ __align__(256) unsigned char scratch[NOALLOC_SCRATCH_BYTES];
 
+// Arrival counters of the contexts alive on a GPU: a slot each, so that contexts on different streams
+// never share a counter.  Zero at load and after every launch, so a slot needs no clearing when it
+// changes hands; contexts beyond the pool allocate their own.
+constexpr int TICKET_SLOTS = 64;
+static __device__ uint32_t ticket_pool[TICKET_SLOTS][rekv::WAVE_TICKETS];
+
 namespace {
 
 thread_local char g_create_err[512] = "";
@@ -39,6 +48,9 @@ thread_local char g_create_err[512] = "";
 constexpr int MAX_DEVICES = 64;
 std::mutex g_scratch_mutex;
 void* g_scratch_ptr[MAX_DEVICES] = {};
+uint32_t* g_ticket_ptr[MAX_DEVICES] = {};
+uint64_t g_ticket_taken[MAX_DEVICES] = {};     // bit i: slot i belongs to a context
+static_assert(TICKET_SLOTS == 64, "one bit per slot");
 
 // Looks the address up once per device; that device must be current.
 hipError_t scratch_address(int device, void** out) {
@@ -53,6 +65,44 @@ hipError_t scratch_address(int device, void** out) {
     }
     *out = g_scratch_ptr[device];
     return hipSuccess;
+}
+
+hipError_t take_tickets(rekv_ctx* c) {
+    {
+        std::lock_guard<std::mutex> lock(g_scratch_mutex);
+        if (!g_ticket_ptr[c->device]) {
+            hipError_t e = hipGetSymbolAddress(reinterpret_cast<void**>(&g_ticket_ptr[c->device]), HIP_SYMBOL(ticket_pool));
+            if (e != hipSuccess) return e;
+        }
+        uint64_t& taken = g_ticket_taken[c->device];
+        if (~taken) {
+            c->ticket_slot = __builtin_ctzll(~taken);
+            taken |= 1ull << c->ticket_slot;
+            c->tickets = g_ticket_ptr[c->device] + c->ticket_slot * rekv::WAVE_TICKETS;
+            return hipSuccess;
+        }
+    }
+    c->ticket_slot = -1;
+    hipError_t e = hipMalloc(reinterpret_cast<void**>(&c->tickets), rekv::WAVE_TICKETS * sizeof(uint32_t));
+    return e == hipSuccess ? hipMemset(c->tickets, 0, rekv::WAVE_TICKETS * sizeof(uint32_t)) : e;
+}
+
+// The context's launches must have finished before another one gets the slot.
+void give_tickets(rekv_ctx* c) {
+    if (!c->tickets) return;
+    if (c->ticket_slot < 0) {
+        (void)hipFree(c->tickets);
+        return;
+    }
+    if (c->tickets_used) {
+        int current = 0;
+        (void)hipGetDevice(&current);
+        if (current != c->device) (void)hipSetDevice(c->device);
+        (void)hipDeviceSynchronize();
+        if (current != c->device) (void)hipSetDevice(current);
+    }
+    std::lock_guard<std::mutex> lock(g_scratch_mutex);
+    g_ticket_taken[c->device] &= ~(1ull << c->ticket_slot);
 }
 
 rekv_status fail(rekv_ctx* ctx, rekv_status code, const char* fmt, ...) {
@@ -116,7 +166,9 @@ rekv_status run_attention(rekv_ctx* c, const rekv::AttnProblem& p, hipStream_t s
         if (s != REKV_OK) return s;
         ws = c->ws;
     }
-    hipError_t e = rekv::attn_bf16_launch(p, plan, ws, stream);
+    c->tickets_used |= plan.wave != 0;
+    hipError_t e = plan.wave ? rekv::attn_wave_launch(p, plan, ws, c->tickets, stream)
+                             : rekv::attn_bf16_launch(p, plan, ws, stream);
     return e == hipSuccess ? REKV_OK : fail_hip(c, "bf16 attention launch", e);
 }
 
@@ -150,6 +202,7 @@ rekv_status rekv_create(const rekv_shape* shape, rekv_ctx** out) {
     c->scale = shape->softmax_scale > 0.f ? shape->softmax_scale : 1.0f / sqrtf((float)shape->head_dim);
     hipError_t e = hipGetDevice(&c->device);
     if (e == hipSuccess) e = scratch_address(c->device, &c->scratch);
+    if (e == hipSuccess) e = take_tickets(c);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_main, hipEventDisableTiming);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_side, hipEventDisableTiming);
@@ -171,6 +224,7 @@ void rekv_destroy(rekv_ctx* c) {
     if (c->ev_main) (void)hipEventDestroy(c->ev_main);
     if (c->ev_side) (void)hipEventDestroy(c->ev_side);
     if (c->ws) (void)hipFree(c->ws);
+    give_tickets(c);
     if (c->idx_host) (void)hipHostFree(c->idx_host);
     delete c;
 }

@@ -33,32 +33,16 @@
 // Eq. 3's retrieved KV + text KV (question prefill and decode steps); INDEXED - segment A read
 // from the KV arena through a frame index list; STREAM - non-temporal tile loads when no
 // other workgroup reads the same keys.
-#include <type_traits>
-
-#include "common.h"
+#include "attention_mfma.h"
 
 namespace rekv {
 namespace {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
-
-#define LDS_AS __attribute__((address_space(3)))
-#define GLOBAL_AS __attribute__((address_space(1)))
-
-constexpr int BN = 32;        // keys per tile (one MFMA row block of S^T)
 constexpr int STAGES = 4;     // LDS stages per tensor
 constexpr int WAVES = 4;
 constexpr int WM = 32;        // query rows per wavefront (one MFMA column block)
 constexpr int BM = WAVES * WM;
 constexpr int THREADS = WAVES * 64;
-constexpr float RESCALE_GAP = 8.0f;  // log2 units the running max may lag before O is rescaled
 
 template <int D>
 struct Cfg {
@@ -69,59 +53,12 @@ struct Cfg {
     static constexpr int TILE_ELEMS = BN * D;
 };
 
-// Swizzle of the chunk index inside a key row: the two 2-bit fields of (key mod 16) swapped.
-// 16 consecutive keys get 16 different values; 4 consecutive keys differ in the upper field.
-template <int D>
-__device__ inline int swz(int key) {
-    return (((key & 3) << 2) | ((key >> 2) & 3)) & (Cfg<D>::CH - 1);
-}
-
 struct KernelArgs {
     AttnProblem p;
     int32_t n_splits, m_tiles;
     float* part_o;    // [item*Hkv + kvh][split][m_tiles*BM][D]
     float* part_ml;   // [item*Hkv + kvh][split][m_tiles*BM][2]
 };
-
-// Blocks are dealt to the 8 XCDs round-robin by hardware; give each XCD one contiguous
-// range of logical blocks so that blocks sharing K/V tiles share an L2.
-__device__ inline int xcd_remap(int bid, int nb) {
-    const int x = bid & 7, per = nb >> 3, rem = nb & 7;
-    return x * per + (x < rem ? x : rem) + (bid >> 3);
-}
-
-__device__ inline void wait_vmem() { __builtin_amdgcn_s_waitcnt(0x0F70); }   // vmcnt(0)
-
-// One 16-byte-per-lane load from global memory straight into LDS: lane i's 16 bytes land at
-// lds_addr + 16 * i.  Written as asm so that the loads stay invisible to the compiler's
-// wait-count bookkeeping: with more than a handful of such loads in a loop it would drain
-// all of them before any LDS read.  Ordering is explicit instead (step_barrier).
-// The source address is a wave-uniform base plus a 32-bit per-lane byte offset.
-// NT marks the load non-temporal: for keys and values that no other workgroup will read again
-// (a decode step), so they stream past the caches instead of displacing what is reused.
-template <bool NT>
-__device__ inline void dma16(const void* base, uint32_t lane_off, uint32_t lds_addr) {
-    if (NT)
-        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 nt"
-                     ::"v"(lane_off), "s"(base), "s"(__builtin_amdgcn_readfirstlane(lds_addr)) : "memory", "m0");
-    else
-        asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-                     ::"v"(lane_off), "s"(base), "s"(__builtin_amdgcn_readfirstlane(lds_addr)) : "memory", "m0");
-}
-__device__ inline uint32_t lds_addr_of(const void* p) {
-    return (uint32_t)(uintptr_t)(LDS_AS const void*)p;
-}
-
-// A query's two lanes (lane, lane ^ 32) combine a value without touching LDS:
-// v_permlane32_swap hands every lane both halves' values.
-__device__ inline float pair_max(float v) {
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
-}
-__device__ inline float pair_sum(float v) {
-    const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
-}
 
 // End of a pipeline step: this wave's loads except the newest N have landed, its LDS reads
 // have returned, then the workgroup barrier.  No fence: a fence would drain the newest loads.
@@ -139,7 +76,6 @@ using IC = std::integral_constant<int, I>;
 // ENCODE selects the segment layout (Eq. 1 window + chunk in one cache, or Eq. 3 retrieved KV +
 // question) at compile time; the two instantiations also show up under separate names in a trace.
 // INDEXED: segment A is read from the KV arena through a frame index list (no gathered copy).
-constexpr int MAX_INDEXED_FRAMES = 1024;   // index entries staged in LDS per workgroup
 
 // STREAM: every K/V tile is read by this workgroup only (one row block per item), see dma16.
 template <int D, bool ENCODE, bool INDEXED, bool STREAM>
@@ -315,8 +251,6 @@ __global__ __launch_bounds__(THREADS, 2) void attn_bf16_kernel(KernelArgs a) {
         for (int j = 0; j < 16; ++j) o[i][j] = 0.f;
     float m_ref = -INFINITY, l_part = 0.f;
     const float sc = p.scale * 1.4426950408889634f;
-
-    typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 tr4_t;
 
     // S^T of one tile (32 keys x 32 queries) from K fragments already in registers
     auto qk = [&](const bf16x8 (&kf)[D / 16], f32x16& s) {
@@ -643,6 +577,7 @@ hipError_t launch(const AttnProblem& p, const AttnPlan& plan, void* workspace, h
 
 AttnPlan attn_bf16_plan(const AttnProblem& p) {
     AttnPlan plan;
+    plan.wave = 0;
     const int G = p.n_q_heads / p.n_kv_heads;
     plan.m_tiles = (p.len_q * G + BM - 1) / BM;
     const int64_t base = (int64_t)p.n_items * p.n_kv_heads * plan.m_tiles;
@@ -663,6 +598,20 @@ AttnPlan attn_bf16_plan(const AttnProblem& p) {
         if (splits > cap) splits = cap;
     }
     plan.n_splits = splits;
+    if (base < target) {
+        // Launches that do not fill the chip by themselves go to attention_wave.hip where that is the
+        // faster one.  Estimate for this kernel, fitted to the same measurements: a 32-key step of
+        // every workgroup 0.74 us (head_dim 64: 0.65); around it 7 us, or with split keys 10 us plus
+        // the partial results' way out and back (0.48 us per MB), in a decode step 9.5 us plus the
+        // merge's walk over the splits (0.04 us each at head_dim 128).
+        const int64_t rows = (int64_t)p.len_q * G < BM ? (int64_t)p.len_q * G : BM;
+        const double part_mb = (double)(base * splits * rows * p.head_dim) * 4e-6;
+        double us = (double)((n_tiles + splits - 1) / splits) * (p.head_dim == 64 ? 0.65 : 0.74);
+        if (splits == 1) us += 7.0;
+        else if (rows <= WM) us += 9.5 + 0.04 * splits * p.head_dim / 128;
+        else us += 10.0 + 0.48 * part_mb;
+        if (attn_wave_plan(p, us, &plan)) return plan;
+    }
     plan.workspace_bytes = 0;
     if (splits > 1)
         plan.workspace_bytes = (size_t)p.n_items * p.n_kv_heads * splits * plan.m_tiles * BM *

@@ -76,14 +76,23 @@ __device__ inline ItemSegs item_segments(const AttnProblem& p, int item) {
     return s;
 }
 
-// Split-KV workspace need of the bf16 kernel, in bytes (0 when one split suffices).
+// How a bf16 attention launch is split, and the workspace its partial results need (0 when one split
+// suffices).  wave: attention_wave.hip takes the launch (m_tiles = 32-row blocks), else
+// attention_bf16.hip (m_tiles = 128-row blocks).
 struct AttnPlan {
+    int32_t wave;
     int32_t n_splits;
     int32_t m_tiles;
     size_t workspace_bytes;
 };
 AttnPlan attn_bf16_plan(const AttnProblem& p);
 hipError_t attn_bf16_launch(const AttnProblem& p, const AttnPlan& plan, void* workspace,
+                            hipStream_t stream);
+// attn_wave_plan: true if that kernel takes the problem (other_us: what it has to beat).  tickets: WAVE_TICKETS zeroed words that only
+// calls ordered on one stream use.
+constexpr int WAVE_TICKETS = 512;
+bool attn_wave_plan(const AttnProblem& p, double other_us, AttnPlan* plan);
+hipError_t attn_wave_launch(const AttnProblem& p, const AttnPlan& plan, void* workspace, uint32_t* tickets,
                             hipStream_t stream);
 hipError_t attn_f32_launch(const AttnProblem& p, hipStream_t stream);
 

@@ -1,0 +1,70 @@
+"""bf16 attention launches that are split over the keys inside a workgroup (few query rows): the sizes
+where that split can go wrong - row counts around a block of 32 and 64 rows, tile counts around the
+number of key runs, launches whose row blocks are shared by several workgroups - against the oracle.
+Every call runs three times: the arrival counters must be back at zero after each launch."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import rekv_oracle as O
+from paper_2503_00540_amd import workloads as W
+from paper_2503_00540_amd.rekv import Rekv
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+# outputs are averages of N(0,1) values, below 4 in size: one bf16 rounding of the result (2^-9 * 4 = 8e-3)
+# and the probabilities' roundings (2^-9 each, averaging out) stay below 2e-2
+TOL = 2e-2
+
+
+def bf16(rng, *shape):
+    return W.round_to_bf16(rng.standard_normal(shape))
+
+
+def dev(x):
+    return torch.from_numpy(np.ascontiguousarray(x, dtype=np.float32)).to(torch.bfloat16).to(DEV)
+
+
+@pytest.mark.parametrize("hq,hkv,d,n_new,n_ret,n_text", [
+    (1, 1, 128, 1, 0, 1),            # one row, one key
+    (7, 1, 128, 1, 31, 5),           # fewer tiles than key runs
+    (8, 1, 128, 4, 224, 32),         # exactly 32 rows, exactly 8 tiles
+    (3, 1, 64, 11, 225, 40),         # 33 rows: a block of one row; a tile of one key
+    (16, 2, 64, 4, 4000, 9),         # row blocks shared by workgroups
+    (28, 4, 128, 9, 1500, 20),       # 63 rows
+    (28, 4, 128, 32, 3136, 32),      # a question of the 7B-class shapes
+    (8, 8, 128, 65, 700, 65),        # one head per group, 65 rows, causal part over three tiles
+    (28, 4, 128, 1, 12544, 97),      # a decode step split over many workgroups
+])
+def test_few_rows_match_oracle(hq, hkv, d, n_new, n_ret, n_text):
+    rng = np.random.default_rng(hq * 1000 + n_new)
+    r = Rekv(hq, hkv, d, 1)
+    for nq in (1, 3):
+        q, kr, vr = bf16(rng, nq, n_new, hq, d), bf16(rng, nq, n_ret, hkv, d), bf16(rng, nq, n_ret, hkv, d)
+        kt, vt = bf16(rng, nq, n_text, hkv, d), bf16(rng, nq, n_text, hkv, d)
+        args = [dev(x) for x in (q, kr, vr, kt, vt)]
+        outs = [r.decode_attention(*args, n_text, no_alloc=bool(i % 2)) for i in range(3)]
+        assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
+        got = outs[0].float().cpu().numpy()
+        for i in range(nq):
+            ref = O.decode_attention(q[i], kr[i], vr[i], kt[i], vt[i])
+            assert np.abs(got[i] - ref).max() < TOL
+
+
+@pytest.mark.parametrize("hq,hkv,d,l_x,n_chunks,l_l,first", [
+    (28, 4, 128, 196, 1, 16 * 196, 16 * 196),    # a live frame, window full
+    (14, 2, 64, 196, 1, 16 * 196, 16 * 196),
+    (28, 4, 128, 37, 2, 100, 60),                # window not full, ragged everything
+    (64, 8, 128, 144, 1, 500, 2000),             # 64-row blocks shared by two waves
+    (4, 4, 64, 33, 1, 0, 0),                     # no window
+])
+def test_live_chunks_match_oracle(hq, hkv, d, l_x, n_chunks, l_l, first):
+    rng = np.random.default_rng(l_x + hq)
+    r = Rekv(hq, hkv, d, 1)
+    n = first + n_chunks * l_x
+    q, k, v = bf16(rng, n_chunks * l_x, hq, d), bf16(rng, n, hkv, d), bf16(rng, n, hkv, d)
+    dq, dk, dv = dev(q), dev(k), dev(v)
+    outs = [r.encode_chunk(dq, dk, dv, first, l_x, n_chunks, l_l) for _ in range(3)]
+    assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
+    ref = O.encode_chunks(q, k, v, first, l_x, n_chunks, l_l)
+    assert np.abs(outs[0].float().cpu().numpy() - ref).max() < TOL
