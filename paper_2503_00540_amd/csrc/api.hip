@@ -132,6 +132,9 @@ rekv_status reserve(rekv_ctx* c, size_t bytes) {
         c->ws_bytes = 0;
         if (e != hipSuccess) return fail_hip(c, "hipFree(workspace)", e);
     }
+    // 8 MiB to start with: scores and pooled questions, and every launch of attention_wave.hip, fit, so
+    // most contexts allocate once (growing costs a hipFree, a hipMalloc and the device's idling)
+    if (bytes < (size_t(8) << 20)) bytes = size_t(8) << 20;
     bytes = (bytes + (size_t(1) << 20) - 1) & ~((size_t(1) << 20) - 1);
     hipError_t e = hipMalloc(&c->ws, bytes);
     if (e != hipSuccess) {

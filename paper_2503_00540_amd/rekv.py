@@ -95,8 +95,13 @@ def lib() -> ctypes.CDLL:
     return L
 
 
+# The current stream's handle without building a torch.cuda.Stream object around it: 0.2 us instead of
+# 2.8 us on every call (the call itself, one kernel launch included, takes about 4 us).
+_get_device, _raw_stream = torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream
+
+
 def _stream() -> int:
-    return torch.cuda.current_stream().cuda_stream
+    return _raw_stream(_get_device())
 
 
 class Rekv:
@@ -139,9 +144,9 @@ class Rekv:
     def _dev(self, t: torch.Tensor, dtype=None, last=None, name="tensor") -> int:
         if not t.is_cuda or not t.is_contiguous():
             raise ValueError(f"{name} must be a contiguous CUDA tensor")
-        if t.dtype != (dtype or self.torch_dtype):
+        if t.dtype is not (dtype or self.torch_dtype):
             raise ValueError(f"{name} has dtype {t.dtype}, expected {dtype or self.torch_dtype}")
-        if last is not None and tuple(t.shape[-len(last):]) != tuple(last):
+        if last is not None and t.shape[-len(last):] != last:
             raise ValueError(f"{name} has shape {tuple(t.shape)}, expected trailing {tuple(last)}")
         return t.data_ptr()
 
