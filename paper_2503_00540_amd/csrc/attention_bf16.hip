@@ -605,12 +605,16 @@ AttnPlan attn_bf16_plan(const AttnProblem& p) {
         // the partial results' way out and back (0.48 us per MB), in a decode step 9.5 us plus the
         // merge's walk over the splits (0.04 us each at head_dim 128).
         const int64_t rows = (int64_t)p.len_q * G < BM ? (int64_t)p.len_q * G : BM;
-        const double part_mb = (double)(base * splits * rows * p.head_dim) * 4e-6;
+        const int64_t ik = (int64_t)p.n_items * p.n_kv_heads;
+        const double part_mb = (double)(ik * splits * p.len_q * G * p.head_dim) * 4e-6;
+        const int64_t kv_tokens = p.is_encode ? p.l_l + (int64_t)p.n_items * p.len_b : (int64_t)p.n_items * (p.len_a + p.len_b);
+        const double kv_mb = rows > WM ? (double)(kv_tokens * p.n_kv_heads * p.head_dim) * 4e-6 : 0.0;
         double us = (double)((n_tiles + splits - 1) / splits) * (p.head_dim == 64 ? 0.65 : 0.74);
         if (splits == 1) us += 7.0;
         else if (rows <= WM) us += 9.5 + 0.04 * splits * p.head_dim / 128;
         else us += 10.0 + 0.48 * part_mb;
-        if (attn_wave_plan(p, us, &plan)) return plan;
+        us += 0.1 * kv_mb;
+        if (attn_wave_plan(p, us, kv_mb, &plan)) return plan;
     }
     plan.workspace_bytes = 0;
     if (splits > 1)

@@ -565,7 +565,10 @@ hipError_t launch(const AttnProblem& p, const AttnPlan& plan, void* workspace, u
 // 1.1 us (head_dim 128, eight private tiles: the CU's 64 B/clk from L2), 1.03 us (four tiles shared by
 // two waves), 0.63 us (head_dim 64; twice that with two workgroups on a CU); a ticket round 3 us plus
 // the last arriver's reading of the partial results, 0.04 us each and 0.07 MB/us.
-bool attn_wave_plan(const AttnProblem& p, double other_us, AttnPlan* plan) {
+// kv_mb: K and V that several row blocks read, from HBM: here 0.36 us per MB on top (0.16 at head_dim 64; the row blocks of a
+// head walk the same tiles together, one step ahead of their use: little in flight), there 0.1.  A
+// question over 64 frames (26 MB): 26.9 us with its KV in the caches and 35.9 without, there 30.8 and 33.2.
+bool attn_wave_plan(const AttnProblem& p, double other_us, double kv_mb, AttnPlan* plan) {
     const int G = p.n_q_heads / p.n_kv_heads, D = p.head_dim;
     const int64_t m_rows = (int64_t)p.len_q * G, ik = (int64_t)p.n_items * p.n_kv_heads;
     const int64_t len_a_max = p.is_encode ? p.l_l : p.len_a;
@@ -574,7 +577,7 @@ bool attn_wave_plan(const AttnProblem& p, double other_us, AttnPlan* plan) {
     // count: 160 (question, head) pairs x 3.2 MB take 171 us there and 192 us here.
     if (m_rows <= WM && ik * n_tiles * BN * D * 4 > (256ll << 20)) return false;
     const int64_t slots = D == 64 ? 512 : 256;   // resident workgroups: LDS holds one (D = 128) or two per CU
-    double best = 0.95 * other_us;               // (estimates closer than that decide nothing)
+    double best = 0.98 * other_us;
     bool take = false;
     for (int rw = 1; rw <= 2; ++rw) {
         const int64_t T = rw * WM, kg = WAVES / rw;
@@ -585,6 +588,7 @@ bool attn_wave_plan(const AttnProblem& p, double other_us, AttnPlan* plan) {
         for (int64_t s = 1; s <= slots / base && (s == 1 || (s - 1) * kg < n_tiles); ++s) {
             const int64_t steps = (n_tiles + s * kg - 1) / (s * kg);
             double us = 8.0 + (double)steps * step_us * (base * s > 256 ? 2.0 : 1.0);
+            us += (D == 64 ? 0.16 : 0.36) * kv_mb;
             if (s > 1) us += 3.0 + (double)s * (0.04 + (double)(rows * D * 4) * 1.4e-5);
             if (us >= best) continue;
             best = us;

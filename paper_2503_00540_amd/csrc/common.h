@@ -91,7 +91,7 @@ hipError_t attn_bf16_launch(const AttnProblem& p, const AttnPlan& plan, void* wo
 // attn_wave_plan: true if that kernel takes the problem (other_us: what it has to beat).  tickets: WAVE_TICKETS zeroed words that only
 // calls ordered on one stream use.
 constexpr int WAVE_TICKETS = 512;
-bool attn_wave_plan(const AttnProblem& p, double other_us, AttnPlan* plan);
+bool attn_wave_plan(const AttnProblem& p, double other_us, double kv_mb, AttnPlan* plan);
 hipError_t attn_wave_launch(const AttnProblem& p, const AttnPlan& plan, void* workspace, uint32_t* tickets,
                             hipStream_t stream);
 hipError_t attn_f32_launch(const AttnProblem& p, hipStream_t stream);
