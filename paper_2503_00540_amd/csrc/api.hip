@@ -482,7 +482,7 @@ rekv_status rekv_gather_kv(rekv_ctx* c, const void* src_k, const void* src_v, in
     if (frame_bytes % 16 != 0) return fail(c, REKV_ERR_UNSUPPORTED, "rekv_gather_kv: frame of %zu bytes is not a multiple of 16", frame_bytes);
 
     if (!src_on_host) {
-        hipError_t e = rekv::gather_launch(src_k, src_v, n_src_frames, idx, (int)n_blocks, frame_bytes,
+        hipError_t e = rekv::gather_launch(src_k, src_v, false, n_src_frames, idx, (int)n_blocks, frame_bytes,
                                            dst_k, dst_v, stream);
         return e == hipSuccess ? REKV_OK : fail_hip(c, "gather launch", e);
     }
@@ -501,7 +501,7 @@ rekv_status rekv_gather_kv(rekv_ctx* c, const void* src_k, const void* src_v, in
         e = hipEventRecord(c->ev_main, stream);
         if (e == hipSuccess) e = hipStreamWaitEvent(c->side, c->ev_main, 0);
         if (e == hipSuccess)
-            e = rekv::gather_launch(dk, dv, n_src_frames, idx, (int)n_blocks, frame_bytes, dst_k, dst_v, c->side);
+            e = rekv::gather_launch(dk, dv, true, n_src_frames, idx, (int)n_blocks, frame_bytes, dst_k, dst_v, c->side);
         if (e == hipSuccess) e = hipEventRecord(c->ev_side, c->side);
         if (e == hipSuccess) e = hipStreamWaitEvent(stream, c->ev_side, 0);
         return e == hipSuccess ? REKV_OK : fail_hip(c, "rekv_gather_kv: zero-copy gather", e);
@@ -609,7 +609,7 @@ rekv_status rekv_gather_kv_rope(rekv_ctx* c, const void* src_k, const void* src_
     if (st != REKV_OK) return st;
     hipStream_t stream = static_cast<hipStream_t>(stream_);
     if (!src_on_host) {
-        hipError_t e = rekv::gather_rope_launch(src_k, src_v, n_src_frames, idx, n_questions, k, c->shape.tokens_per_frame,
+        hipError_t e = rekv::gather_rope_launch(src_k, src_v, false, n_src_frames, idx, n_questions, k, c->shape.tokens_per_frame,
                                                 c->shape.n_kv_heads, c->shape.head_dim, c->shape.dtype, dst_k, dst_v, ra, stream);
         return e == hipSuccess ? REKV_OK : fail_hip(c, "gather_kv_rope launch", e);
     }
@@ -625,7 +625,7 @@ rekv_status rekv_gather_kv_rope(rekv_ctx* c, const void* src_k, const void* src_
     e = hipEventRecord(c->ev_main, stream);
     if (e == hipSuccess) e = hipStreamWaitEvent(c->side, c->ev_main, 0);
     if (e == hipSuccess)
-        e = rekv::gather_rope_launch(dk, dv, n_src_frames, idx, n_questions, k, c->shape.tokens_per_frame, c->shape.n_kv_heads,
+        e = rekv::gather_rope_launch(dk, dv, true, n_src_frames, idx, n_questions, k, c->shape.tokens_per_frame, c->shape.n_kv_heads,
                                      c->shape.head_dim, c->shape.dtype, dst_k, dst_v, ra, c->side);
     if (e == hipSuccess) e = hipEventRecord(c->ev_side, c->side);
     if (e == hipSuccess) e = hipStreamWaitEvent(stream, c->ev_side, 0);
@@ -667,7 +667,7 @@ rekv_status rekv_attention_indexed_rope(rekv_ctx* c, const void* q, const void* 
                                src_pos_offset, &ra);
     if (st != REKV_OK) return st;
     // pre-pass over the index list: the selected frames' keys, turned to their new positions, into k_pos
-    hipError_t e = rekv::gather_rope_launch(k_src, v_src, n_src_frames, idx, n_questions, n_ret_frames, (int)n_f,
+    hipError_t e = rekv::gather_rope_launch(k_src, v_src, false, n_src_frames, idx, n_questions, n_ret_frames, (int)n_f,
                                             c->shape.n_kv_heads, c->shape.head_dim, c->shape.dtype, k_pos, nullptr, ra,
                                             static_cast<hipStream_t>(stream));
     if (e != hipSuccess) return fail_hip(c, "rekv_attention_indexed_rope: key pre-pass", e);

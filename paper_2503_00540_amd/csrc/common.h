@@ -123,9 +123,9 @@ hipError_t block_keys_launch(const float* frame_keys, int n_frames, int b, int d
 hipError_t expand_blocks_launch(const int32_t* block_idx, int n_questions, int k_blocks, int b, int n_frames,
                                 int32_t* frame_idx, int32_t* n_sel, hipStream_t stream);
 
-hipError_t gather_launch(const void* src_k, const void* src_v, int n_src_frames, const int32_t* idx,
-                         int n_blocks, size_t frame_bytes, void* dst_k, void* dst_v,
-                         hipStream_t stream);
+// src_on_host: device addresses of pinned host arrays, read over the host link
+hipError_t gather_launch(const void* src_k, const void* src_v, bool src_on_host, int n_src_frames, const int32_t* idx,
+                         int n_blocks, size_t frame_bytes, void* dst_k, void* dst_v, hipStream_t stream);
 
 constexpr int MAX_GATHER_LAYERS = 64;
 hipError_t gather_layers_launch(const void* const* src_k, const void* const* src_v, int n_layers, int n_src_frames,
@@ -140,9 +140,9 @@ struct RopeArgs {
     int64_t pos_offset, src_pos_offset;
     int32_t is_static, src_rotated, interleaved;
 };
-hipError_t gather_rope_launch(const void* src_k, const void* src_v, int n_src_frames, const int32_t* idx,
-                              int n_questions, int k_slots, int n_f, int n_kv_heads, int d, int dtype,
-                              void* dst_k, void* dst_v, const RopeArgs& ra, hipStream_t stream);
+hipError_t gather_rope_launch(const void* src_k, const void* src_v, bool src_on_host, int n_src_frames,
+                              const int32_t* idx, int n_questions, int k_slots, int n_f, int n_kv_heads, int d,
+                              int dtype, void* dst_k, void* dst_v, const RopeArgs& ra, hipStream_t stream);
 
 // Measurement probes (probe.hip).
 hipError_t launch_probe_copy(void* dst, const void* src, int64_t n_bytes, hipStream_t stream);
