@@ -2,6 +2,8 @@
 // cosine scores with tau = 1, and exact top-k selection.  All of it is memory-bound: the
 // kernels read each input once with 16-byte coalesced accesses and keep reductions in
 // registers / wavefront shuffles.
+#include <type_traits>
+
 #include "common.h"
 
 namespace rekv {
@@ -30,10 +32,11 @@ __device__ inline float wave_sum(float v) {
 // One workgroup streams one frame (a contiguous N_f x D' block) front to back: LPR lanes
 // cover a key row with 16-byte loads (8 bf16 or 4 fp32 each), the 256 / LPR row groups take
 // alternate rows, eight loads are in flight per thread, and the row groups' partial sums
-// meet in LDS.  Rows wider than 256 lanes are split over blockIdx.y.
+// meet in LDS.  Rows wider than 256 lanes are split over blockIdx.y.  The last frame may be short (n_rows in
+// all; a stream's last block of frames).
 // ---------------------------------------------------------------------------------------
 template <bool BF16>
-__global__ __launch_bounds__(256) void frame_keys_kernel(const void* __restrict__ k, int n_f,
+__global__ __launch_bounds__(256) void frame_keys_kernel(const void* __restrict__ k, int n_f_all, int64_t n_rows,
                                                          int d_prime, int lpr_log2,
                                                          float* __restrict__ out) {
     constexpr int VEC = BF16 ? 8 : 4;
@@ -42,12 +45,13 @@ __global__ __launch_bounds__(256) void frame_keys_kernel(const void* __restrict_
     const int lpr = 1 << lpr_log2, n_rg = 256 >> lpr_log2;
     const int cl = threadIdx.x & (lpr - 1), rg = threadIdx.x >> lpr_log2;
     const int col = (blockIdx.y * lpr + cl) * VEC;
-    const int64_t frame = blockIdx.x;
+    const int64_t frame = blockIdx.x, row0 = frame * n_f_all;
+    const int n_f = n_rows - row0 < n_f_all ? (int)(n_rows - row0) : n_f_all;
     float acc[VEC];
 #pragma unroll
     for (int i = 0; i < VEC; ++i) acc[i] = 0.f;
     if (col < d_prime) {
-        const char* base = static_cast<const char*>(k) + ((frame * n_f) * (int64_t)d_prime + col) * ES;
+        const char* base = static_cast<const char*>(k) + (row0 * (int64_t)d_prime + col) * ES;
         const int64_t pitch = (int64_t)d_prime * ES;
         auto add = [&](const u32x4& w) {
             if (BF16) {
@@ -87,72 +91,77 @@ __global__ __launch_bounds__(256) void frame_keys_kernel(const void* __restrict_
 // ---------------------------------------------------------------------------------------
 // Question vector (the mean of the question's N_q query vectors; the G query heads of a KV
 // group averaged so that the vector has D' = Hkv * D entries, like a frame vector).
-// One workgroup per (question, KV group): its columns are the G * D contiguous elements of
-// that group in every token row.  16-byte loads, fp32 sums, the row groups' partial sums and
-// then the G heads meet in LDS.
+// One workgroup per (question, KV group, 128 bytes of a head vector): 8 lanes cover those bytes of a
+// head, the G heads lie side by side and the threads that are left take further token rows.  A
+// thread's loads leave together, up to 16 of them (the rows past the end are masked, not looped
+// over one by one: each turn of such a loop costs a memory round trip).  What bounds it is that one
+// round trip: 28 questions of 48 tokens 8.9 us with a workgroup per (question, KV group) and a loop over the
+// last 8 rows, 4.2 so; 64 questions of 32 tokens at 64/8/128 (33.5 MB) 11 and 9.9.
 // ---------------------------------------------------------------------------------------
-constexpr int POOL_MAX_COLS = 4096;            // G * D per KV group that fits the LDS buffer
+constexpr int POOL_THREADS = 512;
+constexpr int POOL_LANES = 8;                  // 16-byte lanes per head
 
 template <bool BF16>
-__global__ __launch_bounds__(256) void pool_question_kernel(const void* __restrict__ q, int n_q_tokens, int hq,
-                                                            int hkv, int d, float* __restrict__ q_vec) {
+__global__ __launch_bounds__(POOL_THREADS) void pool_question_kernel(const void* __restrict__ q, int n_q_tokens, int hq,
+                                                                     int hkv, int d, float* __restrict__ q_vec) {
     constexpr int VEC = BF16 ? 8 : 4;
     constexpr int ES = BF16 ? 2 : 4;
-    __shared__ float red[256 * VEC];
-    __shared__ float colsum[POOL_MAX_COLS];
-    const int g_sz = hq / hkv, cols = g_sz * d;
-    const int lpr = cols / VEC;                      // 16-byte lanes per row of this group's columns
-    const int lw = lpr < 256 ? lpr : 256;            // lanes working on a row at a time
-    const int n_rg = 256 / lw;                       // row groups
-    const int cl = threadIdx.x % lw, rg = threadIdx.x / lw;
+    constexpr int COLS = POOL_LANES * VEC;           // columns of this workgroup
+    constexpr int PARTS = POOL_THREADS / COLS;
+    __shared__ float red[POOL_THREADS * VEC];        // [thread / 8][column]
+    __shared__ float part[PARTS][COLS];
+    const int g_sz = hq / hkv;
+    const int gw = g_sz < POOL_THREADS / POOL_LANES ? g_sz : POOL_THREADS / POOL_LANES;   // heads side by side
+    const int n_rg = POOL_THREADS / (POOL_LANES * gw);                                    // row groups
+    const int lane8 = threadIdx.x % POOL_LANES, slot = threadIdx.x / POOL_LANES;
+    const int gl = slot % gw, rg = slot / gw;
     const int64_t pitch = (int64_t)hq * d * ES;
-    const char* base = static_cast<const char*>(q) + (int64_t)blockIdx.x * n_q_tokens * pitch +
-                       (int64_t)blockIdx.y * cols * ES;
-    for (int c0 = 0; c0 < lpr; c0 += lw) {
-        float acc[VEC];
+    const int col = (blockIdx.z * POOL_LANES + lane8) * VEC;
+    float acc[VEC];
 #pragma unroll
-        for (int i = 0; i < VEC; ++i) acc[i] = 0.f;
-        const bool on = rg < n_rg && c0 + cl < lpr;
-        if (on) {
-            const char* col = base + (int64_t)(c0 + cl) * 16;
+    for (int i = 0; i < VEC; ++i) acc[i] = 0.f;
+    if (rg < n_rg && col < d) {
+        for (int g = gl; g < g_sz; g += gw) {
+            const char* base = static_cast<const char*>(q) + (int64_t)blockIdx.x * n_q_tokens * pitch +
+                               ((int64_t)(blockIdx.y * g_sz + g) * d + col) * ES;
             constexpr int U = 16;
-            auto add = [&](const u32x4& w) {
-                if (BF16) {
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        acc[2 * i] += bf16_lo(w[i]);
-                        acc[2 * i + 1] += bf16_hi(w[i]);
-                    }
-                } else {
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) acc[i] += __uint_as_float(w[i]);
-                }
-            };
-            int j = rg;
-            for (; j + n_rg * (U - 1) < n_q_tokens; j += n_rg * U) {
+            for (int j0 = rg; j0 < n_q_tokens; j0 += n_rg * U) {
                 u32x4 w[U];
 #pragma unroll
-                for (int u = 0; u < U; ++u) w[u] = *reinterpret_cast<const u32x4*>(col + (j + n_rg * u) * pitch);
+                for (int u = 0; u < U; ++u) {
+                    w[u] = u32x4{0u, 0u, 0u, 0u};
+                    if (j0 + n_rg * u < n_q_tokens) w[u] = *reinterpret_cast<const u32x4*>(base + (j0 + n_rg * u) * pitch);
+                }
 #pragma unroll
-                for (int u = 0; u < U; ++u) add(w[u]);
+                for (int u = 0; u < U; ++u) {
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) {
+                        if (BF16) {
+                            acc[2 * i] += bf16_lo(w[u][i]);
+                            acc[2 * i + 1] += bf16_hi(w[u][i]);
+                        } else {
+                            acc[i] += __uint_as_float(w[u][i]);
+                        }
+                    }
+                }
             }
-            for (; j < n_q_tokens; j += n_rg) add(*reinterpret_cast<const u32x4*>(col + j * pitch));
         }
-#pragma unroll
-        for (int i = 0; i < VEC; ++i) red[threadIdx.x * VEC + i] = acc[i];
-        __syncthreads();
-        for (int c = threadIdx.x; c < lw * VEC; c += 256) {
-            float sum = 0.f;
-            for (int g = 0; g < n_rg; ++g) sum += red[(g * lw) * VEC + c];
-            if (c0 * VEC + c < cols) colsum[c0 * VEC + c] = sum;
-        }
-        __syncthreads();
     }
-    const float inv = 1.f / ((float)g_sz * (float)n_q_tokens);
-    for (int dd = threadIdx.x; dd < d; dd += 256) {
-        float sum = 0.f;
-        for (int g = 0; g < g_sz; ++g) sum += colsum[g * d + dd];
-        q_vec[(int64_t)blockIdx.x * hkv * d + (int64_t)blockIdx.y * d + dd] = sum * inv;
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) red[threadIdx.x * VEC + i] = acc[i];
+    __syncthreads();
+    const int cc = threadIdx.x % COLS, pt = threadIdx.x / COLS;
+    float sum = 0.f;
+#pragma unroll
+    for (int e = 0; e < POOL_THREADS / POOL_LANES / PARTS; ++e) sum += red[(pt + e * PARTS) * COLS + cc];
+    part[pt][cc] = sum;
+    __syncthreads();
+    const int dd = blockIdx.z * COLS + threadIdx.x;
+    if (threadIdx.x < COLS && dd < d) {
+        sum = 0.f;
+#pragma unroll
+        for (int e = 0; e < PARTS; ++e) sum += part[e][threadIdx.x];
+        q_vec[((int64_t)blockIdx.x * hkv + blockIdx.y) * d + dd] = sum * (1.f / ((float)g_sz * (float)n_q_tokens));
     }
 }
 
@@ -240,36 +249,6 @@ __device__ inline void topk_block(const float* s, int n_frames, int k, int32_t* 
         for (int f = tid; f < k; f += TOPK_THREADS) out[f] = f < n_frames ? f : -1;
         if (tid == 0 && n_sel_q) *n_sel_q = n_frames;
         return;
-    }
-
-    // Up to 256 frames (one per thread): count, for every frame, the frames with a higher key - all
-    // keys in LDS, read as broadcasts - and take those with fewer than k above them.  That is the
-    // answer unless equal keys straddle the cut, which shows as more than k taken; then (rarely)
-    // the radix select below decides.
-    if (n_frames <= TOPK_THREADS) {
-        const int n4 = (n_frames + 3) >> 2;        // keys are read four at a time; key 0 pads the tail
-        for (int f = tid; f < n4 * 4; f += TOPK_THREADS) keys[f] = f < n_frames ? order_key(s[f]) : 0u;
-        __syncthreads();
-        const uint4* keys4 = reinterpret_cast<const uint4*>(keys);
-        const uint32_t mine = tid < n_frames ? keys[tid] : 0xFFFFFFFFu;
-        int above = 0;                             // padding keys (0) are above nothing
-#pragma unroll 8
-        for (int j4 = 0; j4 < n4; ++j4) {
-            const uint4 o = keys4[j4];
-            above += o.x > mine;
-            above += o.y > mine;
-            above += o.z > mine;
-            above += o.w > mine;
-        }
-        const bool take = tid < n_frames && above < k;
-        uint64_t tot;
-        const uint64_t pre = block_excl_scan((uint64_t)take, wave_tot, tot);
-        if ((int)tot == k) {                       // uniform over the block
-            if (take) out[(int)pre] = tid;
-            if (tid == 0 && n_sel_q) *n_sel_q = k;
-            return;
-        }
-        __syncthreads();                           // keys[] is laid out anew below
     }
 
     // Up to 4096 frames the keys live in LDS (frame f at [f % SPAN][f / SPAN], which both the
@@ -389,7 +368,7 @@ __global__ __launch_bounds__(SEL_THREADS) void topk_groupmax_kernel(const float*
     __shared__ uint32_t gmax[SEL_GROUPS];
     __shared__ __attribute__((aligned(16))) uint64_t cand[SEL_MAX_FRAMES];
     __shared__ int32_t rank_of[SEL_MAX_FRAMES];
-    __shared__ int32_t sel[SEL_MAX_K];
+    __shared__ __attribute__((aligned(16))) int32_t sel[SEL_MAX_K];
     __shared__ uint32_t sh_t0;
     __shared__ int32_t n_cand, n_taken;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -405,7 +384,11 @@ __global__ __launch_bounds__(SEL_THREADS) void topk_groupmax_kernel(const float*
         key[j] = f < n_frames ? order_key(s[f]) : 0u;        // 0 lies below the key of every number
     }
 #pragma unroll
-    for (int j = 0; j < KPT; ++j) rank_of[tid + j * SEL_THREADS] = 0;
+    for (int j = 0; j < KPT; ++j) {
+        rank_of[tid + j * SEL_THREADS] = 0;
+        cand[tid + j * SEL_THREADS] = 0;                     // ranks before no candidate
+    }
+    if (tid < SEL_MAX_K) sel[tid] = 0x7FFFFFFF;
     if (tid < SEL_GROUPS) gmax[tid] = 0u;
     if (tid == 0) { n_cand = 0; n_taken = 0; }
     __syncthreads();
@@ -414,15 +397,22 @@ __global__ __launch_bounds__(SEL_THREADS) void topk_groupmax_kernel(const float*
     for (int j = 1; j < KPT; ++j) mine = max(mine, key[j]);
     atomicMax(&gmax[tid & (SEL_GROUPS - 1)], mine);          // tid mod 128 == the group of all its keys
     __syncthreads();
-    if (tid < SEL_GROUPS) {
-        const uint32_t v = gmax[tid];
+    {                                                        // rank of every group's maximum, a slice of the others per thread
+        constexpr int SLICE_G = SEL_GROUPS * SEL_GROUPS / SEL_THREADS;
+        const int g = tid & (SEL_GROUPS - 1), j0 = tid / SEL_GROUPS * SLICE_G;
+        const uint32_t v = gmax[g];
         int above = 0;
-#pragma unroll 16
-        for (int j = 0; j < SEL_GROUPS; ++j) {
+#pragma unroll
+        for (int j = j0; j < j0 + SLICE_G; ++j) {
             const uint32_t o = gmax[j];                      // same address in every lane: a broadcast
-            above += (o > v) || (o == v && j < tid);
+            above += (o > v) || (o == v && j < g);
         }
-        if (above == k - 1) sh_t0 = v;
+        atomicAdd(&rank_of[g], above);
+    }
+    __syncthreads();
+    if (tid < SEL_GROUPS) {
+        if (rank_of[tid] == k - 1) sh_t0 = gmax[tid];
+        rank_of[tid] = 0;
     }
     __syncthreads();
     const uint32_t t0 = sh_t0;
@@ -448,19 +438,18 @@ __global__ __launch_bounds__(SEL_THREADS) void topk_groupmax_kernel(const float*
     const int n_slices = n_up < SEL_THREADS ? SEL_THREADS / n_up : 1;
     const int sl = __builtin_amdgcn_readfirstlane(tid / n_up);
     if (sl < n_slices) {
-        const int j0 = (int)((int64_t)n * sl / n_slices), j1 = (int)((int64_t)n * (sl + 1) / n_slices);
+        // slices in whole groups of eight: the last one reads into the zeros behind the list
+        const int n8 = (n + 7) >> 3, j0 = n8 * sl / n_slices * 8, j1 = n8 * (sl + 1) / n_slices * 8;
         for (int i = tid - sl * n_up; i < n; i += SEL_THREADS) {
             const uint64_t ci = cand[i];
             int above = 0;
-            int j = j0;
-            for (; j + 8 <= j1; j += 8) {
+            for (int j = j0; j < j1; j += 8) {
                 uint64_t c[8];
 #pragma unroll
                 for (int u = 0; u < 8; ++u) c[u] = cand[j + u];
 #pragma unroll
                 for (int u = 0; u < 8; ++u) above += c[u] > ci;
             }
-            for (; j < j1; ++j) above += cand[j] > ci;
             if (n_slices > 1) atomicAdd(&rank_of[i], above);
             else rank_of[i] = above;
         }
@@ -471,9 +460,66 @@ __global__ __launch_bounds__(SEL_THREADS) void topk_groupmax_kernel(const float*
     __syncthreads();
     if (tid < k) {
         const int32_t f = sel[tid];
+        // all 64 places (those past k hold no frame): reads that leave together, where a loop over k would wait for each
+        const int4* sel4 = reinterpret_cast<const int4*>(sel);
         int before = 0;
-        for (int j = 0; j < k; ++j) before += sel[j] < f;
+#pragma unroll
+        for (int j = 0; j < SEL_MAX_K / 4; ++j) {
+            const int4 o = sel4[j];
+            before += (o.x < f) + (o.y < f) + (o.z < f) + (o.w < f);
+        }
         out[before] = f;
+    }
+    if (tid == 0 && n_sel) n_sel[qi] = k;
+}
+
+// ---------------------------------------------------------------------------------------
+// Top-k of up to 256 frames: the rank of every frame by (key descending, frame ascending) counted
+// against all others, the pairs spread over 1024 threads, and the frames of rank < k written in order.
+// One workgroup per question.  Bound by the comparisons' issue slots and the one round trip for the scores:
+// 256 frames 4.7 us with one thread per frame, 4.0 us so.
+// ---------------------------------------------------------------------------------------
+constexpr int RANK_MAX_FRAMES = 256;
+constexpr int RANK_THREADS = 1024;
+
+__global__ __launch_bounds__(RANK_THREADS) void topk_rank_kernel(const float* __restrict__ scores, int n_frames, int k,
+                                                                 int32_t* __restrict__ idx, int32_t* __restrict__ n_sel) {
+    __shared__ uint64_t cand[RANK_MAX_FRAMES];               // key in the high half, ~frame in the low half
+    __shared__ int32_t rank_of[RANK_MAX_FRAMES];
+    __shared__ uint64_t taken[RANK_MAX_FRAMES / 64];
+    const int tid = threadIdx.x;
+    const int64_t qi = blockIdx.x;
+    if (tid < RANK_MAX_FRAMES) {
+        cand[tid] = tid < n_frames ? ((uint64_t)order_key(scores[qi * n_frames + tid]) << 32) | (uint32_t)~tid : 0u;
+        rank_of[tid] = 0;
+    }
+    __syncthreads();
+    const int n_up = (n_frames + 63) & ~63;                  // threads per slice of the others, whole waves
+    const int n_slices = RANK_THREADS / n_up;
+    const int sl = __builtin_amdgcn_readfirstlane(tid / n_up), i = tid - sl * n_up;
+    if (sl < n_slices) {
+        const int n8 = (n_frames + 7) >> 3, j0 = n8 * sl / n_slices * 8, j1 = n8 * (sl + 1) / n_slices * 8;
+        const uint64_t ci = cand[i];
+        int above = 0;
+        for (int j = j0; j < j1; j += 8) {
+            uint64_t c[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) c[u] = cand[j + u];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) above += c[u] > ci;
+        }
+        atomicAdd(&rank_of[i], above);
+    }
+    __syncthreads();
+    const bool take = tid < n_frames && rank_of[tid & (RANK_MAX_FRAMES - 1)] < k;
+    const uint64_t mask = __builtin_amdgcn_ballot_w64(take);
+    if (tid < RANK_MAX_FRAMES && (tid & 63) == 0) taken[tid >> 6] = mask;
+    __syncthreads();
+    if (take) {
+        int pos = __popcll(mask & ((1ull << (tid & 63)) - 1ull));
+#pragma unroll
+        for (int w = 0; w < RANK_MAX_FRAMES / 64; ++w) pos += w < (tid >> 6) ? __popcll(taken[w]) : 0;
+        idx[qi * k + pos] = tid;
     }
     if (tid == 0 && n_sel) n_sel[qi] = k;
 }
@@ -615,35 +661,40 @@ __global__ __launch_bounds__(SM_WAVES * 64) void score_shared_mfma_kernel(
     float vv = 0.f, qq = 0.f;
 #pragma unroll
     for (int d = 0; d < DEPTH; ++d) fetch(xa[d], xb[d], d * SM_COLS);
-    // Whole rounds of DEPTH slabs, no branch inside a round: slabs past D' are fetched from
-    // clamped columns and enter the tiles as zeros.
+    // Rounds of DEPTH slabs, no branch inside a round (columns past D' enter the tiles as zeros); the last
+    // round fetches nothing and ends with the last slab.
     const int n_rounds = (d_prime + DEPTH * SM_COLS - 1) / (DEPTH * SM_COLS);
-    for (int round = 0; round < n_rounds; ++round) {
+    auto slab = [&](int d, int cc, auto more) __attribute__((always_inline)) {
 #pragma unroll
-        for (int d = 0; d < DEPTH; ++d) {
-            const int cc = (round * DEPTH + d) * SM_COLS;
-#pragma unroll
-            for (int u = 0; u < PER; ++u) {
-                const int i = threadIdx.x + u * SM_WAVES * 64;
-                const int off = (i / (SM_COLS / 4)) * SM_PITCH + (i % (SM_COLS / 4)) * 4;
-                const bool on = cc + (i % (SM_COLS / 4)) * 4 < d_prime;   // columns past D' count as zero
-                *reinterpret_cast<f32x4*>(tile_a + off) = on ? xa[d][u] : zero;
-                *reinterpret_cast<f32x4*>(tile_b + off) = on ? xb[d][u] : zero;
-            }
-            __syncthreads();
-            fetch(xa[d], xb[d], cc + DEPTH * SM_COLS);
-#pragma unroll
-            for (int g = 0; g < SM_COLS / 8 / SM_WAVES; ++g) {           // this wave's groups of 8 columns
-                const int off = r * SM_PITCH + (wave * (SM_COLS / 8 / SM_WAVES) + g) * 8 + 4 * h;
-                const f32x4 a = *reinterpret_cast<const f32x4*>(tile_a + off);
-                const f32x4 b = *reinterpret_cast<const f32x4*>(tile_b + off);
-                vv += a.x * a.x + a.y * a.y + a.z * a.z + a.w * a.w;
-                qq += b.x * b.x + b.y * b.y + b.z * b.z + b.w * b.w;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[j], b[j], acc[j], 0, 0, 0);
-            }
-            __syncthreads();
+        for (int u = 0; u < PER; ++u) {
+            const int i = threadIdx.x + u * SM_WAVES * 64;
+            const int off = (i / (SM_COLS / 4)) * SM_PITCH + (i % (SM_COLS / 4)) * 4;
+            const bool on = cc + (i % (SM_COLS / 4)) * 4 < d_prime;
+            *reinterpret_cast<f32x4*>(tile_a + off) = on ? xa[d][u] : zero;
+            *reinterpret_cast<f32x4*>(tile_b + off) = on ? xb[d][u] : zero;
         }
+        __syncthreads();
+        if (decltype(more)::value) fetch(xa[d], xb[d], cc + DEPTH * SM_COLS);
+#pragma unroll
+        for (int g = 0; g < SM_COLS / 8 / SM_WAVES; ++g) {               // this wave's groups of 8 columns
+            const int off = r * SM_PITCH + (wave * (SM_COLS / 8 / SM_WAVES) + g) * 8 + 4 * h;
+            const f32x4 a = *reinterpret_cast<const f32x4*>(tile_a + off);
+            const f32x4 b = *reinterpret_cast<const f32x4*>(tile_b + off);
+            vv += a.x * a.x + a.y * a.y + a.z * a.z + a.w * a.w;
+            qq += b.x * b.x + b.y * b.y + b.z * b.z + b.w * b.w;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) acc[j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[j], b[j], acc[j], 0, 0, 0);
+        }
+        __syncthreads();
+    };
+    for (int round = 0; round + 1 < n_rounds; ++round) {
+#pragma unroll
+        for (int d = 0; d < DEPTH; ++d) slab(d, (round * DEPTH + d) * SM_COLS, std::true_type());
+    }
+#pragma unroll
+    for (int d = 0; d < DEPTH; ++d) {
+        const int cc = ((n_rounds - 1) * DEPTH + d) * SM_COLS;
+        if (cc < d_prime) slab(d, cc, std::false_type());
     }
     float* part = lds;                               // [wave][16][64]
 #pragma unroll
@@ -671,20 +722,27 @@ __global__ __launch_bounds__(SM_WAVES * 64) void score_shared_mfma_kernel(
 
 }  // namespace
 
-hipError_t frame_keys_launch(const void* k, int n_frames, int tokens_per_frame, int d_prime,
-                             int dtype, float* frame_keys, hipStream_t stream) {
+namespace {
+
+// one vector per `per` rows, n_rows in all
+hipError_t mean_rows_launch(const void* k, int64_t n_rows, int per, int d_prime, int dtype, float* out, hipStream_t stream) {
     const int vec = dtype == REKV_BF16 ? 8 : 4;
     const int lanes = (d_prime + vec - 1) / vec;          // 16-byte lanes per key row
     int lpr_log2 = 0;
     while ((1 << lpr_log2) < lanes && lpr_log2 < 8) ++lpr_log2;
-    dim3 grid((unsigned)n_frames, (unsigned)((lanes + (1 << lpr_log2) - 1) >> lpr_log2));
+    dim3 grid((unsigned)((n_rows + per - 1) / per), (unsigned)((lanes + (1 << lpr_log2) - 1) >> lpr_log2));
     if (dtype == REKV_BF16)
-        hipLaunchKernelGGL(frame_keys_kernel<true>, grid, dim3(256), 0, stream, k, tokens_per_frame,
-                           d_prime, lpr_log2, frame_keys);
+        hipLaunchKernelGGL(frame_keys_kernel<true>, grid, dim3(256), 0, stream, k, per, n_rows, d_prime, lpr_log2, out);
     else
-        hipLaunchKernelGGL(frame_keys_kernel<false>, grid, dim3(256), 0, stream, k, tokens_per_frame,
-                           d_prime, lpr_log2, frame_keys);
+        hipLaunchKernelGGL(frame_keys_kernel<false>, grid, dim3(256), 0, stream, k, per, n_rows, d_prime, lpr_log2, out);
     return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t frame_keys_launch(const void* k, int n_frames, int tokens_per_frame, int d_prime,
+                             int dtype, float* frame_keys, hipStream_t stream) {
+    return mean_rows_launch(k, (int64_t)n_frames * tokens_per_frame, tokens_per_frame, d_prime, dtype, frame_keys, stream);
 }
 
 namespace {
@@ -721,15 +779,9 @@ __global__ __launch_bounds__(256) void expand_blocks_kernel(const int32_t* __res
 
 hipError_t block_keys_launch(const float* frame_keys, int n_frames, int b, int d_prime, float* block_keys,
                              hipStream_t stream) {
-    // a block vector is the mean of b rows of the fp32 frame table: the frame-vector kernel
-    // with b "tokens" per "frame"; the stream's short last block gets a launch of its own
-    const int n_full = n_frames / b, rest = n_frames % b;
-    hipError_t e = hipSuccess;
-    if (n_full > 0) e = frame_keys_launch(frame_keys, n_full, b, d_prime, REKV_F32, block_keys, stream);
-    if (e == hipSuccess && rest > 0)
-        e = frame_keys_launch(frame_keys + (int64_t)n_full * b * d_prime, 1, rest, d_prime, REKV_F32,
-                              block_keys + (int64_t)n_full * d_prime, stream);
-    return e;
+    // a block vector is the mean of b rows of the fp32 frame table: the frame-vector kernel with b "tokens" per
+    // "frame" (a last block of fewer frames in a launch of its own cost 2 us of kernel time more)
+    return mean_rows_launch(frame_keys, n_frames, b, d_prime, REKV_F32, block_keys, stream);
 }
 
 hipError_t expand_blocks_launch(const int32_t* block_idx, int n_questions, int k_blocks, int b, int n_frames,
@@ -744,20 +796,26 @@ hipError_t retrieve_launch(const RetrieveArgs& a, hipStream_t stream) {
     const float* q_vec = a.q_vec_given;
     hipError_t e = hipSuccess;
     if (!q_vec) {                      // pooled question vectors: [n_questions, D']
-        dim3 grid((unsigned)a.n_questions, (unsigned)a.n_kv_heads);
+        const int cols = POOL_LANES * (a.dtype == REKV_BF16 ? 8 : 4);
+        dim3 grid((unsigned)a.n_questions, (unsigned)a.n_kv_heads, (unsigned)((a.head_dim + cols - 1) / cols));
         if (a.dtype == REKV_BF16)
-            hipLaunchKernelGGL(pool_question_kernel<true>, grid, dim3(256), 0, stream, a.q_question, a.n_q_tokens,
+            hipLaunchKernelGGL(pool_question_kernel<true>, grid, dim3(POOL_THREADS), 0, stream, a.q_question, a.n_q_tokens,
                                a.n_q_heads, a.n_kv_heads, a.head_dim, a.q_vec);
         else
-            hipLaunchKernelGGL(pool_question_kernel<false>, grid, dim3(256), 0, stream, a.q_question, a.n_q_tokens,
+            hipLaunchKernelGGL(pool_question_kernel<false>, grid, dim3(POOL_THREADS), 0, stream, a.q_question, a.n_q_tokens,
                                a.n_q_heads, a.n_kv_heads, a.head_dim, a.q_vec);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
         q_vec = a.q_vec;
     }
-    // Four or more questions on one table: the matrix-core kernel reads the table once per 32 questions.
-    // Otherwise one pass over the (question's own) table per question.
-    if (a.frame_keys_stride == 0 && a.n_questions >= 4) {
+    // Four or more questions on one table: the matrix-core kernel reads the table once per 32 questions, the other
+    // once per question.  Below 56 MB read that way (vectors of up to 1,024 entries, whose loads all leave at once) the
+    // caches carry it: 4 to 8 us against 4.4 to 15; at 51 MB 8.0 against 11.7 us
+    // (32 questions, 777 x 512) and 10.7 against 12.9 (16, 777 x 1,024), at 66 MB 10.2 against 8.5 (64, 2,000 x 128),
+    // 9.8 against 8.8 (16, 2,000 x 512) and 13.4 against 13.0 (8, 2,000 x 1,024).
+    const bool per_question = a.n_questions < 4 ||
+        (d_prime <= 1024 && (int64_t)a.n_questions * a.n_frames * d_prime * 4 <= 56000000);
+    if (a.frame_keys_stride == 0 && !per_question) {
         dim3 grid((unsigned)((a.n_frames + SM_TILE - 1) / SM_TILE), (unsigned)((a.n_questions + SM_TILE - 1) / SM_TILE));
         hipLaunchKernelGGL(score_shared_mfma_kernel, grid, dim3(SM_WAVES * 64), 0, stream, a.frame_keys, a.n_frames,
                            d_prime, q_vec, a.n_questions, a.inv_tau, a.scores);
@@ -775,6 +833,9 @@ hipError_t retrieve_launch(const RetrieveArgs& a, hipStream_t stream) {
     if (e != hipSuccess) return e;
     if (a.n_frames >= SEL_MIN_FRAMES && a.n_frames <= SEL_MAX_FRAMES && a.k <= SEL_MAX_K && a.k < a.n_frames)
         hipLaunchKernelGGL(topk_groupmax_kernel<1024>, dim3((unsigned)a.n_questions), dim3(1024), 0, stream,
+                           a.scores, a.n_frames, a.k, a.idx, a.n_sel);
+    else if (a.n_frames <= RANK_MAX_FRAMES && a.k < a.n_frames)
+        hipLaunchKernelGGL(topk_rank_kernel, dim3((unsigned)a.n_questions), dim3(RANK_THREADS), 0, stream,
                            a.scores, a.n_frames, a.k, a.idx, a.n_sel);
     else
         hipLaunchKernelGGL(topk_kernel, dim3((unsigned)a.n_questions), dim3(TOPK_THREADS), 0, stream,
