@@ -9,12 +9,17 @@
 
 #include "common.h"
 
+struct Buffer {
+    void* p;
+    size_t bytes;
+};
+
 struct rekv_ctx {
     rekv_shape shape;
     float scale;
     int device;
-    void* ws;             // workspace: split-KV partials, or pooled questions + scores
-    size_t ws_bytes;
+    Buffer ws;            // split-KV partials
+    Buffer retrieval_ws;  // pooled questions + scores
     uint32_t* tickets;    // arrival counters of split attention launches, zero between launches
     int ticket_slot;      // their slot of the static pool, -1: an allocation of its own
     bool tickets_used;    // a launch has been given them
@@ -122,29 +127,33 @@ size_t elem_size(const rekv_ctx* c) { return c->shape.dtype == REKV_BF16 ? 2 : 4
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
-// Grows the context's workspace.  Freeing the old block waits for the device, so work that
+// Grows one of the context's workspaces.  Freeing the old block waits for the device, so work that
 // still reads it has finished.
-rekv_status reserve(rekv_ctx* c, size_t bytes) {
-    if (bytes <= c->ws_bytes) return REKV_OK;
-    if (c->ws) {
-        hipError_t e = hipFree(c->ws);
-        c->ws = nullptr;
-        c->ws_bytes = 0;
+rekv_status reserve(rekv_ctx* c, Buffer* ws, size_t bytes, size_t least) {
+    if (bytes <= ws->bytes) return REKV_OK;
+    if (ws->p) {
+        hipError_t e = hipFree(ws->p);
+        ws->p = nullptr;
+        ws->bytes = 0;
         if (e != hipSuccess) return fail_hip(c, "hipFree(workspace)", e);
     }
-    // 8 MiB to start with: scores and pooled questions, and every launch of attention_wave.hip, fit, so
-    // most contexts allocate once (growing costs a hipFree, a hipMalloc and the device's idling)
-    if (bytes < (size_t(8) << 20)) bytes = size_t(8) << 20;
+    if (bytes < least) bytes = least;
     bytes = (bytes + (size_t(1) << 20) - 1) & ~((size_t(1) << 20) - 1);
-    hipError_t e = hipMalloc(&c->ws, bytes);
+    hipError_t e = hipMalloc(&ws->p, bytes);
     if (e != hipSuccess) {
         (void)hipGetLastError();
-        c->ws = nullptr;
+        ws->p = nullptr;
         return fail(c, REKV_ERR_NOMEM, "workspace of %zu bytes: %s", bytes, hipGetErrorString(e));
     }
-    c->ws_bytes = bytes;
+    ws->bytes = bytes;
     return REKV_OK;
 }
+
+// What a workspace starts with.  Attention: every launch of attention_wave.hip fits into 8 MiB, so that most contexts
+// allocate once (growing costs a hipFree, a hipMalloc and the device's idling).  Retrieval has a block of its own, so
+// that a question's first attention does not wait for the retrieval to free it, and a context that only needs
+// scores does not pay for the larger one.
+constexpr size_t ATTENTION_WS = size_t(8) << 20, RETRIEVAL_WS = size_t(1) << 20;
 
 // fixed_ws != NULL: the launch may use only that buffer of fixed_ws_bytes (no allocation);
 // otherwise the context's workspace grows as needed.
@@ -165,9 +174,9 @@ rekv_status run_attention(rekv_ctx* c, const rekv::AttnProblem& p, hipStream_t s
             return fail(c, REKV_ERR_UNSUPPORTED, "this launch needs %zu bytes of scratch, the static buffer holds %zu",
                         plan.workspace_bytes, fixed_ws_bytes);
     } else {
-        rekv_status s = reserve(c, plan.workspace_bytes);
+        rekv_status s = reserve(c, &c->ws, plan.workspace_bytes, ATTENTION_WS);
         if (s != REKV_OK) return s;
-        ws = c->ws;
+        ws = c->ws.p;
     }
     c->tickets_used |= plan.wave != 0;
     hipError_t e = plan.wave ? rekv::attn_wave_launch(p, plan, ws, c->tickets, stream)
@@ -226,7 +235,8 @@ void rekv_destroy(rekv_ctx* c) {
     }
     if (c->ev_main) (void)hipEventDestroy(c->ev_main);
     if (c->ev_side) (void)hipEventDestroy(c->ev_side);
-    if (c->ws) (void)hipFree(c->ws);
+    if (c->ws.p) (void)hipFree(c->ws.p);
+    if (c->retrieval_ws.p) (void)hipFree(c->retrieval_ws.p);
     give_tickets(c);
     if (c->idx_host) (void)hipHostFree(c->idx_host);
     delete c;
@@ -400,7 +410,7 @@ rekv_status rekv_retrieve_topk(rekv_ctx* c, const float* frame_keys, int64_t fra
     if (n_questions > 65535) return fail(c, REKV_ERR_UNSUPPORTED, "rekv_retrieve_topk: at most 65535 questions per call");
     const size_t qv_bytes = ((size_t)n_questions * d_prime * sizeof(float) + 255) & ~size_t(255);
     const size_t sc_bytes = scores ? 0 : (size_t)n_questions * n_frames * sizeof(float);
-    rekv_status s = reserve(c, qv_bytes + sc_bytes);
+    rekv_status s = reserve(c, &c->retrieval_ws, qv_bytes + sc_bytes, RETRIEVAL_WS);
     if (s != REKV_OK) return s;
     rekv::RetrieveArgs a;
     a.frame_keys = frame_keys; a.frame_keys_stride = frame_keys_stride; a.n_frames = n_frames;
@@ -408,8 +418,8 @@ rekv_status rekv_retrieve_topk(rekv_ctx* c, const float* frame_keys, int64_t fra
     a.n_q_heads = c->shape.n_q_heads; a.n_kv_heads = c->shape.n_kv_heads; a.head_dim = c->shape.head_dim;
     a.dtype = c->shape.dtype;
     a.idx = idx; a.n_sel = n_sel;
-    a.q_vec = static_cast<float*>(c->ws);
-    a.scores = scores ? scores : reinterpret_cast<float*>(static_cast<char*>(c->ws) + qv_bytes);
+    a.q_vec = static_cast<float*>(c->retrieval_ws.p);
+    a.scores = scores ? scores : reinterpret_cast<float*>(static_cast<char*>(c->retrieval_ws.p) + qv_bytes);
     a.q_vec_given = nullptr; a.dim = 0; a.inv_tau = 1.f;
     hipError_t e = rekv::retrieve_launch(a, static_cast<hipStream_t>(stream));
     return e == hipSuccess ? REKV_OK : fail_hip(c, "retrieval launch", e);
@@ -428,7 +438,7 @@ rekv_status rekv_retrieve_external(rekv_ctx* c, const float* frame_emb, int32_t 
                     n_frames, n_questions, k, dim, (double)tau);
     if (n_questions > 65535) return fail(c, REKV_ERR_UNSUPPORTED, "rekv_retrieve_external: at most 65535 questions per call");
     if (!scores) {
-        rekv_status s = reserve(c, (size_t)n_questions * n_frames * sizeof(float));
+        rekv_status s = reserve(c, &c->retrieval_ws, (size_t)n_questions * n_frames * sizeof(float), RETRIEVAL_WS);
         if (s != REKV_OK) return s;
     }
     rekv::RetrieveArgs a;
@@ -436,7 +446,7 @@ rekv_status rekv_retrieve_external(rekv_ctx* c, const float* frame_emb, int32_t 
     a.frame_keys = frame_emb; a.frame_keys_stride = 0; a.n_frames = n_frames;
     a.n_questions = n_questions; a.k = k;
     a.idx = idx; a.n_sel = n_sel;
-    a.scores = scores ? scores : static_cast<float*>(c->ws);
+    a.scores = scores ? scores : static_cast<float*>(c->retrieval_ws.p);
     a.q_vec_given = q_emb; a.dim = dim; a.inv_tau = 1.f / tau;
     hipError_t e = rekv::retrieve_launch(a, static_cast<hipStream_t>(stream));
     return e == hipSuccess ? REKV_OK : fail_hip(c, "external retrieval launch", e);
