@@ -20,7 +20,7 @@ struct rekv_ctx {
     int device;
     Buffer ws;            // split-KV partials
     Buffer retrieval_ws;  // pooled questions + scores
-    uint32_t* tickets;    // arrival counters of split attention launches, zero between launches
+    uint32_t* tickets;    // arrival counters of split attention and short retrieval launches, zero between launches
     int ticket_slot;      // their slot of the static pool, -1: an allocation of its own
     bool tickets_used;    // a launch has been given them
     void* scratch;        // this device's copy of the static scratch array
@@ -421,6 +421,8 @@ rekv_status rekv_retrieve_topk(rekv_ctx* c, const float* frame_keys, int64_t fra
     a.q_vec = static_cast<float*>(c->retrieval_ws.p);
     a.scores = scores ? scores : reinterpret_cast<float*>(static_cast<char*>(c->retrieval_ws.p) + qv_bytes);
     a.q_vec_given = nullptr; a.dim = 0; a.inv_tau = 1.f;
+    a.tickets = c->tickets;
+    c->tickets_used = true;
     hipError_t e = rekv::retrieve_launch(a, static_cast<hipStream_t>(stream));
     return e == hipSuccess ? REKV_OK : fail_hip(c, "retrieval launch", e);
 }

@@ -115,6 +115,7 @@ struct RetrieveArgs {
     const float* q_vec_given;
     int32_t dim;     // vector length; 0 = Hkv * D
     float inv_tau;   // 1 for internal retrieval
+    uint32_t* tickets;   // WAVE_TICKETS zeroed words that only calls ordered on one stream use
 };
 hipError_t retrieve_launch(const RetrieveArgs& a, hipStream_t stream);
 

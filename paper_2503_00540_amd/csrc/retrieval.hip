@@ -482,15 +482,15 @@ __global__ __launch_bounds__(SEL_THREADS) void topk_groupmax_kernel(const float*
 constexpr int RANK_MAX_FRAMES = 256;
 constexpr int RANK_THREADS = 1024;
 
-__global__ __launch_bounds__(RANK_THREADS) void topk_rank_kernel(const float* __restrict__ scores, int n_frames, int k,
-                                                                 int32_t* __restrict__ idx, int32_t* __restrict__ n_sel) {
+// The whole workgroup works on one question: score(f) its scores, out its k index slots, n_sel_q its count (may be NULL).
+template <class Score>
+__device__ inline void rank_block(Score score, int n_frames, int k, int32_t* out, int32_t* n_sel_q) {
     __shared__ uint64_t cand[RANK_MAX_FRAMES];               // key in the high half, ~frame in the low half
     __shared__ int32_t rank_of[RANK_MAX_FRAMES];
     __shared__ uint64_t taken[RANK_MAX_FRAMES / 64];
     const int tid = threadIdx.x;
-    const int64_t qi = blockIdx.x;
     if (tid < RANK_MAX_FRAMES) {
-        cand[tid] = tid < n_frames ? ((uint64_t)order_key(scores[qi * n_frames + tid]) << 32) | (uint32_t)~tid : 0u;
+        cand[tid] = tid < n_frames ? ((uint64_t)order_key(score(tid)) << 32) | (uint32_t)~tid : 0u;
         rank_of[tid] = 0;
     }
     __syncthreads();
@@ -519,9 +519,16 @@ __global__ __launch_bounds__(RANK_THREADS) void topk_rank_kernel(const float* __
         int pos = __popcll(mask & ((1ull << (tid & 63)) - 1ull));
 #pragma unroll
         for (int w = 0; w < RANK_MAX_FRAMES / 64; ++w) pos += w < (tid >> 6) ? __popcll(taken[w]) : 0;
-        idx[qi * k + pos] = tid;
+        out[pos] = tid;
     }
-    if (tid == 0 && n_sel) n_sel[qi] = k;
+    if (tid == 0 && n_sel_q) *n_sel_q = k;
+}
+
+__global__ __launch_bounds__(RANK_THREADS) void topk_rank_kernel(const float* __restrict__ scores, int n_frames, int k,
+                                                                 int32_t* __restrict__ idx, int32_t* __restrict__ n_sel) {
+    const int64_t qi = blockIdx.x;
+    const float* s = scores + qi * n_frames;
+    rank_block([&](int f) { return s[f]; }, n_frames, k, idx + qi * k, n_sel ? n_sel + qi : nullptr);
 }
 
 __global__ __launch_bounds__(TOPK_THREADS) void topk_kernel(const float* __restrict__ scores,
@@ -720,6 +727,141 @@ __global__ __launch_bounds__(SM_WAVES * 64) void score_shared_mfma_kernel(
     }
 }
 
+// ---------------------------------------------------------------------------------------
+// Pooling, Eq. 2 and the selection of a short stream (up to 256 frame or block vectors of up to 1,024 entries) in one
+// launch.  A workgroup of 16 wavefronts owns 32 rows of the table, two per wavefront, whose loads leave first;
+// meanwhile it pools the whole question for itself (redundantly: it comes from the L2) into LDS.  The scores go out with
+// device-scope stores, and the workgroup that draws a question's last ticket ranks them (no cache-wide
+// fence: the stores have completed before the ticket is drawn, and the reader's loads follow its own draw; the
+// ticket words start at zero and are set back by the last arriver).
+// What bounds it is a chain of round trips, and as three launches also the host that issues them: replayed from a graph
+// a 32-token question on 256 x 512 takes 10.4 us in three launches and 10.3 in one, 5 of 23 tokens on 98 x 128
+// 9.1 and 8.3; the calls they are part of, issued one after the other, 32.3 and 29.7, 44.1 and 38.9 us.
+// ---------------------------------------------------------------------------------------
+constexpr int SHORT_ROWS = 2 * RANK_THREADS / 64;            // table rows per workgroup
+constexpr int SHORT_MAX_DIM = 1024;
+constexpr int SHORT_MAX_BLOCKS = 64;
+static_assert(SHORT_MAX_BLOCKS <= WAVE_TICKETS, "a ticket per question");
+constexpr int64_t SHORT_MAX_QUESTION = 256 << 10;
+
+template <bool BF16, int NI>                                 // D' <= NI * 256
+__global__ __launch_bounds__(RANK_THREADS) void retrieve_short_kernel(RetrieveArgs a, int d_prime) {
+    constexpr int VEC = BF16 ? 8 : 4;
+    constexpr int ES = BF16 ? 2 : 4;
+    __shared__ __attribute__((aligned(16))) float red[RANK_THREADS * VEC];     // [part][D']
+    __shared__ __attribute__((aligned(16))) float qv[NI * 256];
+    __shared__ uint32_t sh_last;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int64_t qi = blockIdx.y;
+    const int f0 = blockIdx.x * SHORT_ROWS + wave * 2;
+
+    // the rows (past the table: its last row again), in flight while the question is pooled
+    const float* table = a.frame_keys + qi * a.frame_keys_stride;
+    const float4 zero4 = make_float4(0.f, 0.f, 0.f, 0.f);
+    float4 x[2][NI];
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+        const int f = f0 + r < a.n_frames ? f0 + r : a.n_frames - 1;
+#pragma unroll
+        for (int it = 0; it < NI; ++it) {
+            const int i = lane * 4 + it * 256;
+            x[r][it] = i < d_prime ? load_stream(table + (int64_t)f * d_prime + i) : zero4;
+        }
+    }
+
+    // ---- the question: a thread owns 16 bytes of D' and every n_parts-th (token, head of the group)
+    const int g_sz = a.n_q_heads / a.n_kv_heads, d = a.head_dim;
+    const int chunks = d_prime / VEC, n_parts = RANK_THREADS / chunks;
+    const int ch = tid % chunks, part = tid / chunks;
+    const int kvh = ch * VEC / d, col = ch * VEC - kvh * d;
+    const char* base = static_cast<const char*>(a.q_question) +
+        (((int64_t)qi * a.n_q_tokens * a.n_q_heads + kvh * g_sz) * d + col) * ES;
+    const int n_pairs = a.n_q_tokens * g_sz;
+    // from one pair of a thread to its next, without a division per load
+    const int head_b = d * ES, step_t = n_parts / g_sz, step_g = n_parts - step_t * g_sz;
+    const int step_b = (step_t * a.n_q_heads + step_g) * head_b, wrap_b = (a.n_q_heads - g_sz) * head_b;
+    int g = part % g_sz, off = (part / g_sz * a.n_q_heads + g) * head_b;
+    float acc[VEC];
+#pragma unroll
+    for (int i = 0; i < VEC; ++i) acc[i] = 0.f;
+    if (part < n_parts) {
+        constexpr int U = 8;
+        for (int e0 = part; e0 < n_pairs; e0 += n_parts * U) {
+            u32x4 w[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                w[u] = u32x4{0u, 0u, 0u, 0u};
+                if (e0 + u * n_parts < n_pairs) w[u] = *reinterpret_cast<const u32x4*>(base + off);
+                g += step_g;
+                off += step_b;
+                if (g >= g_sz) {
+                    g -= g_sz;
+                    off += wrap_b;
+                }
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    if (BF16) {
+                        acc[2 * i] += bf16_lo(w[u][i]);
+                        acc[2 * i + 1] += bf16_hi(w[u][i]);
+                    } else {
+                        acc[i] += __uint_as_float(w[u][i]);
+                    }
+                }
+        }
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) red[part * d_prime + ch * VEC + i] = acc[i];
+    }
+    __syncthreads();
+    if (tid < NI * 256) {
+        float sum = 0.f;
+        if (tid < d_prime) {
+#pragma unroll 8
+            for (int p = 0; p < n_parts; ++p) sum += red[p * d_prime + tid];
+        }
+        qv[tid] = sum * (1.f / ((float)g_sz * (float)a.n_q_tokens));
+    }
+    __syncthreads();
+
+    // ---- two cosines per wavefront
+    float dot[2] = {0.f, 0.f}, vv[2] = {0.f, 0.f}, qq = 0.f;
+#pragma unroll
+    for (int it = 0; it < NI; ++it) {
+        const float4 y = *reinterpret_cast<const float4*>(qv + lane * 4 + it * 256);
+        qq += y.x * y.x + y.y * y.y + y.z * y.z + y.w * y.w;
+#pragma unroll
+        for (int r = 0; r < 2; ++r) {
+            const float4 v = x[r][it];
+            vv[r] += v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
+            dot[r] += v.x * y.x + v.y * y.y + v.z * y.z + v.w * y.w;
+        }
+    }
+    const float dsum = transpose_reduce<2>(dot, lane);       // row lane / 32
+    const float vsum = transpose_reduce<2>(vv, lane);
+    qq = wave_sum(qq);
+    float* scores = a.scores + qi * a.n_frames;
+    if ((lane & 31) == 0 && f0 + (lane >> 5) < a.n_frames) {
+        const float den = sqrtf(vsum) * sqrtf(qq);
+        __hip_atomic_store(scores + f0 + (lane >> 5), den > 0.f ? dsum / den * a.inv_tau : 0.f, __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+    }
+
+    // ---- the last workgroup of the question selects
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");         // this wave's scores are at the point of coherence
+    __syncthreads();
+    if (tid == 0) {
+        const uint32_t n = __hip_atomic_fetch_add(a.tickets + qi, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        sh_last = n == gridDim.x - 1u;
+        if (sh_last) __hip_atomic_store(a.tickets + qi, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    if (!sh_last) return;
+    rank_block([&](int f) { return __hip_atomic_load(scores + f, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }, a.n_frames,
+               a.k, a.idx + qi * a.k, a.n_sel ? a.n_sel + qi : nullptr);
+}
+
 }  // namespace
 
 namespace {
@@ -795,6 +937,22 @@ hipError_t retrieve_launch(const RetrieveArgs& a, hipStream_t stream) {
     const int d_prime = a.dim > 0 ? a.dim : a.n_kv_heads * a.head_dim;
     const float* q_vec = a.q_vec_given;
     hipError_t e = hipSuccess;
+    // Short streams go through one launch while few workgroups pool their whole question at once and that is not
+    // long: with questions of 448 KB and 512 KB pooling alone takes the kernel to 11.3 and 13.5 us against 9.3 and 11.5 in
+    // three launches, and with 128 and 256 workgroups it is 0.7 and 0.5 us behind (16 questions of 224 KB, 32 of 56 KB).
+    const int short_blocks = (a.n_frames + SHORT_ROWS - 1) / SHORT_ROWS;
+    const int64_t question_bytes = (int64_t)a.n_q_tokens * a.n_q_heads * a.head_dim * (a.dtype == REKV_BF16 ? 2 : 4);
+    if (!q_vec && a.n_frames <= RANK_MAX_FRAMES && a.k < a.n_frames && d_prime <= SHORT_MAX_DIM &&
+        (int64_t)short_blocks * a.n_questions <= SHORT_MAX_BLOCKS && question_bytes <= SHORT_MAX_QUESTION) {
+        const int ni = (d_prime + 255) / 256;
+        const bool bf16 = a.dtype == REKV_BF16;
+        auto kern = ni == 1 ? (bf16 ? retrieve_short_kernel<true, 1> : retrieve_short_kernel<false, 1>)
+                  : ni == 2 ? (bf16 ? retrieve_short_kernel<true, 2> : retrieve_short_kernel<false, 2>)
+                  : ni == 3 ? (bf16 ? retrieve_short_kernel<true, 3> : retrieve_short_kernel<false, 3>)
+                            : (bf16 ? retrieve_short_kernel<true, 4> : retrieve_short_kernel<false, 4>);
+        hipLaunchKernelGGL(kern, dim3((unsigned)short_blocks, (unsigned)a.n_questions), dim3(RANK_THREADS), 0, stream, a, d_prime);
+        return hipGetLastError();
+    }
     if (!q_vec) {                      // pooled question vectors: [n_questions, D']
         const int cols = POOL_LANES * (a.dtype == REKV_BF16 ? 8 : 4);
         dim3 grid((unsigned)a.n_questions, (unsigned)a.n_kv_heads, (unsigned)((a.head_dim + cols - 1) / cols));

@@ -33,11 +33,13 @@ def test_selection_on_its_own_scores(n_frames, distinct):
     for k in sorted({1, min(7, n_frames - 1), min(63, n_frames - 1), min(64, n_frames - 1), n_frames - 1, n_frames, n_frames + 3}):
         if k > 4096:
             continue
-        idx, n_sel, scores = r.retrieve_topk(table, n_frames, q, k, want_scores=True)
-        for i in range(3):
-            n = min(k, n_frames)
-            assert n_sel[i].item() == n
-            assert idx[i].tolist() == best(scores[i].tolist(), n) + [-1] * (k - n)
+        # up to 256 frames: one launch for the first, a selection kernel of its own for the second
+        for idx, n_sel, scores in (r.retrieve_topk(table, n_frames, q, k, want_scores=True),
+                                   r.retrieve_external(table, q.float().mean(dim=(1, 2)), k, want_scores=True)):
+            for i in range(3):
+                n = min(k, n_frames)
+                assert n_sel[i].item() == n
+                assert idx[i].tolist() == best(scores[i].tolist(), n) + [-1] * (k - n)
 
 
 @pytest.mark.parametrize("hq,hkv,d,dtype", [(14, 2, 64, "bf16"), (7, 1, 128, "bf16"), (3, 3, 36, "f32"), (71, 1, 4, "f32"), (8, 1, 256, "f32")])
@@ -76,3 +78,19 @@ def test_short_last_block(n_frames, b):
     got = Rekv(4, 2, 64, 16, "bf16").block_keys(table.cuda(), n_frames, b).cpu().double()
     ref = torch.stack([x.mean(dim=0) for x in table.double().split(b)])
     assert (got - ref).abs().max() < 1e-6
+
+
+def test_short_retrieval_between_split_attention():
+    """Both take their arrival counters from the same words, which every launch leaves at zero."""
+    from paper_2503_00540_amd.rekv import Rekv
+    g = torch.Generator().manual_seed(3)
+    r = Rekv(28, 4, 128, 49, "bf16")
+    table = torch.randn((200, 512), generator=g).cuda()
+    q = torch.randn((2, 9, 28, 128), generator=g).bfloat16().cuda()
+    kv = [torch.randn((2, n, 4, 128), generator=g).bfloat16().cuda() for n in (40 * 49, 40 * 49, 9, 9)]
+    first = None
+    for _ in range(4):
+        got = [*r.retrieve_topk(table, 200, q, 11, want_scores=True), r.qa_attention(q, *kv)]
+        torch.cuda.synchronize()
+        first = first or [x.clone() for x in got]
+        assert all(torch.equal(a, b) for a, b in zip(got, first))
