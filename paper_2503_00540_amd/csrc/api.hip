@@ -23,6 +23,7 @@ struct rekv_ctx {
     uint32_t* tickets;    // arrival counters of split attention and short retrieval launches, zero between launches
     int ticket_slot;      // their slot of the static pool, -1: an allocation of its own
     bool tickets_used;    // a launch has been given them
+    bool tickets_kept;    // a captured allocation-free call holds their address: the graph may outlive the context
     void* scratch;        // this device's copy of the static scratch array
     hipStream_t side;     // host<->device copies of offloaded KV
     hipEvent_t ev_main;   // recorded on the caller's stream, waited on by the side stream
@@ -94,7 +95,7 @@ hipError_t take_tickets(rekv_ctx* c) {
 
 // The context's launches must have finished before another one gets the slot.
 void give_tickets(rekv_ctx* c) {
-    if (!c->tickets) return;
+    if (!c->tickets || c->tickets_kept) return;
     if (c->ticket_slot < 0) {
         (void)hipFree(c->tickets);
         return;
@@ -179,6 +180,10 @@ rekv_status run_attention(rekv_ctx* c, const rekv::AttnProblem& p, hipStream_t s
         ws = c->ws.p;
     }
     c->tickets_used |= plan.wave != 0;
+    if (fixed_ws && plan.wave && plan.n_splits > 1 && stream && !c->tickets_kept) {
+        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+        c->tickets_kept = hipStreamIsCapturing(stream, &capture) == hipSuccess && capture == hipStreamCaptureStatusActive;
+    }
     hipError_t e = plan.wave ? rekv::attn_wave_launch(p, plan, ws, c->tickets, stream)
                              : rekv::attn_bf16_launch(p, plan, ws, stream);
     return e == hipSuccess ? REKV_OK : fail_hip(c, "bf16 attention launch", e);

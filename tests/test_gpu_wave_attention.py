@@ -68,3 +68,29 @@ def test_live_chunks_match_oracle(hq, hkv, d, l_x, n_chunks, l_l, first):
     assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
     ref = O.encode_chunks(q, k, v, first, l_x, n_chunks, l_l)
     assert np.abs(outs[0].float().cpu().numpy() - ref).max() < TOL
+
+
+def test_captured_no_alloc_call_outlives_its_context():
+    """The allocation-free call keeps its scratch and its arrival counters when the context is gone."""
+    import torch
+    from paper_2503_00540_amd.rekv import Rekv
+    g = torch.Generator().manual_seed(2)
+    q, kr, vr, kt, vt = [torch.randn((1, n, h, 128), generator=g).bfloat16().cuda()
+                         for n, h in ((1, 28), (3136, 4), (3136, 4), (97, 4), (97, 4))]
+    r = Rekv(28, 4, 128, 196, "bf16")
+    want = r.decode_attention(q, kr, vr, kt, vt, 97)
+    out = torch.empty_like(q)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side), torch.cuda.graph(graph, stream=side):
+        r.decode_attention(q, kr, vr, kt, vt, 97, out=out, no_alloc=True)
+    torch.cuda.synchronize()
+    r.close()
+    other = Rekv(28, 4, 128, 196, "bf16")
+    for _ in range(3):
+        out.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
+        assert torch.equal(other.decode_attention(q, kr, vr, kt, vt, 97), want)
