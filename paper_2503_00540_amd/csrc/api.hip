@@ -128,10 +128,12 @@ size_t elem_size(const rekv_ctx* c) { return c->shape.dtype == REKV_BF16 ? 2 : 4
 
 bool aligned16(const void* p) { return (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
 
-// Grows one of the context's workspaces.  Freeing the old block waits for the device, so work that
-// still reads it has finished.
-rekv_status reserve(rekv_ctx* c, Buffer* ws, size_t bytes, size_t least) {
-    if (bytes <= ws->bytes) return REKV_OK;
+// A workspace of so many bytes, *out: `ws`, or the context's other one where that is already large enough (the
+// context's calls are ordered, none outlives another's use), or `ws` grown.  Freeing the old block waits for
+// the device, so work that still reads it has finished.
+rekv_status reserve(rekv_ctx* c, Buffer* ws, Buffer* other, size_t bytes, size_t least, void** out) {
+    *out = bytes <= ws->bytes || bytes > other->bytes ? ws->p : other->p;
+    if (bytes <= ws->bytes || bytes <= other->bytes) return REKV_OK;
     if (ws->p) {
         hipError_t e = hipFree(ws->p);
         ws->p = nullptr;
@@ -147,6 +149,7 @@ rekv_status reserve(rekv_ctx* c, Buffer* ws, size_t bytes, size_t least) {
         return fail(c, REKV_ERR_NOMEM, "workspace of %zu bytes: %s", bytes, hipGetErrorString(e));
     }
     ws->bytes = bytes;
+    *out = ws->p;
     return REKV_OK;
 }
 
@@ -175,9 +178,8 @@ rekv_status run_attention(rekv_ctx* c, const rekv::AttnProblem& p, hipStream_t s
             return fail(c, REKV_ERR_UNSUPPORTED, "this launch needs %zu bytes of scratch, the static buffer holds %zu",
                         plan.workspace_bytes, fixed_ws_bytes);
     } else {
-        rekv_status s = reserve(c, &c->ws, plan.workspace_bytes, ATTENTION_WS);
+        rekv_status s = reserve(c, &c->ws, &c->retrieval_ws, plan.workspace_bytes, ATTENTION_WS, &ws);
         if (s != REKV_OK) return s;
-        ws = c->ws.p;
     }
     c->tickets_used |= plan.wave != 0;
     if (fixed_ws && plan.wave && plan.n_splits > 1 && stream && !c->tickets_kept) {
@@ -415,7 +417,8 @@ rekv_status rekv_retrieve_topk(rekv_ctx* c, const float* frame_keys, int64_t fra
     if (n_questions > 65535) return fail(c, REKV_ERR_UNSUPPORTED, "rekv_retrieve_topk: at most 65535 questions per call");
     const size_t qv_bytes = ((size_t)n_questions * d_prime * sizeof(float) + 255) & ~size_t(255);
     const size_t sc_bytes = scores ? 0 : (size_t)n_questions * n_frames * sizeof(float);
-    rekv_status s = reserve(c, &c->retrieval_ws, qv_bytes + sc_bytes, RETRIEVAL_WS);
+    void* ws = nullptr;
+    rekv_status s = reserve(c, &c->retrieval_ws, &c->ws, qv_bytes + sc_bytes, RETRIEVAL_WS, &ws);
     if (s != REKV_OK) return s;
     rekv::RetrieveArgs a;
     a.frame_keys = frame_keys; a.frame_keys_stride = frame_keys_stride; a.n_frames = n_frames;
@@ -423,8 +426,8 @@ rekv_status rekv_retrieve_topk(rekv_ctx* c, const float* frame_keys, int64_t fra
     a.n_q_heads = c->shape.n_q_heads; a.n_kv_heads = c->shape.n_kv_heads; a.head_dim = c->shape.head_dim;
     a.dtype = c->shape.dtype;
     a.idx = idx; a.n_sel = n_sel;
-    a.q_vec = static_cast<float*>(c->retrieval_ws.p);
-    a.scores = scores ? scores : reinterpret_cast<float*>(static_cast<char*>(c->retrieval_ws.p) + qv_bytes);
+    a.q_vec = static_cast<float*>(ws);
+    a.scores = scores ? scores : reinterpret_cast<float*>(static_cast<char*>(ws) + qv_bytes);
     a.q_vec_given = nullptr; a.dim = 0; a.inv_tau = 1.f;
     a.tickets = c->tickets;
     c->tickets_used = true;
@@ -444,8 +447,9 @@ rekv_status rekv_retrieve_external(rekv_ctx* c, const float* frame_emb, int32_t 
                     "rekv_retrieve_external: n_frames=%d n_questions=%d k=%d (1..4096) dim=%d (multiple of 4) tau=%g (> 0)",
                     n_frames, n_questions, k, dim, (double)tau);
     if (n_questions > 65535) return fail(c, REKV_ERR_UNSUPPORTED, "rekv_retrieve_external: at most 65535 questions per call");
+    void* ws = nullptr;
     if (!scores) {
-        rekv_status s = reserve(c, &c->retrieval_ws, (size_t)n_questions * n_frames * sizeof(float), RETRIEVAL_WS);
+        rekv_status s = reserve(c, &c->retrieval_ws, &c->ws, (size_t)n_questions * n_frames * sizeof(float), RETRIEVAL_WS, &ws);
         if (s != REKV_OK) return s;
     }
     rekv::RetrieveArgs a;
@@ -453,7 +457,7 @@ rekv_status rekv_retrieve_external(rekv_ctx* c, const float* frame_emb, int32_t 
     a.frame_keys = frame_emb; a.frame_keys_stride = 0; a.n_frames = n_frames;
     a.n_questions = n_questions; a.k = k;
     a.idx = idx; a.n_sel = n_sel;
-    a.scores = scores ? scores : static_cast<float*>(c->retrieval_ws.p);
+    a.scores = scores ? scores : static_cast<float*>(ws);
     a.q_vec_given = q_emb; a.dim = dim; a.inv_tau = 1.f / tau;
     hipError_t e = rekv::retrieve_launch(a, static_cast<hipStream_t>(stream));
     return e == hipSuccess ? REKV_OK : fail_hip(c, "external retrieval launch", e);

@@ -94,3 +94,28 @@ def test_short_retrieval_between_split_attention():
         torch.cuda.synchronize()
         first = first or [x.clone() for x in got]
         assert all(torch.equal(a, b) for a, b in zip(got, first))
+
+
+def test_retrieval_captured_after_attention_needs_no_allocation():
+    """The context's attention workspace serves a retrieval that is captured before it ever ran."""
+    from paper_2503_00540_amd.rekv import Rekv
+    g = torch.Generator().manual_seed(4)
+    r = Rekv(28, 4, 128, 49, "bf16")
+    table = torch.randn((700, 512), generator=g).cuda()
+    q = torch.randn((2, 9, 28, 128), generator=g).bfloat16().cuda()
+    kv = [torch.randn((2, n, 4, 128), generator=g).bfloat16().cuda() for n in (40 * 49, 40 * 49, 9, 9)]
+    want = Rekv(28, 4, 128, 49, "bf16").retrieve_topk(table, 700, q, 11)
+    r.qa_attention(q, *kv)
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.stream(side), torch.cuda.graph(graph, stream=side):
+        got = r.retrieve_topk(table, 700, q, 11)
+    torch.cuda.synchronize()
+    for _ in range(3):
+        got[0].zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
+        r.qa_attention(q, *kv)
+        torch.cuda.synchronize()
