@@ -562,7 +562,8 @@ hipError_t launch(const AttnProblem& p, const AttnPlan& plan, void* workspace, u
 // The split with the least estimated time, if that beats `other_us`, the estimate for the 128-row
 // kernel.  Fitted to launches of 7B- and 0.5B-class heads (28/4/128, 14/2/64), windows of 2 to 77 frames,
 // 1 to 9 questions: about 8 us before the first tile and after the last, a step of every wave
-// 1.1 us (head_dim 128, eight private tiles: the CU's 64 B/clk from L2), 1.03 us (four tiles shared by
+// 1.25 us (head_dim 128, eight private tiles through the LDS; with 1.1 a live frame of 205 tokens with a window of 24 frames
+// came here and took 41.3 us with its frame vector, 38.8 there), 1.03 us (four tiles shared by
 // two waves), 0.63 us (head_dim 64; twice that with two workgroups on a CU); a ticket round 3 us plus
 // the last arriver's reading of the partial results, 0.04 us each and 0.07 MB/us.
 // kv_mb: K and V that several row blocks read, from HBM: here 0.36 us per MB on top (0.16 at head_dim 64; the row blocks of a
@@ -584,7 +585,7 @@ bool attn_wave_plan(const AttnProblem& p, double other_us, double kv_mb, AttnPla
         if (rw > 1 && m_rows <= WM) break;
         const int64_t m_tiles = (m_rows + T - 1) / T, base = ik * m_tiles, rows = m_rows < T ? m_rows : T;
         if (base > slots) continue;
-        const double step_us = D == 64 ? 0.63 : (rw == 1 ? 1.1 : 1.03);
+        const double step_us = D == 64 ? 0.63 : (rw == 1 ? 1.25 : 1.03);
         for (int64_t s = 1; s <= slots / base && (s == 1 || (s - 1) * kg < n_tiles); ++s) {
             const int64_t steps = (n_tiles + s * kg - 1) / (s * kg);
             double us = 8.0 + (double)steps * step_us * (base * s > 256 ? 2.0 : 1.0);
