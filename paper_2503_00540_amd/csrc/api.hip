@@ -757,4 +757,20 @@ rekv_status rekv_probe_mfma(rekv_ctx* c, float* sink, int32_t n_workgroups, int3
     return e == hipSuccess ? REKV_OK : fail_hip(c, "rekv_probe_mfma", e);
 }
 
+// Not part of the ABI (rekv.h does not declare it): the plan of a bf16 attention launch, so that the dispatch can be
+// tested without a GPU.  len_a: the window of an encode call, the retrieved tokens of a question.
+// out: kernel (0: attention_bf16.hip, else row waves per workgroup of attention_wave.hip), splits of the key range,
+// row blocks, workspace bytes.
+void rekv_internal_attention_plan(int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim, int32_t is_encode,
+                                  int64_t first_token, int32_t n_items, int32_t len_q, int32_t len_a, int32_t len_b,
+                                  int64_t out[4]) {
+    rekv::AttnProblem p;
+    memset(&p, 0, sizeof(p));
+    p.n_q_heads = n_q_heads; p.n_kv_heads = n_kv_heads; p.head_dim = head_dim; p.is_encode = is_encode;
+    p.first_token = first_token; p.n_items = n_items; p.len_q = len_q; p.len_b = len_b;
+    (is_encode ? p.l_l : p.len_a) = len_a;
+    const rekv::AttnPlan plan = rekv::attn_bf16_plan(p);
+    out[0] = plan.wave; out[1] = plan.n_splits; out[2] = plan.m_tiles; out[3] = (int64_t)plan.workspace_bytes;
+}
+
 }  // extern "C"

@@ -32,6 +32,11 @@ constexpr int WAVES = 8;
 constexpr int THREADS = WAVES * 64;
 constexpr int WM = 32;               // query rows per wavefront (one MFMA column block)
 
+// LDS of the tiles, and what the last arriver of a row block of T rows lays over it: a (weight, sum) pair per split and
+// row, then the partial sums of all its thread groups but the first (one group is 64 threads or more).
+constexpr int64_t tile_lds_bytes(int d) { return (int64_t)WAVES * 2 * BN * d * 2; }
+constexpr int64_t merge_lds_bytes(int64_t n_splits, int64_t t) { return n_splits * t * 8 + (THREADS - 64) * 16; }
+
 // Division by a launch constant: n / d for n * d < 2^32 (the quotient of 32-bit division costs about
 // 30 dependent instructions, and a launch this small is mostly its prologue).
 struct FastDiv {
@@ -87,7 +92,7 @@ __global__ __launch_bounds__(THREADS, 2) void attn_wave_kernel(WaveArgs a) {
     constexpr uint32_t PART_B = T * (D + 2) * 4; // bytes of one partial result
     __shared__ int32_t frame_of_slot[INDEXED ? MAX_INDEXED_FRAMES : 1];
     // per key group and stage: a K tile, a V tile; at the end per key group: its O [T][D] fp32
-    __shared__ __attribute__((aligned(1024))) unsigned char lds[WAVES * 2 * TILE_B];
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[tile_lds_bytes(D)];
     __shared__ f32x2 ml[KG][T];
     __shared__ f32x2 ml_all[T];
     __shared__ uint32_t sh_last;
@@ -444,7 +449,8 @@ __global__ __launch_bounds__(THREADS, 2) void attn_wave_kernel(WaveArgs a) {
 
     // ---- last of the row block's workgroups: the splits' results.  Threads form n_grp groups that share
     // the splits; a thread owns P chunks and has P * U loads in flight, the first of them issued
-    // before the weights exp2(m_s - max) / sum are worked out (LPR lanes per row) and passed through LDS.
+    // before the weights exp2(m_s - max) / sum are worked out (LPR lanes per row) and passed through LDS
+    // (merge_lds_bytes, which the plan keeps within the tiles' storage).
     f32x2* wts = reinterpret_cast<f32x2*>(lds);                      // [split][T]: (m, l), then the weight
     f32x4* red = reinterpret_cast<f32x4*>(lds + (size_t)a.n_splits * T * 8);    // [group - 1][chunk]
     auto weights = [&] {
@@ -587,6 +593,7 @@ bool attn_wave_plan(const AttnProblem& p, double other_us, double kv_mb, AttnPla
         if (base > slots) continue;
         const double step_us = D == 64 ? 0.63 : (rw == 1 ? 1.25 : 1.03);
         for (int64_t s = 1; s <= slots / base && (s == 1 || (s - 1) * kg < n_tiles); ++s) {
+            if (s > 1 && merge_lds_bytes(s, T) > tile_lds_bytes(D)) break;
             const int64_t steps = (n_tiles + s * kg - 1) / (s * kg);
             double us = 8.0 + (double)steps * step_us * (base * s > 256 ? 2.0 : 1.0);
             us += (D == 64 ? 0.16 : 0.36) * kv_mb;

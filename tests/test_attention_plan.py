@@ -1,0 +1,65 @@
+"""The plan of a bf16 attention launch (which kernel, how many splits of the key range), without a GPU: what the
+chosen launch needs stays within what the kernel has, over the whole argument range."""
+import ctypes
+import math
+import random
+
+import pytest
+
+from paper_2503_00540_amd import rekv
+
+
+def plan(hq, hkv, d, len_q, len_a, len_b, items=1, encode=False, first=1 << 40):
+    """(row waves per workgroup or 0 for the 128-row kernel, splits, row blocks, workspace bytes)"""
+    f = rekv.lib().rekv_internal_attention_plan
+    f.restype = None
+    f.argtypes = [ctypes.c_int32] * 4 + [ctypes.c_int64] + [ctypes.c_int32] * 4 + [ctypes.c_void_p]
+    out = (ctypes.c_int64 * 4)()
+    f(hq, hkv, d, int(encode), first, items, len_q, len_a, len_b, out)
+    return tuple(out)
+
+
+def last_arriver_lds(wave, splits, rows, d):
+    """Bytes the merge of a row block of so many rows lays over the tiles: a weight pair per split and row, then the
+    partial sums of all thread groups but the first."""
+    n_chunks = rows * d // 4
+    per = -(-n_chunks // 64) * 64
+    groups = 512 // per if per * 2 <= 512 else 1
+    return splits * 32 * wave * 8 + (groups - 1) * per * 16
+
+
+def shapes():
+    # one KV head, few rows, long context: where the split count is largest
+    for hq in (1, 2, 3, 8, 16):
+        for len_q in (1, 2, 3, 31, 32, 33, 65):
+            for len_a in range(800_000, 1_060_000, 9_973):
+                for d in (64, 128):
+                    yield hq, 1, d, len_q, len_a, len_q, 1, len_a % 2 == 0
+    rng = random.Random(7)
+    log_int = lambda lo, hi: int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+    for _ in range(60_000):
+        hkv, len_q, encode = rng.choice([1, 1, 2, 4, 8]), log_int(1, 4000), rng.random() < 0.5
+        yield (hkv * rng.choice([1, 2, 3, 5, 7, 8, 16]), hkv, rng.choice([64, 128]), len_q, log_int(1, 1 << 22),
+               len_q if encode else len_q + rng.choice([0, log_int(1, 4000)]), log_int(1, 600), encode)
+
+
+def test_split_launches_fit_their_kernel():
+    n_split = 0
+    for hq, hkv, d, len_q, len_a, len_b, items, encode in shapes():
+        wave, splits, row_blocks, ws = plan(hq, hkv, d, len_q, len_a, len_b, items, encode)
+        where = (hq, hkv, d, len_q, len_a, len_b, items, encode)
+        assert wave in (0, 1, 2) and splits >= 1, where
+        assert ws <= 33 << 20, where                              # the allocation-free entry point's scratch
+        if not wave:
+            continue
+        m_rows, t = len_q * (hq // hkv), 32 * wave
+        assert row_blocks == -(-m_rows // t), where
+        assert items * hkv * row_blocks * splits <= 512, where    # arrival counters, resident workgroups
+        if splits == 1:
+            assert ws == 0, where
+            continue
+        n_split += 1
+        assert ws >= items * hkv * row_blocks * splits * t * (d + 2) * 4, where
+        last = m_rows - (row_blocks - 1) * t
+        assert max(last_arriver_lds(wave, splits, rows, d) for rows in {last, min(m_rows, t)}) <= 8 * 2 * 32 * d * 2, where
+    assert n_split > 1000
