@@ -288,10 +288,13 @@ rekv_status rekv_decode_attention(rekv_ctx* ctx, const void* q, const void* k_re
  * device array of 33 MiB inside the library (one copy per GPU, held until the process ends)
  * instead of the context's growable workspace, so the call never allocates, frees or
  * synchronises.  A launch that would need more scratch than that is refused with
- * REKV_ERR_UNSUPPORTED (fp32 contexts use no scratch at all).  Every call on a GPU shares that
- * GPU's array: calls that overlap in time on one GPU - other streams, other contexts - race;
- * calls ordered on one stream are safe.  Nothing in the array needs to start at zero: a launch
- * writes every partial result it later reads.
+ * REKV_ERR_UNSUPPORTED (fp32 contexts use no scratch at all).  Beside the array lie the
+ * workgroups' arrival counters, zero when the library is loaded and after every launch; what a
+ * launch reads of the array it has written itself.  Array and counters belong to this entry
+ * point: a captured call depends on nothing of its context, which may run other calls on other
+ * streams meanwhile or be destroyed before the graph.  All calls of this entry point on a GPU share
+ * them: such calls that overlap in time on one GPU - other streams, other contexts - race, and may
+ * leave a counter that spoils later ones; calls ordered on one stream are safe.
  */
 rekv_status rekv_decode_attention_noalloc(rekv_ctx* ctx, const void* q, const void* k_ret,
                                           const void* v_ret, int32_t n_ret_tokens, const int32_t* n_sel,

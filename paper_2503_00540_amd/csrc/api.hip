@@ -14,6 +14,17 @@ struct Buffer {
     size_t bytes;
 };
 
+// Scratch of the allocation-free entry point (rekv_decode_attention_noalloc): the split-KV
+// partial results of one launch and its arrival counters (zero at load and after every launch).  One copy
+// per GPU, held until the process ends; every call on a GPU shares it and nothing else, so a captured call
+// neither depends on its context's workspace nor on what else that context runs.  The bf16 plan never asks for
+// more: at most 512 workgroups x 128 rows x (D + 2) floats when the key range is split.
+struct NoallocScratch {
+    uint32_t tickets[rekv::WAVE_TICKETS];
+    unsigned char partials[(size_t)33 << 20];
+};
+static __device__ __align__(256) NoallocScratch noalloc_scratch;
+
 struct rekv_ctx {
     rekv_shape shape;
     float scale;
@@ -23,8 +34,7 @@ struct rekv_ctx {
     uint32_t* tickets;    // arrival counters of split attention and short retrieval launches, zero between launches
     int ticket_slot;      // their slot of the static pool, -1: an allocation of its own
     bool tickets_used;    // a launch has been given them
-    bool tickets_kept;    // a captured allocation-free call holds their address: the graph may outlive the context
-    void* scratch;        // this device's copy of the static scratch array
+    NoallocScratch* scratch;   // this device's copy of the static scratch
     hipStream_t side;     // host<->device copies of offloaded KV
     hipEvent_t ev_main;   // recorded on the caller's stream, waited on by the side stream
     hipEvent_t ev_side;   // recorded on the side stream, waited on by the caller's stream
@@ -32,13 +42,6 @@ struct rekv_ctx {
     size_t idx_host_cap;  // entries
     char err[512];
 };
-
-// Scratch of the allocation-free entry point (rekv_decode_attention_noalloc): the split-KV
-// partial results of one launch.  One copy per GPU, held until the process ends; every call on a
-// GPU shares it.  The bf16 plan never asks for more: at most 512 workgroups x 128 rows x
-// (D + 2) floats when the key range is split.
-constexpr size_t NOALLOC_SCRATCH_BYTES = (size_t)33 << 20;
-static __device__ __align__(256) unsigned char scratch[NOALLOC_SCRATCH_BYTES];
 
 // Arrival counters of the contexts alive on a GPU: a slot each, so that contexts on different streams
 // never share a counter.  Zero at load and after every launch, so a slot needs no clearing when it
@@ -50,24 +53,24 @@ namespace {
 
 thread_local char g_create_err[512] = "";
 
-// Device address of `scratch` on each GPU (the array's name is only a host-side handle).
+// Device address of `noalloc_scratch` on each GPU (the variable's name is only a host-side handle).
 constexpr int MAX_DEVICES = 64;
 std::mutex g_scratch_mutex;
-void* g_scratch_ptr[MAX_DEVICES] = {};
+NoallocScratch* g_scratch_ptr[MAX_DEVICES] = {};
 uint32_t* g_ticket_ptr[MAX_DEVICES] = {};
 uint64_t g_ticket_taken[MAX_DEVICES] = {};     // bit i: slot i belongs to a context
 static_assert(TICKET_SLOTS == 64, "one bit per slot");
 
 // Looks the address up once per device; that device must be current.
-hipError_t scratch_address(int device, void** out) {
+hipError_t scratch_address(int device, NoallocScratch** out) {
     *out = nullptr;
     if (device < 0 || device >= MAX_DEVICES) return hipErrorInvalidDevice;
     std::lock_guard<std::mutex> lock(g_scratch_mutex);
     if (!g_scratch_ptr[device]) {
         void* ptr = nullptr;
-        hipError_t e = hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch));
+        hipError_t e = hipGetSymbolAddress(&ptr, HIP_SYMBOL(noalloc_scratch));
         if (e != hipSuccess) return e;
-        g_scratch_ptr[device] = ptr;
+        g_scratch_ptr[device] = static_cast<NoallocScratch*>(ptr);
     }
     *out = g_scratch_ptr[device];
     return hipSuccess;
@@ -95,7 +98,7 @@ hipError_t take_tickets(rekv_ctx* c) {
 
 // The context's launches must have finished before another one gets the slot.
 void give_tickets(rekv_ctx* c) {
-    if (!c->tickets || c->tickets_kept) return;
+    if (!c->tickets) return;
     if (c->ticket_slot < 0) {
         (void)hipFree(c->tickets);
         return;
@@ -159,10 +162,9 @@ rekv_status reserve(rekv_ctx* c, Buffer* ws, Buffer* other, size_t bytes, size_t
 // scores does not pay for the larger one.
 constexpr size_t ATTENTION_WS = size_t(8) << 20, RETRIEVAL_WS = size_t(1) << 20;
 
-// fixed_ws != NULL: the launch may use only that buffer of fixed_ws_bytes (no allocation);
-// otherwise the context's workspace grows as needed.
-rekv_status run_attention(rekv_ctx* c, const rekv::AttnProblem& p, hipStream_t stream, void* fixed_ws = nullptr,
-                          size_t fixed_ws_bytes = 0) {
+// fixed != NULL: the launch may use only that scratch (no allocation); otherwise the context's
+// workspace grows as needed.
+rekv_status run_attention(rekv_ctx* c, const rekv::AttnProblem& p, hipStream_t stream, NoallocScratch* fixed = nullptr) {
     if (c->shape.dtype == REKV_F32) {
         if (p.n_items > 65535)
             return fail(c, REKV_ERR_UNSUPPORTED, "fp32 attention takes at most 65535 chunks/questions per call");
@@ -172,21 +174,20 @@ rekv_status run_attention(rekv_ctx* c, const rekv::AttnProblem& p, hipStream_t s
     const rekv::AttnPlan plan = rekv::attn_bf16_plan(p);
     const int64_t blocks = (int64_t)p.n_items * p.n_kv_heads * plan.m_tiles * plan.n_splits;
     if (blocks > 0x7FFFFFFF) return fail(c, REKV_ERR_UNSUPPORTED, "attention grid of %lld workgroups", (long long)blocks);
-    void* ws = fixed_ws;
-    if (fixed_ws) {
-        if (plan.workspace_bytes > fixed_ws_bytes)
+    void* ws = nullptr;
+    uint32_t* tickets = c->tickets;
+    if (fixed) {
+        if (plan.workspace_bytes > sizeof(fixed->partials))
             return fail(c, REKV_ERR_UNSUPPORTED, "this launch needs %zu bytes of scratch, the static buffer holds %zu",
-                        plan.workspace_bytes, fixed_ws_bytes);
+                        plan.workspace_bytes, sizeof(fixed->partials));
+        ws = fixed->partials;
+        tickets = fixed->tickets;
     } else {
         rekv_status s = reserve(c, &c->ws, &c->retrieval_ws, plan.workspace_bytes, ATTENTION_WS, &ws);
         if (s != REKV_OK) return s;
+        c->tickets_used |= plan.wave != 0;
     }
-    c->tickets_used |= plan.wave != 0;
-    if (fixed_ws && plan.wave && plan.n_splits > 1 && stream && !c->tickets_kept) {
-        hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
-        c->tickets_kept = hipStreamIsCapturing(stream, &capture) == hipSuccess && capture == hipStreamCaptureStatusActive;
-    }
-    hipError_t e = plan.wave ? rekv::attn_wave_launch(p, plan, ws, c->tickets, stream)
+    hipError_t e = plan.wave ? rekv::attn_wave_launch(p, plan, ws, tickets, stream)
                              : rekv::attn_bf16_launch(p, plan, ws, stream);
     return e == hipSuccess ? REKV_OK : fail_hip(c, "bf16 attention launch", e);
 }
@@ -328,7 +329,7 @@ static rekv_status decode_attention(rekv_ctx* c, const char* fn, bool no_alloc, 
     p.n_items = n_questions; p.is_encode = 0;
     p.n_q_heads = c->shape.n_q_heads; p.n_kv_heads = c->shape.n_kv_heads; p.head_dim = c->shape.head_dim;
     p.scale = c->scale;
-    if (no_alloc) return run_attention(c, p, static_cast<hipStream_t>(stream), c->scratch, NOALLOC_SCRATCH_BYTES);
+    if (no_alloc) return run_attention(c, p, static_cast<hipStream_t>(stream), c->scratch);
     return run_attention(c, p, static_cast<hipStream_t>(stream));
 }
 

@@ -94,3 +94,32 @@ def test_captured_no_alloc_call_outlives_its_context():
         torch.cuda.synchronize()
         assert torch.equal(out, want)
         assert torch.equal(other.decode_attention(q, kr, vr, kt, vt, 97), want)
+
+
+def test_captured_no_alloc_call_beside_its_contexts_other_calls():
+    """A replayed allocation-free call on one stream, split attention and retrieval of the same context on another:
+    they have no counters and no scratch in common."""
+    g = torch.Generator().manual_seed(5)
+    q, kr, vr, kt, vt = [torch.randn((1, n, h, 128), generator=g).bfloat16().to(DEV)
+                         for n, h in ((1, 28), (12544, 4), (12544, 4), (97, 4), (97, 4))]
+    qq, qk, qv = [torch.randn((1, 32, h, 128), generator=g).bfloat16().to(DEV) for h in (28, 4, 4)]
+    table = torch.randn((200, 512), generator=g).to(DEV)
+    r = Rekv(28, 4, 128, 196)
+    want = r.decode_attention(q, kr, vr, kt, vt, 97)
+    want_qa, want_idx = r.qa_attention(qq, kr, vr, qk, qv), r.retrieve_topk(table, 200, qq, 16)[0]
+    out = torch.empty_like(q)
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side), torch.cuda.graph(graph, stream=side):
+        for _ in range(20):
+            r.decode_attention(q, kr, vr, kt, vt, 97, out=out, no_alloc=True)
+    torch.cuda.synchronize()
+    for _ in range(5):
+        out.zero_()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(side):
+            graph.replay()
+        got = [(r.qa_attention(qq, kr, vr, qk, qv), r.retrieve_topk(table, 200, qq, 16)[0]) for _ in range(10)]
+        torch.cuda.synchronize()
+        assert torch.equal(out, want)
+        assert all(torch.equal(a, want_qa) and torch.equal(i, want_idx) for a, i in got)
