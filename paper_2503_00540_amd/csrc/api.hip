@@ -33,7 +33,7 @@ struct rekv_ctx {
     Buffer retrieval_ws;  // pooled questions + scores
     uint32_t* tickets;    // arrival counters of split attention and short retrieval launches, zero between launches
     int ticket_slot;      // their slot of the static pool, -1: an allocation of its own
-    bool tickets_used;    // a launch has been given them
+    bool tickets_used;    // a launch may have counted in them
     NoallocScratch* scratch;   // this device's copy of the static scratch
     hipStream_t side;     // host<->device copies of offloaded KV
     hipEvent_t ev_main;   // recorded on the caller's stream, waited on by the side stream
@@ -93,23 +93,19 @@ hipError_t take_tickets(rekv_ctx* c) {
     }
     c->ticket_slot = -1;
     hipError_t e = hipMalloc(reinterpret_cast<void**>(&c->tickets), rekv::WAVE_TICKETS * sizeof(uint32_t));
-    return e == hipSuccess ? hipMemset(c->tickets, 0, rekv::WAVE_TICKETS * sizeof(uint32_t)) : e;
+    // zero before the call returns: the caller's streams need not be ordered after any of ours
+    if (e == hipSuccess) e = hipMemsetAsync(c->tickets, 0, rekv::WAVE_TICKETS * sizeof(uint32_t), c->side);
+    return e == hipSuccess ? hipStreamSynchronize(c->side) : e;
 }
 
-// The context's launches must have finished before another one gets the slot.
-void give_tickets(rekv_ctx* c) {
+// idle: the context's launches have finished.  A slot whose last launch may still count in it goes to nobody.
+void give_tickets(rekv_ctx* c, bool idle) {
     if (!c->tickets) return;
     if (c->ticket_slot < 0) {
         (void)hipFree(c->tickets);
         return;
     }
-    if (c->tickets_used) {
-        int current = 0;
-        (void)hipGetDevice(&current);
-        if (current != c->device) (void)hipSetDevice(c->device);
-        (void)hipDeviceSynchronize();
-        if (current != c->device) (void)hipSetDevice(current);
-    }
+    if (c->tickets_used && !idle) return;
     std::lock_guard<std::mutex> lock(g_scratch_mutex);
     g_ticket_taken[c->device] &= ~(1ull << c->ticket_slot);
 }
@@ -185,7 +181,7 @@ rekv_status run_attention(rekv_ctx* c, const rekv::AttnProblem& p, hipStream_t s
     } else {
         rekv_status s = reserve(c, &c->ws, &c->retrieval_ws, plan.workspace_bytes, ATTENTION_WS, &ws);
         if (s != REKV_OK) return s;
-        c->tickets_used |= plan.wave != 0;
+        c->tickets_used |= plan.wave && plan.n_splits > 1;
     }
     hipError_t e = plan.wave ? rekv::attn_wave_launch(p, plan, ws, tickets, stream)
                              : rekv::attn_bf16_launch(p, plan, ws, stream);
@@ -222,8 +218,8 @@ rekv_status rekv_create(const rekv_shape* shape, rekv_ctx** out) {
     c->scale = shape->softmax_scale > 0.f ? shape->softmax_scale : 1.0f / sqrtf((float)shape->head_dim);
     hipError_t e = hipGetDevice(&c->device);
     if (e == hipSuccess) e = scratch_address(c->device, &c->scratch);
-    if (e == hipSuccess) e = take_tickets(c);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking);
+    if (e == hipSuccess) e = take_tickets(c);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_main, hipEventDisableTiming);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_side, hipEventDisableTiming);
     if (e != hipSuccess) {
@@ -243,9 +239,11 @@ void rekv_destroy(rekv_ctx* c) {
     }
     if (c->ev_main) (void)hipEventDestroy(c->ev_main);
     if (c->ev_side) (void)hipEventDestroy(c->ev_side);
-    if (c->ws.p) (void)hipFree(c->ws.p);
-    if (c->retrieval_ws.p) (void)hipFree(c->retrieval_ws.p);
-    give_tickets(c);
+    // Every launch that counts arrivals also uses a workspace, and hipFree waits for the device.
+    int freed = 0, failed = 0;
+    for (void* p : {c->ws.p, c->retrieval_ws.p})
+        if (p) ++(hipFree(p) == hipSuccess ? freed : failed);
+    give_tickets(c, freed > 0 && failed == 0);
     if (c->idx_host) (void)hipHostFree(c->idx_host);
     delete c;
 }

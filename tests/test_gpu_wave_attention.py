@@ -123,3 +123,23 @@ def test_captured_no_alloc_call_beside_its_contexts_other_calls():
         torch.cuda.synchronize()
         assert torch.equal(out, want)
         assert all(torch.equal(a, want_qa) and torch.equal(i, want_idx) for a, i in got)
+
+
+def test_more_contexts_than_static_counter_slots():
+    """70 contexts at once, each on a stream of its own; destroyed with their work still queued, and 70 more."""
+    g = torch.Generator().manual_seed(6)
+    q, kr, vr, kt, vt = [torch.randn((1, n, h, 128), generator=g).bfloat16().to(DEV)
+                         for n, h in ((32, 28), (3136, 4), (3136, 4), (32, 4), (32, 4))]
+    want = Rekv(28, 4, 128, 196).qa_attention(q, kr, vr, kt, vt)
+    streams = [torch.cuda.Stream() for _ in range(8)]
+    torch.cuda.synchronize()
+    for _ in range(2):
+        got = []
+        contexts = [Rekv(28, 4, 128, 196) for _ in range(70)]
+        for i, r in enumerate(contexts):
+            with torch.cuda.stream(streams[i % 8]):
+                got += [r.qa_attention(q, kr, vr, kt, vt) for _ in range(2)]
+        for r in contexts:
+            r.close()
+        torch.cuda.synchronize()
+        assert all(torch.equal(x, want) for x in got)
