@@ -152,8 +152,8 @@ rekv_status reserve(rekv_ctx* c, Buffer* ws, Buffer* other, size_t bytes, size_t
     return REKV_OK;
 }
 
-// What a workspace starts with.  Attention: every launch of attention_wave.hip fits into 8 MiB, so that most contexts
-// allocate once (growing costs a hipFree, a hipMalloc and the device's idling).  Retrieval has a block of its own, so
+// What a workspace starts with.  Attention: nearly every launch of attention_wave.hip asks for less than 8 MiB, so that most
+// contexts allocate once (growing costs a hipFree, a hipMalloc and the device's idling).  Retrieval has a block of its own, so
 // that a question's first attention does not wait for the retrieval to free it, and a context that only needs
 // scores does not pay for the larger one.
 constexpr size_t ATTENTION_WS = size_t(8) << 20, RETRIEVAL_WS = size_t(1) << 20;
@@ -179,7 +179,7 @@ rekv_status run_attention(rekv_ctx* c, const rekv::AttnProblem& p, hipStream_t s
         ws = fixed->partials;
         tickets = fixed->tickets;
     } else {
-        rekv_status s = reserve(c, &c->ws, &c->retrieval_ws, plan.workspace_bytes, ATTENTION_WS, &ws);
+        rekv_status s = reserve(c, &c->ws, &c->retrieval_ws, plan.reserve_bytes, ATTENTION_WS, &ws);
         if (s != REKV_OK) return s;
         c->tickets_used |= plan.wave && plan.n_splits > 1;
     }
@@ -759,10 +759,10 @@ rekv_status rekv_probe_mfma(rekv_ctx* c, float* sink, int32_t n_workgroups, int3
 // Not part of the ABI (rekv.h does not declare it): the plan of a bf16 attention launch, so that the dispatch can be
 // tested without a GPU.  len_a: the window of an encode call, the retrieved tokens of a question.
 // out: kernel (0: attention_bf16.hip, else row waves per workgroup of attention_wave.hip), splits of the key range,
-// row blocks, workspace bytes.
+// row blocks, workspace bytes, bytes the context holds after the call.
 void rekv_internal_attention_plan(int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim, int32_t is_encode,
                                   int64_t first_token, int32_t n_items, int32_t len_q, int32_t len_a, int32_t len_b,
-                                  int64_t out[4]) {
+                                  int64_t out[5]) {
     rekv::AttnProblem p;
     memset(&p, 0, sizeof(p));
     p.n_q_heads = n_q_heads; p.n_kv_heads = n_kv_heads; p.head_dim = head_dim; p.is_encode = is_encode;
@@ -770,6 +770,7 @@ void rekv_internal_attention_plan(int32_t n_q_heads, int32_t n_kv_heads, int32_t
     (is_encode ? p.l_l : p.len_a) = len_a;
     const rekv::AttnPlan plan = rekv::attn_bf16_plan(p);
     out[0] = plan.wave; out[1] = plan.n_splits; out[2] = plan.m_tiles; out[3] = (int64_t)plan.workspace_bytes;
+    out[4] = (int64_t)plan.reserve_bytes;
 }
 
 }  // extern "C"

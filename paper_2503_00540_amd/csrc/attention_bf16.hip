@@ -598,6 +598,11 @@ AttnPlan attn_bf16_plan(const AttnProblem& p) {
         if (splits > cap) splits = cap;
     }
     plan.n_splits = splits;
+    plan.workspace_bytes = 0;
+    if (splits > 1)
+        plan.workspace_bytes = (size_t)p.n_items * p.n_kv_heads * splits * plan.m_tiles * BM *
+                               (size_t)(p.head_dim + 2) * sizeof(float);
+    plan.reserve_bytes = plan.workspace_bytes;
     if (base < target) {
         // Launches that do not fill the chip by themselves go to attention_wave.hip where that is the
         // faster one.  Estimate for this kernel, fitted to the same measurements: a 32-key step of
@@ -614,12 +619,8 @@ AttnPlan attn_bf16_plan(const AttnProblem& p) {
         else if (rows <= WM) us += 9.5 + 0.04 * splits * p.head_dim / 128;
         else us += 10.0 + 0.48 * part_mb;
         us += 0.1 * kv_mb;
-        if (attn_wave_plan(p, us, kv_mb, &plan)) return plan;
+        attn_wave_plan(p, us, kv_mb, &plan);
     }
-    plan.workspace_bytes = 0;
-    if (splits > 1)
-        plan.workspace_bytes = (size_t)p.n_items * p.n_kv_heads * splits * plan.m_tiles * BM *
-                               (size_t)(p.head_dim + 2) * sizeof(float);
     return plan;
 }
 

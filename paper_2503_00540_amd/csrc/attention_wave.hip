@@ -593,7 +593,8 @@ bool attn_wave_plan(const AttnProblem& p, double other_us, double kv_mb, AttnPla
         if (base > slots) continue;
         const double step_us = D == 64 ? 0.63 : (rw == 1 ? 1.25 : 1.03);
         for (int64_t s = 1; s <= slots / base && (s == 1 || (s - 1) * kg < n_tiles); ++s) {
-            if (s > 1 && merge_lds_bytes(s, T) > tile_lds_bytes(D)) break;
+            const size_t ws = s > 1 ? (size_t)(base * s) * T * (size_t)(D + 2) * sizeof(float) : 0;
+            if (ws > plan->reserve_bytes || (s > 1 && merge_lds_bytes(s, T) > tile_lds_bytes(D))) break;
             const int64_t steps = (n_tiles + s * kg - 1) / (s * kg);
             double us = 8.0 + (double)steps * step_us * (base * s > 256 ? 2.0 : 1.0);
             us += (D == 64 ? 0.16 : 0.36) * kv_mb;
@@ -604,7 +605,7 @@ bool attn_wave_plan(const AttnProblem& p, double other_us, double kv_mb, AttnPla
             plan->wave = rw;
             plan->n_splits = (int32_t)s;
             plan->m_tiles = (int32_t)m_tiles;
-            plan->workspace_bytes = s > 1 ? (size_t)(base * s) * T * (size_t)(D + 2) * sizeof(float) : 0;
+            plan->workspace_bytes = ws;
         }
     }
     return take;

@@ -77,18 +77,22 @@ __device__ inline ItemSegs item_segments(const AttnProblem& p, int item) {
 }
 
 // How a bf16 attention launch is split, and the workspace its partial results need (0 when one split
-// suffices).  wave: attention_wave.hip takes the launch (m_tiles = 32-row blocks), else
-// attention_bf16.hip (m_tiles = 128-row blocks).
+// suffices).  wave: row waves per workgroup of attention_wave.hip where it takes the launch (m_tiles = blocks of
+// 32 * wave rows), 0: attention_bf16.hip (m_tiles = 128-row blocks).
+// reserve_bytes: what the context holds after the call, never less than workspace_bytes: the partial results
+// of attention_bf16.hip for this problem, whichever kernel takes it.  A program may run a prompt and then capture calls it
+// has not run before, relying on the prompt's workspace, so the choice of the kernel must not shrink it.
 struct AttnPlan {
     int32_t wave;
     int32_t n_splits;
     int32_t m_tiles;
-    size_t workspace_bytes;
+    size_t workspace_bytes, reserve_bytes;
 };
 AttnPlan attn_bf16_plan(const AttnProblem& p);
 hipError_t attn_bf16_launch(const AttnProblem& p, const AttnPlan& plan, void* workspace,
                             hipStream_t stream);
-// attn_wave_plan: true if that kernel takes the problem (other_us: what it has to beat).  tickets: WAVE_TICKETS zeroed words that only
+// attn_wave_plan: true if that kernel takes the problem (other_us: what it has to beat; plan->reserve_bytes: the most
+// workspace it may ask for).  tickets: WAVE_TICKETS zeroed words that only
 // calls ordered on one stream use.
 constexpr int WAVE_TICKETS = 512;
 bool attn_wave_plan(const AttnProblem& p, double other_us, double kv_mb, AttnPlan* plan);

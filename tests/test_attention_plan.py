@@ -10,11 +10,11 @@ from paper_2503_00540_amd import rekv
 
 
 def plan(hq, hkv, d, len_q, len_a, len_b, items=1, encode=False, first=1 << 40):
-    """(row waves per workgroup or 0 for the 128-row kernel, splits, row blocks, workspace bytes)"""
+    """(row waves per workgroup or 0 for the 128-row kernel, splits, row blocks, workspace bytes, reserved bytes)"""
     f = rekv.lib().rekv_internal_attention_plan
     f.restype = None
     f.argtypes = [ctypes.c_int32] * 4 + [ctypes.c_int64] + [ctypes.c_int32] * 4 + [ctypes.c_void_p]
-    out = (ctypes.c_int64 * 4)()
+    out = (ctypes.c_int64 * 5)()
     f(hq, hkv, d, int(encode), first, items, len_q, len_a, len_b, out)
     return tuple(out)
 
@@ -26,6 +26,17 @@ def last_arriver_lds(wave, splits, rows, d):
     per = -(-n_chunks // 64) * 64
     groups = 512 // per if per * 2 <= 512 else 1
     return splits * 32 * wave * 8 + (groups - 1) * per * 16
+
+
+def workspace_of_128_row_blocks(hq, hkv, d, len_q, len_a, len_b, items):
+    """What a context holds after a call, whichever kernel takes it: the partial results of splitting 128-row workgroups
+    over the keys (512 of them in all, each with at least 8 tiles of 32 keys, 2 where it has at most 32 rows)."""
+    m_rows = len_q * (hq // hkv)
+    row_blocks = -(-m_rows // 128)
+    base = items * hkv * row_blocks
+    tiles = -(-len_a // 32) + -(-len_b // 32)
+    splits = max(1, min(512 // base, tiles // (2 if m_rows <= 32 else 8))) if base < 512 else 1
+    return base * splits * 128 * (d + 2) * 4 if splits > 1 else 0
 
 
 def shapes():
@@ -46,10 +57,12 @@ def shapes():
 def test_split_launches_fit_their_kernel():
     n_split = 0
     for hq, hkv, d, len_q, len_a, len_b, items, encode in shapes():
-        wave, splits, row_blocks, ws = plan(hq, hkv, d, len_q, len_a, len_b, items, encode)
+        wave, splits, row_blocks, ws, reserved = plan(hq, hkv, d, len_q, len_a, len_b, items, encode)
         where = (hq, hkv, d, len_q, len_a, len_b, items, encode)
         assert wave in (0, 1, 2) and splits >= 1, where
         assert ws <= 33 << 20, where                              # the allocation-free entry point's scratch
+        assert reserved == workspace_of_128_row_blocks(hq, hkv, d, len_q, len_a, len_b, items), where
+        assert ws <= reserved, where
         if not wave:
             continue
         m_rows, t = len_q * (hq // hkv), 32 * wave

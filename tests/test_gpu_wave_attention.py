@@ -9,6 +9,7 @@ import torch
 from oracle import rekv_oracle as O
 from paper_2503_00540_amd import workloads as W
 from paper_2503_00540_amd.rekv import Rekv
+from test_attention_plan import plan
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -143,3 +144,29 @@ def test_more_contexts_than_static_counter_slots():
             r.close()
         torch.cuda.synchronize()
         assert all(torch.equal(x, want) for x in got)
+
+
+def test_calls_captured_after_an_unsplit_launch_need_no_allocation():
+    """A live frame that one workgroup per row block serves leaves the workspace that splitting it would have left, so
+    that a question's retrieval and attention can be captured before they ever ran."""
+    g = torch.Generator().manual_seed(7)
+    mk = lambda *s: torch.randn(s, generator=g).bfloat16().to(DEV)
+    r, other = Rekv(28, 4, 128, 196), Rekv(28, 4, 128, 196)
+    assert plan(28, 4, 128, 196, 16 * 196, 196, encode=True)[1] == 1
+    k, v = mk(17 * 196, 4, 128), mk(17 * 196, 4, 128)
+    r.encode_chunk(mk(196, 28, 128), k, v, 16 * 196, 196, 1, 16 * 196)
+    q, kr, vr, ks, vs = mk(1, 32, 28, 128), mk(1, 3136, 4, 128), mk(1, 3136, 4, 128), mk(1, 32, 4, 128), mk(1, 32, 4, 128)
+    table = torch.randn((900, 512), generator=g).to(DEV)
+    assert plan(28, 4, 128, 32, 3136, 32)[1] > 1
+    want = other.qa_attention(q, kr, vr, ks, vs), other.retrieve_topk(table, 900, q, 16)[0]
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.stream(side), torch.cuda.graph(graph, stream=side):
+        got = r.qa_attention(q, kr, vr, ks, vs), r.retrieve_topk(table, 900, q, 16)[0]
+    torch.cuda.synchronize()
+    for _ in range(3):
+        for x in got:
+            x.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(got[0], want[0]) and torch.equal(got[1], want[1])
