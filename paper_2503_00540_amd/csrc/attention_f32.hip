@@ -175,6 +175,7 @@ __global__ __launch_bounds__(NW * 64) void attn_f32_mfma_kernel(AttnProblem p, i
     if (last_tok > p.len_q - 1) last_tok = p.len_q - 1;
     const int n_keys = seg.len_a + last_tok + q_pos0 + 1;             // keys any row of the block sees
     const int n_steps = (n_keys + KT - 1) / KT;
+    const int n_all = seg.len_a + rb * FR / G + q_pos0 + 1;           // keys every row of the block sees
     const int64_t qo = (((int64_t)item * p.len_q + tok) * p.n_q_heads + kvh * G + (row - tok * G)) * D;
 
     // row of segment A's token j in k_a / v_a: j itself, or through the frame index list
@@ -195,6 +196,7 @@ __global__ __launch_bounds__(NW * 64) void attn_f32_mfma_kernel(AttnProblem p, i
 #pragma unroll
         for (int e = 0; e < 4; ++e) o[b][e] = f32x4{0.f, 0.f, 0.f, 0.f};
     float m = -INFINITY, l = 0.f;
+    uint64_t dropped = 0;
     f32x4 kf[KB][QD / 4], vf[KB][4][VB];
     auto load_k = [&](int j0) {
 #pragma unroll
@@ -250,6 +252,32 @@ __global__ __launch_bounds__(NW * 64) void attn_f32_mfma_kernel(AttnProblem p, i
         for (int b = 0; b < VB; ++b)
 #pragma unroll
             for (int e = 0; e < 4; ++e) o[b][e] *= alpha;
+        // Where not every row sees every key, a probability of 0 keeps a value out only if that value is finite (0 * inf
+        // is NaN): a step with others takes none of its non-finite values, which are added after the loop.
+        if (j0 + KT > n_all) {
+            float nan_or_0 = 0.f;
+#pragma unroll
+            for (int kbk = 0; kbk < KB; ++kbk)
+#pragma unroll
+                for (int jj = 0; jj < 4; ++jj)
+#pragma unroll
+                    for (int b = 0; b < VB; ++b)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) nan_or_0 = fmaf(vf[kbk][jj][b][e], 0.f, nan_or_0);
+            const uint64_t some = __builtin_amdgcn_ballot_w64(nan_or_0 != 0.f);
+            if (some != 0) {
+                dropped |= some;
+#pragma unroll
+                for (int kbk = 0; kbk < KB; ++kbk)
+#pragma unroll
+                    for (int jj = 0; jj < 4; ++jj)
+#pragma unroll
+                        for (int b = 0; b < VB; ++b)
+#pragma unroll
+                            for (int e = 0; e < 4; ++e)
+                                vf[kbk][jj][b][e] = __builtin_fabsf(vf[kbk][jj][b][e]) < INFINITY ? vf[kbk][jj][b][e] : 0.f;
+            }
+        }
 #pragma unroll
         for (int kbk = 0; kbk < KB; ++kbk)
 #pragma unroll
@@ -263,8 +291,35 @@ __global__ __launch_bounds__(NW * 64) void attn_f32_mfma_kernel(AttnProblem p, i
                         o[b][e] = __builtin_amdgcn_mfma_f32_16x16x4f32(vf[kbk][jj][b][e], pj, o[b][e], 0, 0, 0);
             }
     }
-    l = quad_combine<false>(l);
     // lane (q = r, g), register i of block e of o[b]: dim b*64 + 4*(4g + i) + e
+    if (dropped != 0) {
+        // worked out again, so that the loop above does not carry in registers what only this block needs
+        const int lane2 = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+        const int g2 = lane2 >> 4, row2 = rb * FR + (lane2 & 15), tok2 = row2 / G;
+        const int n_vis2 = row2 < m_rows ? seg.len_a + tok2 + q_pos0 + 1 : 0;
+        const float* qrow = static_cast<const float*>(p.q) + (((int64_t)item * p.len_q + tok2) * p.n_q_heads + kvh * G + (row2 - tok2 * G)) * D;
+        for (int st = wave; st < n_steps; st += NW) {
+            if (st * KT + KT <= n_all) continue;
+            for (int j = st * KT; j < st * KT + KT && j < n_vis2; ++j) {
+                const float* krow = j < seg.len_a ? ka + a_row(j, k_dense) * row_stride : kb + (int64_t)(j - seg.len_a) * row_stride;
+                const float* vrow = j < seg.len_a ? va + a_row(j, false) * row_stride : vb + (int64_t)(j - seg.len_a) * row_stride;
+                float s = 0.f;
+#pragma unroll 1
+                for (int i = 0; i < D; ++i) s = fmaf(krow[i], qrow[i], s);
+                const float pj = expf(s * p.scale - (m == -INFINITY ? 0.f : m));
+#pragma unroll
+                for (int b = 0; b < VB; ++b)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            const float v = vrow[b * 64 + g2 * 16 + i * 4 + e];
+                            if (!(__builtin_fabsf(v) < INFINITY)) o[b][e][i] = fmaf(pj, v, o[b][e][i]);
+                        }
+            }
+        }
+    }
+    l = quad_combine<false>(l);
     float* out = static_cast<float*>(p.out) + qo;
     if constexpr (NW == 1) {
         if (!row_ok) return;

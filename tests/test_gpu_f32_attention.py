@@ -66,3 +66,26 @@ def test_indexed_keys_match_oracle(n_f, frames):
     for i in range(2):
         rk, rv = O.gather_kv(k, v, idx[i], n_f)
         assert np.abs(got[i] - O.decode_attention(q[i], rk, rv, kt[i], vt[i])).max() < TOL
+
+
+@pytest.mark.parametrize("d", [64, 128, 32])          # 32: the kernel on the vector ALU
+@pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan])
+@pytest.mark.parametrize("n_ret,n_text,n_new,hq,nq", [(0, 9, 9, 2, 1), (37, 50, 20, 3, 1), (200, 33, 33, 8, 40), (16, 40, 1, 16, 2)])
+def test_values_no_row_sees_stay_out(d, bad, n_ret, n_text, n_new, hq, nq):
+    """An infinity or NaN in a text token's value reaches exactly the rows that see the token, whatever shares a tile or a
+    row block with them; in the last visible key, which fills up ragged tiles, it stays what it is."""
+    rng = np.random.default_rng(n_text)
+    r = Rekv(hq, 1, d, 1, "f32")
+    g = lambda *shape: rng.standard_normal(shape).astype(np.float32)
+    q, kr, vr, kt, vt = g(nq, n_new, hq, d), g(nq, n_ret, 1, d), g(nq, n_ret, 1, d), g(nq, n_text, 1, d), g(nq, n_text, 1, d)
+    for at in sorted({n_text - n_new, n_text - n_new // 2 - 1, n_text - 1}):
+        broken = vt.copy()
+        broken[:, at, 0, ::3] = bad
+        got = r.decode_attention(dev(q), dev(kr), dev(vr), dev(kt), dev(broken), n_text).cpu().numpy()
+        seen = np.arange(n_text - n_new, n_text) >= at               # rows that see token `at`
+        for i in range(0, nq, 13):
+            ref = O.decode_attention(q[i], kr[i], vr[i], kt[i], vt[i])
+            assert np.abs(got[i][~seen] - ref[~seen]).max(initial=0) < TOL
+            assert np.abs(got[i][seen][..., 1::3] - ref[seen][..., 1::3]).max(initial=0) < TOL
+            hit = got[i][seen][..., ::3]
+            assert np.isnan(hit).all() if np.isnan(bad) else (hit == bad).all()
