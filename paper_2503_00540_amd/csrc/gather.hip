@@ -117,10 +117,14 @@ __global__ __launch_bounds__(GATHER_THREADS) void gather_layers_kernel(
 // base^(-2i/D) are set up once per workgroup in double precision; the angle position * theta_i
 // is formed and reduced to a fraction of a turn in double precision too, so positions in the
 // hundreds of thousands lose nothing, and the hardware sine and cosine take it from there.
+// Grid: blocks in x, a block's units interleaved over y, so that what is in flight spreads over many frames.  A run of units per
+// workgroup in address order, as the plain copy has it, is slower for keys (keys and values, us): 42 frames of 196 KB 10.3
+// against 9.4 so, 41 of 388 KB 15.1 and 14.0, 35 questions x 46 of 392 KB 349 and 293.  From host memory 512
+// workgroups and one per frame part take the same (51 MB: 557 us).
 template <bool BF16>
 __global__ __launch_bounds__(GATHER_THREADS) void gather_rope_kernel(
     const char* __restrict__ src_k, int n_src_frames, const int32_t* __restrict__ idx, int64_t n_blocks, int k_slots,
-    int n_f, int n_kv_heads, int d, int parts, char* __restrict__ dst_k, RopeArgs ra) {
+    int n_f, int n_kv_heads, int d, char* __restrict__ dst_k, RopeArgs ra) {
     constexpr int EPC = BF16 ? 8 : 4;            // elements per 16-byte chunk
     __shared__ double theta[128];                // D / 2 <= 128 pair frequencies
     const int half = d / 2;
@@ -130,17 +134,13 @@ __global__ __launch_bounds__(GATHER_THREADS) void gather_rope_kernel(
     const int cpr = half / EPC;                  // chunk pairs per head row
     const int units = n_f * n_kv_heads * cpr;
     const size_t row_bytes = (size_t)n_kv_heads * d * (BF16 ? 2 : 4);
-    // work item: part `w % parts` of a block (over (question, selected slot)), a run of its units
-    const int per_part = (units + parts - 1) / parts;
-    for (int64_t w = blockIdx.x; w < n_blocks * parts; w += gridDim.x) {
-        const int64_t blk = w / parts;
+    for (int64_t blk = blockIdx.x; blk < n_blocks; blk += gridDim.x) {     // over (question, selected slot)
         const int f = idx[blk];
         const bool have = f >= 0 && f < n_src_frames;
         const int slot = (int)(blk % k_slots);
         const char* src = src_k + (size_t)(have ? f : 0) * n_f * row_bytes;
         char* dst = dst_k + (size_t)blk * n_f * row_bytes;
-        const int u0 = (int)(w - blk * parts) * per_part, u1 = u0 + per_part < units ? u0 + per_part : units;
-        for (int u = u0 + threadIdx.x; u < u1; u += GATHER_THREADS) {
+        for (int u = blockIdx.y * GATHER_THREADS + threadIdx.x; u < units; u += gridDim.y * GATHER_THREADS) {
             const int c = u % cpr, th = u / cpr;     // th = token * Hkv + head
             const int tok = th / n_kv_heads;
             const size_t off = ((size_t)th * d + (size_t)c * EPC) * (BF16 ? 2 : 4);
@@ -223,18 +223,16 @@ hipError_t gather_rope_launch(const void* src_k, const void* src_v, bool src_on_
         if (e != hipSuccess) return e;
     }
     const int units = n_f * n_kv_heads * (d / 2) / (dtype == REKV_BF16 ? 8 : 4);
-    int parts = (units + GATHER_THREADS * 4 - 1) / (GATHER_THREADS * 4);   // about 4 units per thread
-    if (parts < 1) parts = 1;
-    int64_t grid = n_blocks * parts < (1 << 22) ? n_blocks * parts : (1 << 22);
-    if (src_on_host && grid > HOST_WORKGROUPS) grid = HOST_WORKGROUPS;
-    const dim3 kgrid((unsigned)grid);
+    int gy = (units + GATHER_THREADS * 4 - 1) / (GATHER_THREADS * 4);      // about 4 units per thread
+    if (gy < 1) gy = 1;
+    const dim3 kgrid((unsigned)(n_blocks < (1 << 22) ? n_blocks : (1 << 22)), (unsigned)gy);
     if (dtype == REKV_BF16)
         hipLaunchKernelGGL(gather_rope_kernel<true>, kgrid, dim3(GATHER_THREADS), 0, stream,
-                           static_cast<const char*>(src_k), n_src_frames, idx, n_blocks, k_slots, n_f, n_kv_heads, d, parts,
+                           static_cast<const char*>(src_k), n_src_frames, idx, n_blocks, k_slots, n_f, n_kv_heads, d,
                            static_cast<char*>(dst_k), ra);
     else
         hipLaunchKernelGGL(gather_rope_kernel<false>, kgrid, dim3(GATHER_THREADS), 0, stream,
-                           static_cast<const char*>(src_k), n_src_frames, idx, n_blocks, k_slots, n_f, n_kv_heads, d, parts,
+                           static_cast<const char*>(src_k), n_src_frames, idx, n_blocks, k_slots, n_f, n_kv_heads, d,
                            static_cast<char*>(dst_k), ra);
     return hipGetLastError();
 }
