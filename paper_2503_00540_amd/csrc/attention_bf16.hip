@@ -609,17 +609,27 @@ AttnPlan attn_bf16_plan(const AttnProblem& p) {
         // every workgroup 0.74 us (head_dim 64: 0.65); around it 7 us, or with split keys 10 us plus
         // the partial results' way out and back (0.48 us per MB), in a decode step 9.5 us plus the
         // merge's walk over the splits (0.04 us each at head_dim 128).
+        // A window counts as far as the stream behind it reaches.
         const int64_t rows = (int64_t)p.len_q * G < BM ? (int64_t)p.len_q * G : BM;
         const int64_t ik = (int64_t)p.n_items * p.n_kv_heads;
         const double part_mb = (double)(ik * splits * p.len_q * G * p.head_dim) * 4e-6;
-        const int64_t kv_tokens = p.is_encode ? p.l_l + (int64_t)p.n_items * p.len_b : (int64_t)p.n_items * (p.len_a + p.len_b);
-        const double kv_mb = rows > WM ? (double)(kv_tokens * p.n_kv_heads * p.head_dim) * 4e-6 : 0.0;
-        double us = (double)((n_tiles + splits - 1) / splits) * (p.head_dim == 64 ? 0.65 : 0.74);
-        if (splits == 1) us += 7.0;
-        else if (rows <= WM) us += 9.5 + 0.04 * splits * p.head_dim / 128;
-        else us += 10.0 + 0.48 * part_mb;
-        us += 0.1 * kv_mb;
-        attn_wave_plan(p, us, kv_mb, &plan);
+        int64_t len_a = len_a_max;
+        if (p.is_encode) {
+            const int64_t past = p.first_token + (int64_t)(p.n_items - 1) * p.len_b;
+            if (past < len_a) len_a = past;
+        }
+        const int64_t kv_tokens = p.is_encode ? len_a + (int64_t)p.n_items * p.len_b : p.n_items * (len_a + p.len_b);
+        AttnLoad load;
+        load.tiles = (len_a + BN - 1) / BN + (p.len_b + BN - 1) / BN;
+        load.kv_mb = (double)(kv_tokens * p.n_kv_heads * p.head_dim) * 4e-6;
+        load.splits = splits;
+        load.workgroups = base * splits;
+        load.us = (double)((load.tiles + splits - 1) / splits) * (p.head_dim == 64 ? 0.65 : 0.74);
+        if (splits == 1) load.us += 7.0;
+        else if (rows <= WM) load.us += 9.5 + 0.04 * splits * p.head_dim / 128;
+        else load.us += 10.0 + 0.48 * part_mb;
+        if (rows > WM) load.us += 0.1 * load.kv_mb;
+        attn_wave_plan(p, load, &plan);
     }
     return plan;
 }

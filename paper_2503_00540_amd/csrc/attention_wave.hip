@@ -563,29 +563,71 @@ hipError_t launch(const AttnProblem& p, const AttnPlan& plan, void* workspace, u
     return hipGetLastError();
 }
 
+// Where the estimates of attn_wave_plan are not close enough: up to 32 rows, where both kernels are a few microseconds of
+// latencies, and at head_dim 64.  There a launch is taken only if a finer estimate of its split (us) also lies below
+// 0.98 of the same for the 128-row kernel.  Reading through a frame index list costs that kernel more: of 2,900 such
+// launches 14 of 1,655 at head_dim 128 were over 3% slower here without this line and none of them by 10%, so it is
+// left out there; at head_dim 64 it takes 55 of 1,270 down to 15 at 1.0.  Both are least-squares fits to times replayed from a graph of 11,500 random shapes: heads
+// from 4/4/64 to 64/8/128; live chunks with windows of 2 to 77 frames on young and old streams, questions and decode
+// steps of 1 to 64 users over 1 to 64 frames; up to 32 rows the mean of K and V in the caches and from HBM, beyond HBM
+// alone, where the row blocks of a head, which walk the same tiles together, have little in flight.  Of 9,000 of the shapes
+// 79 (K and V warm) and 90 (cold) take over 3% longer than on the 128-row kernel; without this 639 and 722, up to 1.6
+// times as long (16/8/64, 392 tokens, a window of 60 frames from HBM: 39 us there, 64 here).
+struct WaveCost {      // around the steps; a 32-key step, and what it takes more where compute units hold two workgroups; ticket;
+    double fixed, step, step_of_two, ticket, split, split_10kb, kv_mb, row;    // per partial result; per 10 KB of it; K, V; merge per row
+};
+struct RowsCost {      // likewise; the merge launch; the partial results' way out and back per MB; its walk over the splits
+    double fixed, step, step_of_two, merge, part_mb, split, kv_mb;
+};
+bool wave_pays(const AttnProblem& p, const AttnLoad& other, const AttnPlan& plan) {
+    constexpr RowsCost ROWS[4] = {{4.634, 0.365, 0.244, 2.464, 0.604, 0.037, 0.087},      // up to 32 rows, D = 128
+                                  {4.473, 0.131, 0.305, 2.492, 0.703, 0.020, 0.055},      // D = 64
+                                  {3.802, 0.480, 0.152, 2.939, 0.867, 0.0, 0.073},        // more rows, D = 64, up to 8 MB of K and V
+                                  {5.714, 0.334, 0.206, 1.858, 0.875, 0.0, 0.052}};       // more than that
+    constexpr WaveCost WAVE[4][2] = {{{4.550, 1.969, 0.0, 3.691, 0.044, 0.009, 0.086, 0.045}},
+                                     {{3.910, 1.100, 1.469, 3.353, 0.048, 0.0, 0.087, 0.0}},
+                                     {{4.418, 0.901, 0.734, 3.586, 0.016, 0.0, 0.107, 0.0}, {5.508, 0.768, 0.371, 1.940, 0.0, 0.346, 0.045, 0.0}},
+                                     {{4.630, 1.087, 0.775, 3.546, 0.023, 0.0, 0.124, 0.0}, {5.498, 0.798, 0.349, 4.106, 0.0, 0.125, 0.124, 0.0}}};
+    const int64_t m_rows = (int64_t)p.len_q * (p.n_q_heads / p.n_kv_heads), ik = (int64_t)p.n_items * p.n_kv_heads;
+    const bool few = m_rows <= WM, d64 = p.head_dim == 64;
+    if (!d64 && (!few || p.a_index)) return true;
+    const int cls = few ? (d64 ? 1 : 0) : (other.kv_mb <= 8.0 ? 2 : 3);
+    const RowsCost& r = ROWS[cls];
+    double rows_us = r.fixed + (double)other.tiles / (double)other.splits * (r.step + (other.workgroups > 256 ? r.step_of_two : 0.0)) + r.kv_mb * other.kv_mb;
+    if (other.splits > 1)
+        rows_us += r.merge + r.part_mb * (double)(ik * other.splits * m_rows * p.head_dim) * 4e-6 + r.split * (double)other.splits;
+    const WaveCost& w = WAVE[cls][plan.wave - 1];
+    const int64_t s = plan.n_splits, T = plan.wave * WM, rows = m_rows < T ? m_rows : T;
+    double us = w.fixed + (double)other.tiles / (double)(s * (WAVES / plan.wave)) * (w.step + (ik * plan.m_tiles * s > 256 ? w.step_of_two : 0.0)) +
+                w.kv_mb * other.kv_mb + (few ? w.row * (double)rows : 0.0);
+    if (s > 1) us += w.ticket + (double)s * (w.split + w.split_10kb * (double)(rows * p.head_dim) * 4e-4);
+    return us < (p.a_index ? 1.0 : 0.98) * rows_us;
+}
+
 }  // namespace
 
-// The split with the least estimated time, if that beats `other_us`, the estimate for the 128-row
+// The split with the least estimated time, if that beats `other.us`, the estimate for the 128-row
 // kernel.  Fitted to launches of 7B- and 0.5B-class heads (28/4/128, 14/2/64), windows of 2 to 77 frames,
 // 1 to 9 questions: about 8 us before the first tile and after the last, a step of every wave
 // 1.25 us (head_dim 128, eight private tiles through the LDS; with 1.1 a live frame of 205 tokens with a window of 24 frames
 // came here and took 41.3 us with its frame vector, 38.8 there), 1.03 us (four tiles shared by
 // two waves), 0.63 us (head_dim 64; twice that with two workgroups on a CU); a ticket round 3 us plus
 // the last arriver's reading of the partial results, 0.04 us each and 0.07 MB/us.
-// kv_mb: K and V that several row blocks read, from HBM: here 0.36 us per MB on top (0.16 at head_dim 64; the row blocks of a
+// K and V that several row blocks read, from HBM: here 0.36 us per MB on top (0.16 at head_dim 64; the row blocks of a
 // head walk the same tiles together, one step ahead of their use: little in flight), there 0.1.  A
 // question over 64 frames (26 MB): 26.9 us with its KV in the caches and 35.9 without, there 30.8 and 33.2.
-bool attn_wave_plan(const AttnProblem& p, double other_us, double kv_mb, AttnPlan* plan) {
+bool attn_wave_plan(const AttnProblem& p, const AttnLoad& other, AttnPlan* plan) {
     const int G = p.n_q_heads / p.n_kv_heads, D = p.head_dim;
-    const int64_t m_rows = (int64_t)p.len_q * G, ik = (int64_t)p.n_items * p.n_kv_heads;
-    const int64_t len_a_max = p.is_encode ? p.l_l : p.len_a;
-    const int64_t n_tiles = (len_a_max + BN - 1) / BN + (p.len_b + BN - 1) / BN;
-    // A decode step over much KV is bound by HBM, and there the 128-row kernel's three tiles of prefetch
-    // count: 160 (question, head) pairs x 3.2 MB take 171 us there and 192 us here.
-    if (m_rows <= WM && ik * n_tiles * BN * D * 4 > (256ll << 20)) return false;
+    const int64_t m_rows = (int64_t)p.len_q * G, ik = (int64_t)p.n_items * p.n_kv_heads, n_tiles = other.tiles;
+    // Beyond what the last-level cache holds a launch is bound by HBM, where the 128-row kernel's three tiles of prefetch
+    // count: 102 shapes of more than 32 rows above this line took 1.0 to 1.13 times its time on average, between 128 and
+    // 256 MB 0.76 to 0.80 with K and V warm and 1.03 cold; 160 (question, head) pairs x 3.2 MB of a decode step 171 us there
+    // and 192 us here.  (Frames read in place are fewer than their count: questions share them.)
+    if ((m_rows <= WM || !p.a_index) && other.kv_mb > 268.0) return false;
     const int64_t slots = D == 64 ? 512 : 256;   // resident workgroups: LDS holds one (D = 128) or two per CU
-    double best = 0.98 * other_us;
-    bool take = false;
+    const double kv_us = m_rows > WM ? (D == 64 ? 0.16 : 0.36) * other.kv_mb : 0.0;
+    double best = 0.98 * other.us;
+    AttnPlan split = *plan;
     for (int rw = 1; rw <= 2; ++rw) {
         const int64_t T = rw * WM, kg = WAVES / rw;
         if (rw > 1 && m_rows <= WM) break;
@@ -596,19 +638,19 @@ bool attn_wave_plan(const AttnProblem& p, double other_us, double kv_mb, AttnPla
             const size_t ws = s > 1 ? (size_t)(base * s) * T * (size_t)(D + 2) * sizeof(float) : 0;
             if (ws > plan->reserve_bytes || (s > 1 && merge_lds_bytes(s, T) > tile_lds_bytes(D))) break;
             const int64_t steps = (n_tiles + s * kg - 1) / (s * kg);
-            double us = 8.0 + (double)steps * step_us * (base * s > 256 ? 2.0 : 1.0);
-            us += (D == 64 ? 0.16 : 0.36) * kv_mb;
+            double us = 8.0 + (double)steps * step_us * (base * s > 256 ? 2.0 : 1.0) + kv_us;
             if (s > 1) us += 3.0 + (double)s * (0.04 + (double)(rows * D * 4) * 1.4e-5);
             if (us >= best) continue;
             best = us;
-            take = true;
-            plan->wave = rw;
-            plan->n_splits = (int32_t)s;
-            plan->m_tiles = (int32_t)m_tiles;
-            plan->workspace_bytes = ws;
+            split.wave = rw;
+            split.n_splits = (int32_t)s;
+            split.m_tiles = (int32_t)m_tiles;
+            split.workspace_bytes = ws;
         }
     }
-    return take;
+    if (!split.wave || !wave_pays(p, other, split)) return false;
+    *plan = split;
+    return true;
 }
 
 hipError_t attn_wave_launch(const AttnProblem& p, const AttnPlan& plan, void* workspace, uint32_t* tickets,

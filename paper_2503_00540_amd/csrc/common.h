@@ -89,13 +89,21 @@ struct AttnPlan {
     size_t workspace_bytes, reserve_bytes;
 };
 AttnPlan attn_bf16_plan(const AttnProblem& p);
+// What the time of a launch is estimated from: the 32-key tiles of the longest item, the MB of K and V of all items, the
+// splits of the 128-row kernel and the workgroups these make, and that kernel's estimate (us).
+struct AttnLoad {
+    int64_t tiles;
+    double kv_mb;
+    int64_t splits, workgroups;
+    double us;
+};
 hipError_t attn_bf16_launch(const AttnProblem& p, const AttnPlan& plan, void* workspace,
                             hipStream_t stream);
-// attn_wave_plan: true if that kernel takes the problem (other_us: what it has to beat; plan->reserve_bytes: the most
+// attn_wave_plan: true if that kernel takes the problem (other: what it has to beat; plan->reserve_bytes: the most
 // workspace it may ask for).  tickets: WAVE_TICKETS zeroed words that only
 // calls ordered on one stream use.
 constexpr int WAVE_TICKETS = 512;
-bool attn_wave_plan(const AttnProblem& p, double other_us, double kv_mb, AttnPlan* plan);
+bool attn_wave_plan(const AttnProblem& p, const AttnLoad& other, AttnPlan* plan);
 hipError_t attn_wave_launch(const AttnProblem& p, const AttnPlan& plan, void* workspace, uint32_t* tickets,
                             hipStream_t stream);
 hipError_t attn_f32_launch(const AttnProblem& p, hipStream_t stream);

@@ -76,3 +76,30 @@ def test_split_launches_fit_their_kernel():
         last = m_rows - (row_blocks - 1) * t
         assert max(last_arriver_lds(wave, splits, rows, d) for rows in {last, min(m_rows, t)}) <= 8 * 2 * 32 * d * 2, where
     assert n_split > 1000
+
+
+@pytest.mark.parametrize("hq,hkv,d,l_x,items", [(8, 2, 128, 66, 1), (28, 4, 128, 196, 1), (14, 2, 64, 144, 2), (16, 8, 64, 392, 1)])
+@pytest.mark.parametrize("past", [0, 66, 1000])
+def test_a_window_counts_as_far_as_the_stream_reaches(hq, hkv, d, l_x, items, past):
+    """A window that is not full is split like one of the stream's length, not for tiles that do not exist."""
+    reach = past + (items - 1) * l_x
+    chosen = plan(hq, hkv, d, l_x, 15_000, l_x, items, True, past)
+    assert chosen[0] > 0
+    assert chosen[1] <= max(1, -(-(-(-reach // 32) + -(-l_x // 32)) // (8 // chosen[0])))
+    assert chosen[:4] == plan(hq, hkv, d, l_x, 1 << 24, l_x, items, True, past)[:4]
+
+
+@pytest.mark.parametrize("d,hq,hkv,len_q", [(64, 16, 8, 25), (128, 64, 8, 1), (64, 14, 2, 1)])
+def test_beyond_the_last_level_cache_the_128_row_kernel(d, hq, hkv, len_q):
+    for len_a in (4000, 8000, 20_000):
+        items = -(-270_000_000 // (len_a * hkv * d * 4))
+        assert plan(hq, hkv, d, len_q, len_a, len_q, items)[0] == 0
+
+
+@pytest.mark.parametrize("hq,hkv,d,len_q,len_a,encode", [
+    (16, 8, 64, 392, 60 * 196, True),        # 39 us with 128-row workgroups and K and V from HBM, 64 without
+    (16, 8, 64, 8, 31 * 196, False),         # 10.4 and 11.5
+    (28, 4, 128, 1, 3 * 144, False),         # 8.1 and 10.1 from HBM
+])
+def test_launches_that_splitting_the_keys_slows_down(hq, hkv, d, len_q, len_a, encode):
+    assert plan(hq, hkv, d, len_q, len_a, len_q, 1, encode)[0] == 0
