@@ -95,3 +95,17 @@ int main(void) {{
            "-L", lib_dir, "-l:librekv.so", "-Wl,--unresolved-symbols=ignore-in-shared-libs", "-o", str(exe)]
     p = subprocess.run(cmd, capture_output=True, text=True)
     assert p.returncode == 0, p.stderr
+
+
+def test_binding_imports_with_a_torch_that_lacks_the_raw_stream_lookup():
+    """The two private names only make the stream lookup cheaper: without them (a CPU-only build) the import works."""
+    import subprocess
+    import sys
+    code = ("import torch\n"
+            "for name in ('_cuda_getDevice', '_cuda_getCurrentRawStream'):\n"
+            "    if hasattr(torch._C, name): delattr(torch._C, name)\n"
+            "torch.cuda.current_stream = lambda: type('S', (), {'cuda_stream': 77})\n"
+            "from paper_2503_00540_amd import rekv\n"
+            "assert rekv._stream() == 77\n")
+    p = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True)
+    assert p.returncode == 0, p.stderr
