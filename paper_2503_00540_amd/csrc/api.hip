@@ -762,12 +762,14 @@ rekv_status rekv_probe_mfma(rekv_ctx* c, float* sink, int32_t n_workgroups, int3
 // row blocks, workspace bytes, bytes the context holds after the call.
 void rekv_internal_attention_plan(int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim, int32_t is_encode,
                                   int64_t first_token, int32_t n_items, int32_t len_q, int32_t len_a, int32_t len_b,
-                                  int64_t out[5]) {
+                                  int32_t in_place, int64_t out[5]) {
     rekv::AttnProblem p;
     memset(&p, 0, sizeof(p));
     p.n_q_heads = n_q_heads; p.n_kv_heads = n_kv_heads; p.head_dim = head_dim; p.is_encode = is_encode;
     p.first_token = first_token; p.n_items = n_items; p.len_q = len_q; p.len_b = len_b;
     (is_encode ? p.l_l : p.len_a) = len_a;
+    static const int32_t some_index = 0;         // only whether there is a list matters
+    if (in_place) p.a_index = &some_index;
     const rekv::AttnPlan plan = rekv::attn_bf16_plan(p);
     out[0] = plan.wave; out[1] = plan.n_splits; out[2] = plan.m_tiles; out[3] = (int64_t)plan.workspace_bytes;
     out[4] = (int64_t)plan.reserve_bytes;

@@ -9,13 +9,13 @@ import pytest
 from paper_2503_00540_amd import rekv
 
 
-def plan(hq, hkv, d, len_q, len_a, len_b, items=1, encode=False, first=1 << 40):
+def plan(hq, hkv, d, len_q, len_a, len_b, items=1, encode=False, first=1 << 40, in_place=False):
     """(row waves per workgroup or 0 for the 128-row kernel, splits, row blocks, workspace bytes, reserved bytes)"""
     f = rekv.lib().rekv_internal_attention_plan
     f.restype = None
-    f.argtypes = [ctypes.c_int32] * 4 + [ctypes.c_int64] + [ctypes.c_int32] * 4 + [ctypes.c_void_p]
+    f.argtypes = [ctypes.c_int32] * 4 + [ctypes.c_int64] + [ctypes.c_int32] * 5 + [ctypes.c_void_p]
     out = (ctypes.c_int64 * 5)()
-    f(hq, hkv, d, int(encode), first, items, len_q, len_a, len_b, out)
+    f(hq, hkv, d, int(encode), first, items, len_q, len_a, len_b, int(in_place), out)
     return tuple(out)
 
 

@@ -83,6 +83,9 @@ def test_short_last_block(n_frames, b):
 def test_short_retrieval_between_split_attention():
     """Both take their arrival counters from the same words, which every launch leaves at zero."""
     from paper_2503_00540_amd.rekv import Rekv
+    from test_attention_plan import plan
+    chosen = plan(28, 4, 128, 9, 40 * 49, 9, 2)
+    assert chosen[0] == 1 and chosen[1] > 1
     g = torch.Generator().manual_seed(3)
     r = Rekv(28, 4, 128, 49, "bf16")
     table = torch.randn((200, 512), generator=g).cuda()
