@@ -111,11 +111,17 @@ def cmd_trace(argv):
             text.append("This run includes the benchmark's extras: the launches on all-zero inputs are among those calls and "
                         "pull the average down (they are the fastest ones); the trace of the --no-extras command holds the "
                         "timed configuration alone.")
-        # the workload's own algorithmic FLOP per launch, as the benchmark line of the same run states it
-        flop = b["roofline"]["algorithmic_flop_per_launch"] if b else ENCODE_FLOP_C1
-        what = b["config"]["workload"].split(":")[0] if b else "C1-7B-1layer"
-        text.append(f"{what}: {flop:.4e} algorithmic FLOP per launch -> {flop / avg / 1e3:.0f} TFLOP/s = "
-                    f"{100 * flop / avg / 1e3 / 2500:.1f} % of the 2.5 PFLOP/s bf16 MFMA peak.")
+        # the workload's own algorithmic FLOP per launch, as the benchmark line of the same run states it; without that line
+        # they are known for the default workload only
+        workload = re.search(r"--workload[ =](\S+)", command)
+        flop = what = None
+        if b:
+            flop, what = b["roofline"]["algorithmic_flop_per_launch"], b["config"]["workload"].split(":")[0]
+        elif not workload or workload.group(1) == "C1":
+            flop, what = ENCODE_FLOP_C1, "C1-7B-1layer"
+        if flop:
+            text.append(f"{what}: {flop:.4e} algorithmic FLOP per launch -> {flop / avg / 1e3:.0f} TFLOP/s = "
+                        f"{100 * flop / avg / 1e3 / 2500:.1f} % of the 2.5 PFLOP/s bf16 MFMA peak.")
     if b and "offloaded" in b["config"]["workload"] and enc:
         text.append(f"Under the profiler the offload copies on the side stream slow the encode launches they overlap: the "
                     f"step's first launch, which overlaps none, is the minimum ({min(v) / 1e3:.1f} us); without the profiler "

@@ -91,3 +91,19 @@ def test_bench_quotes_traffic_only_for_the_source_it_was_measured_on(tmp_path, m
     sha_new = hashlib.sha256(b"// kernel v2\n").hexdigest()
     (root / bench.TRAFFIC_PROFILE["C1-7B-1layer"]).write_text(f"traffic_bytes_per_launch: 123\nkernel_source_sha256: {sha_new}\n")
     assert bench.measured_traffic("C1-7B-1layer")[0] == 123
+
+
+def test_trace_summary_prices_a_launch_only_with_its_own_workloads_flop(tmp_path):
+    """Without the benchmark's line only the default workload's FLOP are known."""
+    d = str(tmp_path / "run")
+    _write_run(d, [(1, ENC, 37748736, 0, 21_000_000)])
+    out = str(tmp_path / "trace.txt")
+    for command, priced in (("python3 bench.py --no-extras", True), ("python3 bench.py --workload C1 --no-extras", True),
+                            ("python3 bench.py --no-extras --workload C4", False), ("python3 bench.py --workload=C3", False)):
+        PS.main(["trace", d, out, command])
+        assert ("TFLOP/s" in open(out).read()) == priced, command
+    line = tmp_path / "bench.json"
+    line.write_text('{"roofline": {"algorithmic_flop_per_launch": 2.1e13, "avg_launch_ms": 21.0, "frac": 0.4}, '
+                    '"config": {"workload": "C4-72B: 64 questions"}}\n')
+    PS.main(["trace", d, out, "python3 bench.py --workload C4", "--bench-json", str(line)])
+    assert "C4-72B: 2.1000e+13 algorithmic FLOP per launch -> 1000 TFLOP/s" in open(out).read()
