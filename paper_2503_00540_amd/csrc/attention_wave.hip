@@ -17,11 +17,11 @@
 //
 // What bounds it.  These launches are a chain of latencies: about 2 us to the first tile in LDS, 1 us
 // for the waves' merge, 3 us for ticket and last arriver; between them a step of 32 keys per wave takes
-// 1.1 us because eight private K/V tiles (128 KB) come through the CU's 64 B/clk path from L2.
+// 1.25 us because eight private K/V tiles (128 KB) come through the CU's 64 B/clk path from L2.
 // Measured against splitting 128-row workgroups over the keys with a merge launch (as replayed from a
-// graph, us): 7B-class live frame, 16-frame window 32.9 -> 23.3; 0.5B-class 18.9 -> 13.4; one
-// question over 16 frames 16.3 -> 13.0, four of them 25.8 -> 17.0; a decode step over 64 frames 16.1 ->
-// 14.8.  A software-pipelined step (S of the next tile during the softmax, as in
+// graph, us; K and V in the caches, then from HBM): 7B-class live frame, 16-frame window 32.4 -> 22.4, 32.1 -> 29.1; 0.5B-class
+// 18.3 -> 12.7, 18.8 -> 13.4; one question over 16 frames 16.2 -> 13.1, 17.1 -> 14.5; a decode step over 64 frames 16.0 ->
+// 13.9, 18.1 -> 15.9.  A software-pipelined step (S of the next tile during the softmax, as in
 // attention_bf16.hip) measured no faster here and needs 20 to 30 registers more.
 #include "attention_mfma.h"
 
@@ -563,45 +563,39 @@ hipError_t launch(const AttnProblem& p, const AttnPlan& plan, void* workspace, u
     return hipGetLastError();
 }
 
-// Where the estimates of attn_wave_plan are not close enough: up to 32 rows, where both kernels are a few microseconds of
-// latencies, and at head_dim 64.  There a launch is taken only if a finer estimate of its split (us) also lies below
-// 0.98 of the same for the 128-row kernel.  Reading through a frame index list costs that kernel more: of 2,900 such
-// launches 14 of 1,655 at head_dim 128 were over 3% slower here without this line and none of them by 10%, so it is
-// left out there; at head_dim 64 it takes 55 of 1,270 down to 15 at 1.0.  Both are least-squares fits to times replayed from a graph of 11,500 random shapes: heads
-// from 4/4/64 to 64/8/128; live chunks with windows of 2 to 77 frames on young and old streams, questions and decode
-// steps of 1 to 64 users over 1 to 64 frames; up to 32 rows the mean of K and V in the caches and from HBM, beyond HBM
-// alone, where the row blocks of a head, which walk the same tiles together, have little in flight.  Of 9,000 of the shapes
-// 79 (K and V warm) and 90 (cold) take over 3% longer than on the 128-row kernel; without this 639 and 722, up to 1.6
-// times as long (16/8/64, 392 tokens, a window of 60 frames from HBM: 39 us there, 64 here).
+// head_dim 64 with more than 32 rows, where the estimates of attn_wave_plan are not close enough once K and V come from HBM: the
+// row blocks of a head walk the same tiles together and have little in flight.  There a launch is taken only if a finer
+// estimate of its split (us) also lies below 0.98 of the same for the 128-row kernel.  Both are least-squares fits to times
+// from HBM, replayed from a graph, of 4,100 random shapes (heads from 4/4/64 to 24/8/64; live chunks with windows of 2 to 77
+// frames on young and old streams, questions of 1 to 64 users over 1 to 64 frames).  Without this line 7% of such launches
+// take over 3% longer than on the 128-row kernel, up to 1.6 times as long (16/8/64, 392 tokens, a window of 60 frames: 39 us
+// there, 64 here), with it 2%.  Frames read in place cost the 128-row kernel more: there all are taken.
+// Up to 32 rows a line like this was not worth it: replayed from a graph 14 (K and V warm) and 26 (from HBM) of 170 decode steps
+// are over 3% slower here, by 25% at most, but issued one by one only one of each is, because the 128-row kernel's merge is a
+// second launch (9 us a call here and 11.6 there where both kernels together take 7 to 10).
 struct WaveCost {      // around the steps; a 32-key step, and what it takes more where compute units hold two workgroups; ticket;
-    double fixed, step, step_of_two, ticket, split, split_10kb, kv_mb, row;    // per partial result; per 10 KB of it; K, V; merge per row
+    double fixed, step, step_of_two, ticket, split, split_10kb, kv_mb;    // per partial result; per 10 KB of it; K and V per MB
 };
-struct RowsCost {      // likewise; the merge launch; the partial results' way out and back per MB; its walk over the splits
-    double fixed, step, step_of_two, merge, part_mb, split, kv_mb;
+struct RowsCost {      // likewise; the merge launch; the partial results' way out and back per MB
+    double fixed, step, step_of_two, merge, part_mb, kv_mb;
 };
 bool wave_pays(const AttnProblem& p, const AttnLoad& other, const AttnPlan& plan) {
-    constexpr RowsCost ROWS[4] = {{4.634, 0.365, 0.244, 2.464, 0.604, 0.037, 0.087},      // up to 32 rows, D = 128
-                                  {4.473, 0.131, 0.305, 2.492, 0.703, 0.020, 0.055},      // D = 64
-                                  {3.802, 0.480, 0.152, 2.939, 0.867, 0.0, 0.073},        // more rows, D = 64, up to 8 MB of K and V
-                                  {5.714, 0.334, 0.206, 1.858, 0.875, 0.0, 0.052}};       // more than that
-    constexpr WaveCost WAVE[4][2] = {{{4.550, 1.969, 0.0, 3.691, 0.044, 0.009, 0.086, 0.045}},
-                                     {{3.910, 1.100, 1.469, 3.353, 0.048, 0.0, 0.087, 0.0}},
-                                     {{4.418, 0.901, 0.734, 3.586, 0.016, 0.0, 0.107, 0.0}, {5.508, 0.768, 0.371, 1.940, 0.0, 0.346, 0.045, 0.0}},
-                                     {{4.630, 1.087, 0.775, 3.546, 0.023, 0.0, 0.124, 0.0}, {5.498, 0.798, 0.349, 4.106, 0.0, 0.125, 0.124, 0.0}}};
+    constexpr RowsCost ROWS[2] = {{3.802, 0.480, 0.152, 2.939, 0.867, 0.073},       // up to 8 MB of K and V
+                                  {5.714, 0.334, 0.206, 1.858, 0.875, 0.052}};      // more than that
+    constexpr WaveCost WAVE[2][2] = {{{4.418, 0.901, 0.734, 3.586, 0.016, 0.0, 0.107}, {5.508, 0.768, 0.371, 1.940, 0.0, 0.346, 0.045}},
+                                     {{4.630, 1.087, 0.775, 3.546, 0.023, 0.0, 0.124}, {5.498, 0.798, 0.349, 4.106, 0.0, 0.125, 0.124}}};
     const int64_t m_rows = (int64_t)p.len_q * (p.n_q_heads / p.n_kv_heads), ik = (int64_t)p.n_items * p.n_kv_heads;
-    const bool few = m_rows <= WM, d64 = p.head_dim == 64;
-    if (!d64 && (!few || p.a_index)) return true;
-    const int cls = few ? (d64 ? 1 : 0) : (other.kv_mb <= 8.0 ? 2 : 3);
-    const RowsCost& r = ROWS[cls];
+    if (p.a_index || p.head_dim != 64 || m_rows <= WM) return true;
+    const int large = other.kv_mb > 8.0;
+    const RowsCost& r = ROWS[large];
     double rows_us = r.fixed + (double)other.tiles / (double)other.splits * (r.step + (other.workgroups > 256 ? r.step_of_two : 0.0)) + r.kv_mb * other.kv_mb;
-    if (other.splits > 1)
-        rows_us += r.merge + r.part_mb * (double)(ik * other.splits * m_rows * p.head_dim) * 4e-6 + r.split * (double)other.splits;
-    const WaveCost& w = WAVE[cls][plan.wave - 1];
+    if (other.splits > 1) rows_us += r.merge + r.part_mb * (double)(ik * other.splits * m_rows * p.head_dim) * 4e-6;
+    const WaveCost& w = WAVE[large][plan.wave - 1];
     const int64_t s = plan.n_splits, T = plan.wave * WM, rows = m_rows < T ? m_rows : T;
     double us = w.fixed + (double)other.tiles / (double)(s * (WAVES / plan.wave)) * (w.step + (ik * plan.m_tiles * s > 256 ? w.step_of_two : 0.0)) +
-                w.kv_mb * other.kv_mb + (few ? w.row * (double)rows : 0.0);
+                w.kv_mb * other.kv_mb;
     if (s > 1) us += w.ticket + (double)s * (w.split + w.split_10kb * (double)(rows * p.head_dim) * 4e-4);
-    return us < (p.a_index ? 1.0 : 0.98) * rows_us;
+    return us < 0.98 * rows_us;
 }
 
 }  // namespace

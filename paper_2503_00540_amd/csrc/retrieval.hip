@@ -96,7 +96,8 @@ __global__ __launch_bounds__(256) void frame_keys_kernel(const void* __restrict_
 // thread's loads leave together, up to 16 of them (the rows past the end are masked, not looped
 // over one by one: each turn of such a loop costs a memory round trip).  What bounds it is that one
 // round trip: 28 questions of 48 tokens 8.9 us with a workgroup per (question, KV group) and a loop over the
-// last 8 rows, 4.2 so; 64 questions of 32 tokens at 64/8/128 (33.5 MB) 11 and 9.9.
+// last 8 rows, 4.2 so.  Many questions that the caches hold are slower this way: 64 of 32 tokens at 64/8/128 (33.5 MB) 7.7
+// and 10.2 (the retrieval they are part of 29.9 and 28.1 warm, 33.0 and 30.7 from HBM, with its other kernels' changes).
 // ---------------------------------------------------------------------------------------
 constexpr int POOL_THREADS = 512;
 constexpr int POOL_LANES = 8;                  // 16-byte lanes per head

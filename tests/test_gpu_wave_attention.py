@@ -50,7 +50,7 @@ def test_the_bound_sees_a_lost_key_range():
 @pytest.mark.parametrize("hq,hkv,d,n_new,n_ret,n_text,row_waves", [
     (1, 1, 128, 1, 0, 1, 0),            # one row, one key: the 128-row kernel
     (7, 1, 128, 1, 31, 5, 0),
-    (8, 1, 128, 4, 224, 32, 0),         # exactly 32 rows, exactly 8 tiles
+    (8, 1, 128, 4, 224, 32, 1),         # exactly 32 rows, exactly 8 tiles
     (1, 1, 128, 1, 150, 8, 1),          # fewer tiles than key runs
     (3, 1, 64, 11, 225, 40, 1),         # 33 rows: a block of one row; a tile of one key
     (16, 2, 64, 4, 4000, 9, 0),
@@ -111,6 +111,21 @@ def test_every_path_matches_oracle(hq, hkv, d, n_new, n_ret, n_text, nq, want):
         got = outs[0].float().cpu().numpy()
         for i, n in enumerate(valid):
             assert agrees(got[i], O.decode_attention(q[i], kr[i, :n], vr[i, :n], kt[i], vt[i])), (i, n)
+
+
+@gpu
+@pytest.mark.parametrize("n_ret", [975_343, 1_045_000])
+def test_the_longest_context_matches_oracle(n_ret):
+    """One row over a million keys: the most splits the last arriver's LDS has room for."""
+    wave, splits, *_ = plan(1, 1, 64, 1, n_ret, 1)
+    assert wave == 1 and splits > 200
+    g = torch.Generator().manual_seed(n_ret)
+    q, kr, vr, kt, vt = [torch.randn((1, n, 1, 64), generator=g).bfloat16() for n in (1, n_ret, n_ret, 1, 1)]
+    r = Rekv(1, 1, 64, 1)
+    outs = [r.decode_attention(*(x.to(DEV) for x in (q, kr, vr, kt, vt)), 1, no_alloc=bool(i)) for i in range(2)]
+    assert torch.equal(outs[0], outs[1])
+    ref = O.decode_attention(*(x[0].double().numpy() for x in (q, kr, vr, kt, vt)))
+    assert agrees(outs[0][0].float().cpu().numpy(), ref)
 
 
 @gpu
