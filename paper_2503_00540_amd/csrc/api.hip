@@ -152,10 +152,9 @@ rekv_status reserve(rekv_ctx* c, Buffer* ws, Buffer* other, size_t bytes, size_t
     return REKV_OK;
 }
 
-// What a workspace starts with.  Attention: nearly every launch of attention_wave.hip asks for less than 8 MiB, so that most
-// contexts allocate once (growing costs a hipFree, a hipMalloc and the device's idling).  Retrieval has a block of its own, so
-// that a question's first attention does not wait for the retrieval to free it, and a context that only needs
-// scores does not pay for the larger one.
+// What a workspace starts with.  Attention: with 8 MiB a context of short calls allocates once (growing costs a hipFree, a
+// hipMalloc and the device's idling).  Retrieval has a block of its own, so that a question's first attention does not wait
+// for the retrieval to free it, and a context that only needs scores does not pay for the larger one.
 constexpr size_t ATTENTION_WS = size_t(8) << 20, RETRIEVAL_WS = size_t(1) << 20;
 
 // fixed != NULL: the launch may use only that scratch (no allocation); otherwise the context's
