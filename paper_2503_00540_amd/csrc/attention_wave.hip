@@ -567,9 +567,10 @@ hipError_t launch(const AttnProblem& p, const AttnPlan& plan, void* workspace, u
 // row blocks of a head walk the same tiles together and have little in flight.  There a launch is taken only if a finer
 // estimate of its split (us) also lies below 0.98 of the same for the 128-row kernel.  Both are least-squares fits to times
 // from HBM, replayed from a graph, of 4,100 random shapes (heads from 4/4/64 to 24/8/64; live chunks with windows of 2 to 77
-// frames on young and old streams, questions of 1 to 64 users over 1 to 64 frames).  Without this line 7% of such launches
-// take over 3% longer than on the 128-row kernel, up to 1.6 times as long (16/8/64, 392 tokens, a window of 60 frames: 39 us
-// there, 64 here), with it 2%.  Frames read in place cost the 128-row kernel more: there all are taken.
+// frames on young and old streams, questions of 1 to 64 users over 1 to 64 frames).  Of 900 more with over 8 MB of K and V
+// 162 take over 3% longer than on the 128-row kernel without this line, up to 1.6 times as long (16/8/64, 392 tokens, a
+// window of 60 frames: 39 us there, 64 here), and 46 with it, 1.28 at most.  Frames read in place cost the 128-row kernel
+// more: there all are taken.
 // Up to 32 rows a line like this was not worth it: replayed from a graph 14 (K and V warm) and 26 (from HBM) of 170 decode steps
 // are over 3% slower here, by 25% at most, but issued one by one only one of each is, because the 128-row kernel's merge is a
 // second launch (9 us a call here and 11.6 there where both kernels together take 7 to 10).
