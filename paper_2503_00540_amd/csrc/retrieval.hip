@@ -12,6 +12,9 @@ namespace {
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
+template <int I>
+using IC = std::integral_constant<int, I>;
+
 // 16-byte load that is not kept in the caches (a table row is read once per pass)
 __device__ inline float4 load_stream(const float* p) {
     const f32x4 v = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(p));
@@ -29,19 +32,25 @@ __device__ inline float wave_sum(float v) {
 
 // ---------------------------------------------------------------------------------------
 // Frame vectors: v_f = (1/N_f) sum_j k_{f,j}, heads concatenated.
-// One workgroup streams one frame (a contiguous N_f x D' block) front to back: LPR lanes
-// cover a key row with 16-byte loads (8 bf16 or 4 fp32 each), the 256 / LPR row groups take
-// alternate rows, eight loads are in flight per thread, and the row groups' partial sums
-// meet in LDS.  Rows wider than 256 lanes are split over blockIdx.y.  The last frame may be short (n_rows in
-// all; a stream's last block of frames).
+// A workgroup streams a slab of columns of one frame (a contiguous N_f x D' block): LPR lanes cover the
+// slab's row with 16-byte loads (8 bf16 or 4 fp32 each), the 256 / LPR row groups take alternate rows, and their
+// partial sums meet in LDS.  A thread's loads leave together, up to eight, and the rows that are left over as one
+// batch of just as many (the last row read twice where a row group has one less): each turn of a loop costs a memory round
+// trip, and with few frames those are the whole time.  Hence also the slab: 128 bytes wide, 32 row groups, one
+// or two batches per thread (mean_rows_launch).  The last frame may be short (n_rows in all; a stream's last block of
+// frames).  Many frames are bound by HBM.  Measured with whole rows per workgroup and a loop over the left-over rows, then
+// so (us, replayed from a graph; keys in the caches / from HBM): one frame of 196 x 512 4.4 / 6.6 -> 2.4 / 2.4, of 196 x 128 2.7 / 4.3 ->
+// 2.2 / 2.6, 64 frames of 196 x 512 7.5 / 8.3 -> 3.4 / 4.7, 256 of them 8.9 / 11.0 -> 7.8 / 10.0 (5.3 TB/s).
 // ---------------------------------------------------------------------------------------
-template <bool BF16>
+// ONE: a frame has no more rows than there are row groups (block vectors, tiny frames): less code to fetch.
+template <bool BF16, bool ONE>
 __global__ __launch_bounds__(256) void frame_keys_kernel(const void* __restrict__ k, int n_f_all, int64_t n_rows,
                                                          int d_prime, int lpr_log2,
                                                          float* __restrict__ out) {
     constexpr int VEC = BF16 ? 8 : 4;
     constexpr int ES = BF16 ? 2 : 4;
-    __shared__ float red[256 * VEC];
+    __shared__ __attribute__((aligned(16))) float red[256 * VEC];    // [row group][column of the slab]
+    __shared__ float part[256];
     const int lpr = 1 << lpr_log2, n_rg = 256 >> lpr_log2;
     const int cl = threadIdx.x & (lpr - 1), rg = threadIdx.x >> lpr_log2;
     const int col = (blockIdx.y * lpr + cl) * VEC;
@@ -53,38 +62,76 @@ __global__ __launch_bounds__(256) void frame_keys_kernel(const void* __restrict_
     if (col < d_prime) {
         const char* base = static_cast<const char*>(k) + (row0 * (int64_t)d_prime + col) * ES;
         const int64_t pitch = (int64_t)d_prime * ES;
-        auto add = [&](const u32x4& w) {
-            if (BF16) {
+        auto add = [&](const u32x4& w, bool on) {
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    acc[2 * i] += bf16_lo(w[i]);
-                    acc[2 * i + 1] += bf16_hi(w[i]);
+            for (int i = 0; i < 4; ++i) {
+                if (BF16) {
+                    acc[2 * i] += on ? bf16_lo(w[i]) : 0.f;
+                    acc[2 * i + 1] += on ? bf16_hi(w[i]) : 0.f;
+                } else {
+                    acc[i] += on ? __uint_as_float(w[i]) : 0.f;
                 }
-            } else {
-#pragma unroll
-                for (int i = 0; i < 4; ++i) acc[i] += __uint_as_float(w[i]);
             }
         };
-        constexpr int U = 8;
-        int j = rg;
-        for (; j + n_rg * (U - 1) < n_f; j += n_rg * U) {
+        // n loads that leave together; where rows may be missing, the last one is read again and its values left out
+        auto batch = [&](int j, auto n, auto whole) __attribute__((always_inline)) {
+            constexpr int U = decltype(n)::value;
+            constexpr bool WHOLE = decltype(whole)::value;
             u32x4 w[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) w[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(base + (j + n_rg * u) * pitch));
+            for (int u = 0; u < U; ++u) {
+                const int r = j + n_rg * u;
+                w[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(base + (WHOLE || r < n_f ? r : n_f - 1) * pitch));
+            }
 #pragma unroll
-            for (int u = 0; u < U; ++u) add(w[u]);
+            for (int u = 0; u < U; ++u) add(w[u], WHOLE || j + n_rg * u < n_f);
+        };
+        if constexpr (ONE) {
+            if (rg < n_f) batch(rg, IC<1>(), std::true_type());
+        } else {
+            int j0 = 0;                              // rows before j0 are in
+            for (; j0 + n_rg * 8 <= n_f; j0 += n_rg * 8) batch(j0 + rg, IC<8>(), std::true_type());
+            const auto some = std::false_type();
+            switch ((n_f - j0 + n_rg - 1) / n_rg) {  // the rows that are left, per row group
+                case 8: batch(j0 + rg, IC<8>(), some); break;
+                case 7: batch(j0 + rg, IC<7>(), some); break;
+                case 6: batch(j0 + rg, IC<6>(), some); break;
+                case 5: batch(j0 + rg, IC<5>(), some); break;
+                case 4: batch(j0 + rg, IC<4>(), some); break;
+                case 3: batch(j0 + rg, IC<3>(), some); break;
+                case 2: batch(j0 + rg, IC<2>(), some); break;
+                case 1: batch(j0 + rg, IC<1>(), some); break;
+            }
         }
-        for (; j < n_f; j += n_rg) add(__builtin_nontemporal_load(reinterpret_cast<const u32x4*>(base + j * pitch)));
     }
 #pragma unroll
-    for (int i = 0; i < VEC; ++i) red[(rg * lpr + cl) * VEC + i] = acc[i];
+    for (int i = 0; i < VEC; ++i) red[threadIdx.x * VEC + i] = acc[i];
     __syncthreads();
-    // lpr * VEC columns, summed over the row groups
-    for (int c = threadIdx.x; c < lpr * VEC; c += 256) {
-        float sum = 0.f;
-        for (int g = 0; g < n_rg; ++g) sum += red[g * lpr * VEC + c];
-        const int oc = blockIdx.y * lpr * VEC + c;
+    const int cols = lpr * VEC;                      // of the slab
+    auto write = [&](int c, float sum) {
+        const int oc = blockIdx.y * cols + c;
         if (oc < d_prime) out[frame * d_prime + oc] = sum / (float)n_f;
+    };
+    const int n_used = n_f < n_rg ? n_f : n_rg;      // row groups that had a row
+    if (cols >= 256 || n_used <= 16) {
+        for (int c = threadIdx.x; c < cols; c += 256) {
+            float sum = 0.f;
+            for (int g = 0; g < n_used; ++g) sum += red[g * cols + c];
+            write(c, sum);
+        }
+        return;
+    }
+    // few columns, many row groups: VEC of them per thread, then those sums
+    const int c = threadIdx.x & (cols - 1), pt = threadIdx.x / cols;
+    float sum = 0.f;
+#pragma unroll
+    for (int g = 0; g < VEC; ++g) sum += red[(pt * VEC + g) * cols + c];
+    part[threadIdx.x] = sum;
+    __syncthreads();
+    if (threadIdx.x < cols) {
+        sum = 0.f;
+        for (int g = 0; g < 256 / cols; ++g) sum += part[g * cols + c];
+        write(c, sum);
     }
 }
 
@@ -867,17 +914,24 @@ __global__ __launch_bounds__(RANK_THREADS) void retrieve_short_kernel(RetrieveAr
 
 namespace {
 
-// one vector per `per` rows, n_rows in all
+// One vector per `per` rows, n_rows in all.  Lanes per workgroup: a whole row's (up to 256), narrowed to 128 bytes while the
+// frames have two rows or more for each row group and the narrow slabs are at most 4,096 workgroups.  Beyond that the chip is
+// full either way and whole rows are level or ahead: 1,024 frames of 256 x 512 39.8 us and 41.3 us in slabs (fp32: 450 blocks of 8 x 512 2.8
+// and 6.1), 2,048 of 33 x 256 5.3 and 9.0.
+constexpr int MIN_LPR_LOG2 = 3, MAX_SLABS = 4096;
 hipError_t mean_rows_launch(const void* k, int64_t n_rows, int per, int d_prime, int dtype, float* out, hipStream_t stream) {
     const int vec = dtype == REKV_BF16 ? 8 : 4;
     const int lanes = (d_prime + vec - 1) / vec;          // 16-byte lanes per key row
+    const int64_t frames = (n_rows + per - 1) / per;
     int lpr_log2 = 0;
     while ((1 << lpr_log2) < lanes && lpr_log2 < 8) ++lpr_log2;
-    dim3 grid((unsigned)((n_rows + per - 1) / per), (unsigned)((lanes + (1 << lpr_log2) - 1) >> lpr_log2));
-    if (dtype == REKV_BF16)
-        hipLaunchKernelGGL(frame_keys_kernel<true>, grid, dim3(256), 0, stream, k, per, n_rows, d_prime, lpr_log2, out);
-    else
-        hipLaunchKernelGGL(frame_keys_kernel<false>, grid, dim3(256), 0, stream, k, per, n_rows, d_prime, lpr_log2, out);
+    if (frames * ((lanes + (1 << MIN_LPR_LOG2) - 1) >> MIN_LPR_LOG2) <= MAX_SLABS)
+        while (lpr_log2 > MIN_LPR_LOG2 && (1024 >> lpr_log2) <= per) --lpr_log2;
+    dim3 grid((unsigned)frames, (unsigned)((lanes + (1 << lpr_log2) - 1) >> lpr_log2));
+    const bool bf16 = dtype == REKV_BF16, one = per <= 256 >> lpr_log2;
+    auto kern = bf16 ? (one ? frame_keys_kernel<true, true> : frame_keys_kernel<true, false>)
+                     : (one ? frame_keys_kernel<false, true> : frame_keys_kernel<false, false>);
+    hipLaunchKernelGGL(kern, grid, dim3(256), 0, stream, k, per, n_rows, d_prime, lpr_log2, out);
     return hipGetLastError();
 }
 
