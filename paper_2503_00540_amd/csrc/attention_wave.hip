@@ -448,87 +448,85 @@ __global__ __launch_bounds__(THREADS, 2) void attn_wave_kernel(WaveArgs a) {
     if (!sh_last) return;
 
     // ---- last of the row block's workgroups: the splits' results.  Threads form n_grp groups that share
-    // the splits; a thread owns P chunks and has P * U loads in flight, the first of them issued
-    // before the weights exp2(m_s - max) / sum are worked out (LPR lanes per row) and passed through LDS
-    // (merge_lds_bytes, which the plan keeps within the tiles' storage).
-    f32x2* wts = reinterpret_cast<f32x2*>(lds);                      // [split][T]: (m, l), then the weight
-    f32x4* red = reinterpret_cast<f32x4*>(lds + (size_t)a.n_splits * T * 8);    // [group - 1][chunk]
-    auto weights = [&] {
-        constexpr int LPR = THREADS / T;
-        const int r = tid / LPR, j = tid % LPR;
-        float m = -INFINITY, l = 0.f;
-        if (r < n_rows)
-            for (int s = j; s < a.n_splits; s += LPR) {
-                const f32x2 x = __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(
-                    part, part0 + (uint32_t)s * PART_B + T * D * 4 + r * 8, 0, SC1));
-                wts[s * T + r] = x;
-                m = fmaxf(m, x[0]);
-            }
-#pragma unroll
-        for (int o2 = 1; o2 < LPR; o2 <<= 1) m = fmaxf(m, __shfl_xor(m, o2));
-        if (r < n_rows)
-            for (int s = j; s < a.n_splits; s += LPR) {
-                const f32x2 x = wts[s * T + r];
-                const float w = x[0] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(x[0] - m);
-                l += x[1] * w;
-                wts[s * T + r][0] = w;
-            }
-#pragma unroll
-        for (int o2 = 1; o2 < LPR; o2 <<= 1) l += __shfl_xor(l, o2);
-        if (r < n_rows && j == 0) ml_all[r] = f32x2{m, l};
-    };
+    // the splits; a thread owns P chunks and fetches P * U of them together with their (maximum, sum) pairs, so that up
+    // to n_grp * U splits cost one memory round trip and nothing waits for a weight.  The groups meet in LDS.
+    f32x4* red = reinterpret_cast<f32x4*>(lds);                      // [group - 1][chunk]
+    f32x2* red_ml = reinterpret_cast<f32x2*>(lds + (THREADS - 64) * 16);
     auto merge = [&](auto pc, int n_grp, int per) {
         constexpr int P = decltype(pc)::value, U = 16 / P;
-        const int grp = n_grp > 1 ? tid / per : 0;
+        const int grp = __builtin_amdgcn_readfirstlane(n_grp > 1 ? tid / per : 0);     // (whole waves)
         const int e0 = n_grp > 1 ? tid - grp * per : tid;
-        buf4 x[P][U];
-        auto fetch = [&](int s0) {
+        uint32_t off_o[P], off_ml[P];            // past the last chunk: that one again
+#pragma unroll
+        for (int i = 0; i < P; ++i) {
+            const int e = e0 + i * THREADS < n_chunks ? e0 + i * THREADS : n_chunks - 1;
+            off_o[i] = part0 + e * 16;
+            off_ml[i] = part0 + T * D * 4 + e / CPR * 8;
+        }
+        f32x4 acc[P];
+        float m[P], l[P];
+#pragma unroll
+        for (int i = 0; i < P; ++i) {
+            acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
+            m[i] = -INFINITY;
+            l[i] = 0.f;
+        }
+        for (int s0 = grp; s0 < a.n_splits && grp < n_grp; s0 += U * n_grp) {
+            f32x4 x[P][U];
+            f32x2 w[P][U];
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const int s = s0 + u * n_grp;
 #pragma unroll
                 for (int i = 0; i < P; ++i) {
-                    x[i][u] = buf4{0u, 0u, 0u, 0u};
-                    if (grp < n_grp && s < a.n_splits && e0 + i * THREADS < n_chunks)
-                        x[i][u] = __builtin_bit_cast(buf4, __builtin_amdgcn_raw_buffer_load_b128(
-                            part, part0 + (uint32_t)s * PART_B + (e0 + i * THREADS) * 16, 0, SC1));
-                }
-            }
-        };
-        fetch(grp);
-        weights();
-        __syncthreads();
-        f32x4 acc[P];
-#pragma unroll
-        for (int i = 0; i < P; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-        for (int s0 = grp;;) {
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int s = s0 + u * n_grp;
-                if (s < a.n_splits) {
-#pragma unroll
-                    for (int i = 0; i < P; ++i) {
-                        const int e = e0 + i * THREADS;
-                        if (e < n_chunks) acc[i] += __builtin_bit_cast(f32x4, x[i][u]) * wts[s * T + e / CPR][0];
+                    w[i][u] = f32x2{-INFINITY, 0.f};
+                    x[i][u] = f32x4{0.f, 0.f, 0.f, 0.f};
+                    if (s < a.n_splits) {
+                        w[i][u] = __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(part, off_ml[i], s * PART_B, SC1));
+                        x[i][u] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(part, off_o[i], s * PART_B, SC1));
                     }
                 }
             }
-            s0 += U * n_grp;
-            if (s0 >= a.n_splits) break;
-            fetch(s0);
-        }
-        if (n_grp > 1) {
-            if (grp > 0 && grp < n_grp && e0 < n_chunks) red[(grp - 1) * per + e0] = acc[0];
-            __syncthreads();
-            if (grp == 0 && e0 < n_chunks)
-                for (int g = 1; g < n_grp; ++g) acc[0] += red[(g - 1) * per + e0];
-        }
-        if (grp == 0) {
 #pragma unroll
             for (int i = 0; i < P; ++i) {
-                const int e = e0 + i * THREADS;
-                if (e < n_chunks) write_out(e, acc[i] * (1.f / ml_all[e / CPR][1]));
+                float m_new = m[i];
+#pragma unroll
+                for (int u = 0; u < U; ++u) m_new = fmaxf(m_new, w[i][u][0]);
+                const float f = m[i] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m[i] - m_new);
+                l[i] *= f;
+                acc[i] *= f;
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const float f_u = w[i][u][0] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(w[i][u][0] - m_new);
+                    l[i] += w[i][u][1] * f_u;
+                    acc[i] += x[i][u] * f_u;
+                }
+                m[i] = m_new;
             }
+        }
+        if (n_grp > 1) {
+            if (grp > 0 && grp < n_grp) {
+                red[(grp - 1) * per + e0] = acc[0];
+                red_ml[(grp - 1) * per + e0] = f32x2{m[0], l[0]};
+            }
+            __syncthreads();
+            if (grp > 0) return;
+            float m_all = m[0];
+            for (int g = 0; g < n_grp - 1; ++g) m_all = fmaxf(m_all, red_ml[g * per + e0][0]);
+            const float f = m[0] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(m[0] - m_all);
+            l[0] *= f;
+            acc[0] *= f;
+            for (int g = 0; g < n_grp - 1; ++g) {
+                const f32x2 x = red_ml[g * per + e0];
+                const float f_g = x[0] == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(x[0] - m_all);
+                l[0] += x[1] * f_g;
+                acc[0] += red[g * per + e0] * f_g;
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < P; ++i) {
+            const int e = e0 + i * THREADS;
+            if (e < n_chunks) write_out(e, acc[i] * (1.f / l[i]));
         }
     };
     constexpr int P_MAX = T * CPR / THREADS;
