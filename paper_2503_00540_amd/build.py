@@ -1,4 +1,5 @@
-"""Builds librekv.so (the C-ABI library of HIP kernels) for gfx950, in-tree, and the C test program.
+"""Builds librekv.so (the C-ABI library of HIP kernels) for gfx950, in-tree, the native half of the Python binding and the C
+test program.
 
     python -m paper_2503_00540_amd.build
 """
@@ -32,6 +33,31 @@ def build_library(verbose: bool = True, extra: list[str] | None = None) -> str:
     return LIB
 
 
+BINDING_SRC = os.path.join(CSRC, "binding.cpp")
+BINDING = os.path.join(PKG, "_binding.so")
+
+
+def build_binding(verbose: bool = True) -> str:
+    """The native half of the Python binding: host compiler only, linked against torch and librekv.so."""
+    import sysconfig
+
+    import torch
+    tdir = os.path.dirname(torch.__file__)
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    includes = [os.path.join(ROOT, "include"), os.path.join(tdir, "include"), os.path.join(tdir, "include", "torch", "csrc", "api", "include"),
+                sysconfig.get_paths()["include"], os.path.join(rocm, "include")]
+    tlib = os.path.join(tdir, "lib")
+    cmd = ["g++", "-std=c++17", "-O2", "-fPIC", "-shared", "-Wall", "-DUSE_ROCM", "-D__HIP_PLATFORM_AMD__",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           *[a for i in includes for a in ("-isystem" if i != includes[0] else "-I", i)], BINDING_SRC, "-o", BINDING,
+           "-L", PKG, "-l:librekv.so", "-L", tlib, "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python",
+           "-Wl,-rpath,$ORIGIN", f"-Wl,-rpath,{tlib}"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    subprocess.run(cmd, check=True)
+    return BINDING
+
+
 C_PROGRAM_SRC = os.path.join(ROOT, "tests", "abi_chain.c")
 C_PROGRAM = os.path.join(ROOT, "tests", "abi_chain")
 
@@ -52,4 +78,5 @@ def build_c_program(verbose: bool = True) -> str:
 
 if __name__ == "__main__":
     build_library(extra=sys.argv[1:])
+    build_binding()
     build_c_program()

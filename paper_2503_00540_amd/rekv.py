@@ -3,6 +3,10 @@
 Every step of the path runs in the HIP kernels behind the C ABI (`include/rekv.h`).  PyTorch
 appears here only as the owner of device / pinned memory and of the current stream.  If the
 library has not been built the binding raises; there is no fallback.
+
+An ordinary call (plain device tensors, everything valid) goes through the native half of the binding
+(`csrc/binding.cpp`, _binding.so), which checks and marshals the same arguments for the same C call in a
+fraction of the time; it returns None for any other call, which the method here then serves or refuses.
 """
 from __future__ import annotations
 
@@ -39,6 +43,7 @@ class RekvError(RuntimeError):
 
 
 _lib = None
+_native = None
 
 
 def lib() -> ctypes.CDLL:
@@ -91,8 +96,20 @@ def lib() -> ctypes.CDLL:
     L.rekv_probe_mfma.argtypes = [c_void_p, c_void_p, c_int32, c_int32, POINTER(ctypes.c_double), c_void_p]
     for name in SYMBOLS[3:]:
         getattr(L, name).restype = c_int32
+    global _native
+    try:
+        from . import _binding
+    except ImportError as e:
+        raise RuntimeError(f"the native binding beside {LIB_PATH} does not load ({e}): build it with "
+                           "`python -m paper_2503_00540_amd.build`; there is no fallback path") from e
+    _binding.set_raise(_raise_status)
+    _native = _binding
     _lib = L
     return L
+
+
+def _raise_status(status: int, context: int):
+    raise RekvError(status, _lib.rekv_last_error(c_void_p(context)).decode())
 
 
 # The current stream's handle without building a torch.cuda.Stream object around it: 0.2 us instead of
@@ -124,6 +141,7 @@ class Rekv:
         if st != 0:
             raise RekvError(st, self._lib.rekv_last_error(None).decode())
         self._h = h
+        self._fast = _native.Context(h.value, n_q_heads, n_kv_heads, head_dim, tokens_per_frame, code)
 
     @classmethod
     def for_workload(cls, w, softmax_scale: float = 0.0) -> "Rekv":
@@ -131,6 +149,8 @@ class Rekv:
 
     def close(self):
         if getattr(self, "_h", None):
+            if getattr(self, "_fast", None):
+                self._fast.close()
             self._lib.rekv_destroy(self._h)
             self._h = None
 
@@ -171,6 +191,9 @@ class Rekv:
     # -- the entry points -----------------------------------------------------------------
     def encode_chunk(self, q, k_cache, v_cache, first_token: int, l_x: int, n_chunks: int, l_l: int,
                      out=None):
+        done = self._fast.encode_chunk(q, k_cache, v_cache, first_token, l_x, n_chunks, l_l, out)
+        if done is not None:
+            return done
         qh, kh = (self.n_q_heads, self.head_dim), (self.n_kv_heads, self.head_dim)
         if q.shape[0] != n_chunks * l_x:
             raise ValueError("q must hold n_chunks * l_x tokens")
@@ -186,6 +209,9 @@ class Rekv:
         return out
 
     def frame_keys(self, k, n_frames: int, out=None):
+        done = self._fast.frame_keys(k, n_frames, out)
+        if done is not None:
+            return done
         kh = (self.n_kv_heads, self.head_dim)
         if k.shape[0] < n_frames * self.tokens_per_frame:
             raise ValueError("k is shorter than n_frames * tokens_per_frame")
@@ -201,6 +227,9 @@ class Rekv:
     def retrieve_topk(self, frame_keys, n_frames: int, q_question, k: int, frame_keys_stride: int = 0,
                       want_scores: bool = False):
         """q_question [n_questions, N_q, Hq, D].  Returns (idx [n_questions, k] int32, n_sel, scores|None)."""
+        done = self._fast.retrieve_topk(frame_keys, n_frames, q_question, k, frame_keys_stride, want_scores)
+        if done is not None:
+            return done
         if q_question.dim() != 4:
             raise ValueError("q_question must be [n_questions, N_q, Hq, D]")
         nq, n_q_tokens = q_question.shape[0], q_question.shape[1]
@@ -221,6 +250,9 @@ class Rekv:
 
     def retrieve_external(self, frame_emb, q_emb, k: int, tau: float = 1.0, want_scores: bool = False):
         """frame_emb [n_frames, dim] fp32, q_emb [n_questions, dim] fp32 -> (idx, n_sel, scores|None)."""
+        done = self._fast.retrieve_external(frame_emb, q_emb, k, tau, want_scores)
+        if done is not None:
+            return done
         if frame_emb.dim() != 2 or q_emb.dim() != 2 or frame_emb.shape[1] != q_emb.shape[1]:
             raise ValueError("frame_emb [n_frames, dim] and q_emb [n_questions, dim] must share dim")
         n_frames, dim = frame_emb.shape
@@ -237,6 +269,9 @@ class Rekv:
 
     def block_keys(self, frame_keys, n_frames: int, b: int, out=None):
         """frame_keys [>= n_frames, D'] fp32 -> block vectors [ceil(n_frames / b), D'] fp32."""
+        done = self._fast.block_keys(frame_keys, n_frames, b, out)
+        if done is not None:
+            return done
         d_prime = self.n_kv_heads * self.head_dim
         n_blocks = -(-n_frames // b) if b > 0 else 0
         if frame_keys.numel() < n_frames * d_prime:
@@ -252,6 +287,9 @@ class Rekv:
 
     def expand_blocks(self, block_idx, b: int, n_frames: int):
         """block_idx [n_questions, k_blocks] int32 -> (frame_idx [n_questions, k_blocks * b], n_sel)."""
+        done = self._fast.expand_blocks(block_idx, b, n_frames)
+        if done is not None:
+            return done
         if block_idx.dim() != 2 or block_idx.dtype != torch.int32 or not block_idx.is_cuda:
             raise ValueError("block_idx must be a device tensor [n_questions, k_blocks] int32")
         nq, kb = block_idx.shape
@@ -265,6 +303,9 @@ class Rekv:
                   host_mode: int = 2):
         """idx [n_questions, k] int32 on the device.  src on the device, or pinned on the host
         (host_mode 1: copy-engine copies per frame run, 2: the kernel reads host memory itself)."""
+        done = self._fast.gather_kv(src_k, src_v, idx, n_src_frames, dst_k, dst_v)
+        if done is not None:
+            return done
         kh = (self.n_kv_heads, self.head_dim)
         on_host = not src_k.is_cuda
         nf = src_k.shape[0] // self.tokens_per_frame if n_src_frames is None else n_src_frames
@@ -288,6 +329,9 @@ class Rekv:
     def gather_kv_layers(self, src_k: list, src_v: list, idx, n_src_frames: int | None = None, dst_k=None, dst_v=None):
         """rekv_gather_kv_layers: src_k / src_v are lists of one device arena per layer; idx
         [n_layers, n_questions, k] int32 on the device."""
+        done = self._fast.gather_kv_layers(src_k, src_v, idx, n_src_frames, dst_k, dst_v)
+        if done is not None:
+            return done
         kh = (self.n_kv_heads, self.head_dim)
         n_layers = len(src_k)
         if len(src_v) != n_layers or idx.dim() != 3 or idx.shape[0] != n_layers or idx.dtype != torch.int32:
@@ -313,6 +357,9 @@ class Rekv:
                        pos_offset: int = 0, src_rotated: bool = False, src_pos_offset: int = 0,
                        base: float = 10000.0, layout: str = "half"):
         """rekv_gather_kv_rope: idx [n_questions, k] int32 on the device; source in HBM or pinned on the host."""
+        done = self._fast.gather_kv_rope(src_k, src_v, idx, n_src_frames, mode, pos_offset, src_rotated, src_pos_offset, base, layout)
+        if done is not None:
+            return done
         kh = (self.n_kv_heads, self.head_dim)
         on_host = not src_k.is_cuda
         nf = src_k.shape[0] // self.tokens_per_frame if n_src_frames is None else n_src_frames
@@ -339,6 +386,10 @@ class Rekv:
                                base: float = 10000.0, layout: str = "half", k_pos=None, out=None):
         """rekv_attention_indexed_rope: idx [n_questions, n_ret_frames] int32 (contiguous, device).
         Returns (out, k_pos)."""
+        done = self._fast.attention_indexed_rope(q, k_src, v_src, idx, k_text, v_text, n_text_tokens, n_src_frames, n_sel, mode, pos_offset,
+                                                 src_rotated, src_pos_offset, base, layout, k_pos, out)
+        if done is not None:
+            return done
         qh, kh = (self.n_q_heads, self.head_dim), (self.n_kv_heads, self.head_dim)
         if q.dim() != 4 or k_text.dim() != 4 or idx.dim() != 2 or idx.dtype != torch.int32 or not idx.is_cuda \
                 or not idx.is_contiguous():
@@ -369,6 +420,9 @@ class Rekv:
     def qa_attention(self, q, k_ret, v_ret, k_self, v_self, out=None, n_sel=None):
         """q [n_questions, N_q, Hq, D]; k_ret/v_ret [n_questions, n_ret, Hkv, D]; k_self/v_self
         [n_questions, N_q, Hkv, D]."""
+        done = self._fast.qa_attention(q, k_ret, v_ret, k_self, v_self, out, n_sel)
+        if done is not None:
+            return done
         qh, kh = (self.n_q_heads, self.head_dim), (self.n_kv_heads, self.head_dim)
         if q.dim() != 4 or k_ret.dim() != 4 or k_self.dim() != 4:
             raise ValueError("q, k_ret, k_self must be 4-d with a leading question dimension")
@@ -394,6 +448,9 @@ class Rekv:
         """q [n_questions, n_new, Hq, D]; k_ret/v_ret [n_questions, n_ret, Hkv, D]; k_text/v_text
         [n_questions, text_stride, Hkv, D] whose first n_text_tokens rows are valid and end with
         the new tokens' own K/V."""
+        done = self._fast.decode_attention(q, k_ret, v_ret, k_text, v_text, n_text_tokens, out, n_sel, no_alloc)
+        if done is not None:
+            return done
         qh, kh = (self.n_q_heads, self.head_dim), (self.n_kv_heads, self.head_dim)
         if q.dim() != 4 or k_ret.dim() != 4 or k_text.dim() != 4:
             raise ValueError("q, k_ret, k_text must be 4-d with a leading question dimension")
@@ -420,6 +477,9 @@ class Rekv:
         """Eq. 3 with the retrieved KV read in place: q [n_questions, n_new, Hq, D]; k_src/v_src the
         arena [tokens, Hkv, D]; idx [n_questions, >= n_ret_frames] int32; k_text/v_text
         [n_questions, text_stride, Hkv, D]."""
+        done = self._fast.attention_indexed(q, k_src, v_src, idx, n_ret_frames, k_text, v_text, n_text_tokens, n_src_frames, out, n_sel)
+        if done is not None:
+            return done
         qh, kh = (self.n_q_heads, self.head_dim), (self.n_kv_heads, self.head_dim)
         if q.dim() != 4 or k_text.dim() != 4 or idx.dim() != 2 or idx.dtype != torch.int32:
             raise ValueError("q, k_text must be 4-d; idx [n_questions, slots] int32")
