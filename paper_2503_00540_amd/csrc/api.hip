@@ -180,10 +180,10 @@ rekv_status run_attention(rekv_ctx* c, const rekv::AttnProblem& p, hipStream_t s
     } else {
         rekv_status s = reserve(c, &c->ws, &c->retrieval_ws, plan.reserve_bytes, ATTENTION_WS, &ws);
         if (s != REKV_OK) return s;
-        c->tickets_used |= plan.wave && plan.n_splits > 1;
+        c->tickets_used |= (plan.wave || plan.key_groups == 2) && plan.n_splits > 1;
     }
     hipError_t e = plan.wave ? rekv::attn_wave_launch(p, plan, ws, tickets, stream)
-                             : rekv::attn_bf16_launch(p, plan, ws, stream);
+                             : rekv::attn_bf16_launch(p, plan, ws, tickets, stream);
     return e == hipSuccess ? REKV_OK : fail_hip(c, "bf16 attention launch", e);
 }
 
@@ -755,13 +755,9 @@ rekv_status rekv_probe_mfma(rekv_ctx* c, float* sink, int32_t n_workgroups, int3
     return e == hipSuccess ? REKV_OK : fail_hip(c, "rekv_probe_mfma", e);
 }
 
-// Not part of the ABI (rekv.h does not declare it): the plan of a bf16 attention launch, so that the dispatch can be
-// tested without a GPU.  len_a: the window of an encode call, the retrieved tokens of a question.
-// out: kernel (0: attention_bf16.hip, else row waves per workgroup of attention_wave.hip), splits of the key range,
-// row blocks, workspace bytes, bytes the context holds after the call.
-void rekv_internal_attention_plan(int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim, int32_t is_encode,
-                                  int64_t first_token, int32_t n_items, int32_t len_q, int32_t len_a, int32_t len_b,
-                                  int32_t in_place, int64_t out[5]) {
+static rekv::AttnProblem internal_problem(int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim, int32_t is_encode,
+                                          int64_t first_token, int32_t n_items, int32_t len_q, int32_t len_a, int32_t len_b,
+                                          int32_t in_place) {
     rekv::AttnProblem p;
     memset(&p, 0, sizeof(p));
     p.n_q_heads = n_q_heads; p.n_kv_heads = n_kv_heads; p.head_dim = head_dim; p.is_encode = is_encode;
@@ -769,9 +765,28 @@ void rekv_internal_attention_plan(int32_t n_q_heads, int32_t n_kv_heads, int32_t
     (is_encode ? p.l_l : p.len_a) = len_a;
     static const int32_t some_index = 0;         // only whether there is a list matters
     if (in_place) p.a_index = &some_index;
-    const rekv::AttnPlan plan = rekv::attn_bf16_plan(p);
+    return p;
+}
+
+// Not part of the ABI (rekv.h does not declare it): the plan of a bf16 attention launch, so that the dispatch can be
+// tested without a GPU.  len_a: the window of an encode call, the retrieved tokens of a question.
+// out: kernel (0: attention_bf16.hip, else row waves per workgroup of attention_wave.hip), splits of the key range,
+// row blocks, workspace bytes, bytes the context holds after the call.
+void rekv_internal_attention_plan(int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim, int32_t is_encode,
+                                  int64_t first_token, int32_t n_items, int32_t len_q, int32_t len_a, int32_t len_b,
+                                  int32_t in_place, int64_t out[5]) {
+    const rekv::AttnPlan plan = rekv::attn_bf16_plan(internal_problem(n_q_heads, n_kv_heads, head_dim, is_encode, first_token, n_items,
+                                                                      len_q, len_a, len_b, in_place));
     out[0] = plan.wave; out[1] = plan.n_splits; out[2] = plan.m_tiles; out[3] = (int64_t)plan.workspace_bytes;
     out[4] = (int64_t)plan.reserve_bytes;
+}
+
+// And with how many key groups per workgroup.
+int32_t rekv_internal_attention_key_groups(int32_t n_q_heads, int32_t n_kv_heads, int32_t head_dim, int32_t is_encode,
+                                           int64_t first_token, int32_t n_items, int32_t len_q, int32_t len_a, int32_t len_b,
+                                           int32_t in_place) {
+    return rekv::attn_bf16_plan(internal_problem(n_q_heads, n_kv_heads, head_dim, is_encode, first_token, n_items, len_q, len_a, len_b,
+                                                 in_place)).key_groups;
 }
 
 }  // extern "C"

@@ -4,9 +4,14 @@
 // Work split.  A workgroup of 4 wavefronts owns BM = 128 query rows of one (item, KV head):
 // the G = Hq / Hkv query heads that share the KV head are stacked into the row dimension
 // (row = token * G + head-in-group), so one K/V tile staged in LDS serves all of them.
-// The key range (segment A unmasked, then segment B causal) is walked in tiles of 32 keys;
-// optionally several workgroups split the tile list (split-KV) and a merge kernel combines
-// their (max, sum, unnormalised O) partial results.
+// The key range (segment A unmasked, then segment B causal) is walked in tiles of 32 keys.  Where the row blocks do not
+// fill the chip, either two key groups of four wavefronts take half of the tiles each and merge in LDS, and workgroups beyond
+// the row blocks split the tiles further, the last arriver of a row block adding up (device-scope accesses and tickets as in
+// attention_wave.hip); or, with few row blocks and many splits, where that last arriver reads too much (16 splits of a
+// 128-row block are 1 MB through one CU), several workgroups of one group and a merge kernel over all CUs.
+// Measured one group -> two (us): a live frame of 28/4/128 with a 40-frame window 39.4 -> 35.6, of 64/8/128 with 16 frames 33.8 -> 23.1, four frames
+// of 28/4/128 with 16 frames 73.0 -> 57.1, 8 questions of 64 tokens over 5,760 keys at 64/8/128 118 -> 99, 16 of 64 over 1,200 at 16/8/64
+// 34.0 -> 17.1; and the other way, one question of 64 tokens over 12,544 keys 30.0 -> 32.8.  attention_plan.hip chooses.
 //
 // Each wavefront computes S^T = K Q^T and O^T = V^T P^T with v_mfma_f32_32x32x16_bf16, so
 // that a query is an MFMA column: it lives in one lane (and its partner lane + 32), softmax
@@ -39,10 +44,9 @@ namespace rekv {
 namespace {
 
 constexpr int STAGES = 4;     // LDS stages per tensor
-constexpr int WAVES = 4;
+constexpr int WAVES = 4;      // row waves
 constexpr int WM = 32;        // query rows per wavefront (one MFMA column block)
 constexpr int BM = WAVES * WM;
-constexpr int THREADS = WAVES * 64;
 
 template <int D>
 struct Cfg {
@@ -56,8 +60,12 @@ struct Cfg {
 struct KernelArgs {
     AttnProblem p;
     int32_t n_splits, m_tiles;
-    float* part_o;    // [item*Hkv + kvh][split][m_tiles*BM][D]
-    float* part_ml;   // [item*Hkv + kvh][split][m_tiles*BM][2]
+    // partial results of split keys, fp32.  One key group: the merge kernel's
+    float* part_o;        // [item*Hkv + kvh][split][m_tiles*BM][D]
+    float* part_ml;       // [item*Hkv + kvh][split][m_tiles*BM][2]
+    // two key groups: the last arriver's, and the arrival counters
+    float* part;          // [row block][split] of { O, as the registers of 8 wavefronts hold it; (maximum, sum) [BM] }
+    uint32_t* tickets;    // [row block]
 };
 
 // End of a pipeline step: this wave's loads except the newest N have landed, its LDS reads
@@ -70,28 +78,30 @@ __device__ inline void step_barrier() {
     __builtin_amdgcn_sched_barrier(0);
 }
 
-template <int I>
-using IC = std::integral_constant<int, I>;
-
 // ENCODE selects the segment layout (Eq. 1 window + chunk in one cache, or Eq. 3 retrieved KV +
 // question) at compile time; the two instantiations also show up under separate names in a trace.
 // INDEXED: segment A is read from the KV arena through a frame index list (no gathered copy).
 
 // STREAM: every K/V tile is read by this workgroup only (one row block per item), see dma16.
-template <int D, bool ENCODE, bool INDEXED, bool STREAM>
-__global__ __launch_bounds__(THREADS, 2) void attn_bf16_kernel(KernelArgs a) {
+// KG: key groups, sets of four wavefronts that take a part each of the workgroup's tiles and merge in LDS.
+template <int D, bool ENCODE, bool INDEXED, bool STREAM, int KG>
+__global__ __launch_bounds__(KG * WAVES * 64, 2) void attn_bf16_kernel(KernelArgs a) {
     static_assert(!(ENCODE && INDEXED), "the encode window is contiguous");
+    static_assert(KG == 1 || KG == 2, "the merge below");
+    constexpr int THREADS = KG * WAVES * 64;
     static_assert(!(STREAM && (ENCODE || INDEXED)), "streaming loads serve the plain QA / decode layout");
     typedef Cfg<D> C;
     __shared__ int32_t frame_of_slot[INDEXED ? MAX_INDEXED_FRAMES : 1];
-    // K stages 0..3, then V stages 0..3; one array so that every stage is a constant offset
-    __shared__ __attribute__((aligned(1024))) bf16_t lds[2 * STAGES * C::TILE_ELEMS];
+    // per key group: K stages 0..3, then V stages 0..3; one array so that every stage is a constant offset
+    __shared__ __attribute__((aligned(1024))) bf16_t lds[KG * 2 * STAGES * C::TILE_ELEMS];
+    __shared__ uint32_t sh_last;
     constexpr uint32_t TILE_B = C::TILE_ELEMS * 2;           // bytes per stage
 
     AttnProblem p = a.p;
     p.is_encode = ENCODE;
     const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6) % WAVES;     // row wave
+    const int kg = __builtin_amdgcn_readfirstlane(tid >> 6) / WAVES;       // key group
     const int col = lane & 31, hh = lane >> 5;
     const int G = p.n_q_heads / p.n_kv_heads;
 
@@ -129,18 +139,19 @@ __global__ __launch_bounds__(THREADS, 2) void attn_bf16_kernel(KernelArgs a) {
     // the causal tiles of segment B this row block can see
     const int tiles_a = (seg.len_a + BN - 1) / BN;
     const int a_full = seg.len_a / BN;
-    const int tiles_b_all = (p.len_b + BN - 1) / BN;
     const int q_pos0 = p.len_b - p.len_q;         // position of query token 0 inside segment B
     int last_tok = (m0 + BM - 1) / G;
     if (last_tok > p.len_q - 1) last_tok = p.len_q - 1;
     const int n_tiles = tiles_a + (last_tok + q_pos0) / BN + 1;
-    const int per_split = (tiles_a + tiles_b_all + a.n_splits - 1) / a.n_splits;
-    const int t_begin = split * per_split;
-    int t_end = t_begin + per_split;
-    if (t_end > n_tiles) t_end = n_tiles;
+    // this key group's run of them (the first t_rest runs are one longer), and the steps of the workgroup's longest
+    const int n_slots = a.n_splits * KG, slot = split * KG + kg;
+    const int t_each = n_tiles / n_slots, t_rest = n_tiles - t_each * n_slots;
+    const int t_begin = t_each * slot + (slot < t_rest ? slot : t_rest);
+    const int t_end = t_begin + t_each + (slot < t_rest);
+    const int n_steps = t_each + (split * KG < t_rest);
 
     // ---- lane-constant addressing -----------------------------------------------------
-    const uint32_t lds0 = lds_addr_of(lds);
+    const uint32_t lds0 = lds_addr_of(lds) + (uint32_t)kg * (2 * STAGES * TILE_B);
     // global -> LDS: load j of this wave fills LDS rows dma_row + j*RPI, chunk slot dma_p
     const int dma_row = wave * C::DMA_PER_WAVE * C::RPI + lane / C::CH;
     const int dma_p = lane % C::CH;
@@ -434,43 +445,141 @@ __global__ __launch_bounds__(THREADS, 2) void attn_bf16_kernel(KernelArgs a) {
         }
         wait_vmem();               // no load may still be writing LDS when the workgroup retires
     }
-
     const float l_tot = pair_sum(l_part);
-    if (a.n_splits == 1) {
-        if (row_ok) {
-            const float inv = 1.f / l_tot;
-            bf16_t* orow = static_cast<bf16_t*>(p.out) +
-                (((int64_t)item * p.len_q + tok) * p.n_q_heads + kvh * G + (row - tok * G)) * D;
-#pragma unroll
-            for (int db = 0; db < D / 32; ++db)
-#pragma unroll
-                for (int j4 = 0; j4 < 4; ++j4) {
-                    f32x2 lo = {o[db][j4 * 4] * inv, o[db][j4 * 4 + 1] * inv};
-                    f32x2 hi = {o[db][j4 * 4 + 2] * inv, o[db][j4 * 4 + 3] * inv};
-                    bf16x2 blo = __builtin_convertvector(lo, bf16x2);
-                    bf16x2 bhi = __builtin_convertvector(hi, bf16x2);
-                    u32x2 w;
-                    w.x = __builtin_bit_cast(uint32_t, blo);
-                    w.y = __builtin_bit_cast(uint32_t, bhi);
-                    *reinterpret_cast<u32x2*>(orow + db * 32 + j4 * 8 + hh * 4) = w;
-                }
-        }
-    } else {
-        const int64_t rows_pad = (int64_t)a.m_tiles * BM;
-        const int64_t base = (((int64_t)item * p.n_kv_heads + kvh) * a.n_splits + split) * rows_pad + row;
+    bf16_t* orow = static_cast<bf16_t*>(p.out) +
+        (((int64_t)item * p.len_q + tok) * p.n_q_heads + kvh * G + (row - tok * G)) * D;
+    auto write_out = [&](int db, int j4, const f32x4& v) {
+        u32x2 w;
+        w.x = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{v[0], v[1]}), bf16x2));
+        w.y = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{v[2], v[3]}), bf16x2));
+        *reinterpret_cast<u32x2*>(orow + db * 32 + j4 * 8 + hh * 4) = w;
+    };
+    if constexpr (KG == 1) {
+        if (!row_ok) return;           // the merge reads only real rows
+        const bool whole = a.n_splits == 1;
+        const float inv = whole ? 1.f / l_tot : 1.f;
+        const int64_t base = (((int64_t)item * p.n_kv_heads + kvh) * a.n_splits + split) * a.m_tiles * BM + row;
         float* po = a.part_o + base * D;
-        if (row_ok) {                  // the merge reads only real rows
 #pragma unroll
-            for (int db = 0; db < D / 32; ++db)
+        for (int db = 0; db < D / 32; ++db)
 #pragma unroll
-                for (int j4 = 0; j4 < 4; ++j4) {
-                    f32x4 w = {o[db][j4 * 4], o[db][j4 * 4 + 1], o[db][j4 * 4 + 2], o[db][j4 * 4 + 3]};
-                    *reinterpret_cast<f32x4*>(po + db * 32 + j4 * 8 + hh * 4) = w;
+            for (int j4 = 0; j4 < 4; ++j4) {
+                const f32x4 v = {o[db][j4 * 4] * inv, o[db][j4 * 4 + 1] * inv, o[db][j4 * 4 + 2] * inv, o[db][j4 * 4 + 3] * inv};
+                if (whole) write_out(db, j4, v);
+                else *reinterpret_cast<f32x4*>(po + db * 32 + j4 * 8 + hh * 4) = v;
+            }
+        if (!whole && hh == 0) *reinterpret_cast<f32x2*>(a.part_ml + base * 2) = f32x2{m_ref, l_tot};
+    } else {
+        // ---- a group with a shorter run joins the barriers it has not seen
+        for (int i = t_begin < t_end ? 2 + t_end - t_begin : 0; i < (n_steps ? 2 + n_steps : 0); ++i)
+            asm volatile("s_barrier" ::: "memory");
+        __syncthreads();
+
+        // ---- the two groups' results meet in LDS: each keeps half of the output's dimensions and hands over the other half,
+        // as its registers lie, so that both write and read whole 1 KB rows and share the rest of the work
+        constexpr int HB = D / 64, K4 = HB * 4;          // 32-dimension blocks and 16-byte pieces of a half
+        f32x4* mine = reinterpret_cast<f32x4*>(lds) + ((kg * WAVES + wave) * K4) * 64 + lane;
+        const f32x4* theirs = reinterpret_cast<const f32x4*>(lds) + (((1 - kg) * WAVES + wave) * K4) * 64 + lane;
+        f32x2* ml = reinterpret_cast<f32x2*>(reinterpret_cast<f32x4*>(lds) + 2 * WAVES * K4 * 64);
+        f32x4 acc[K4];
+        auto hand_over = [&](auto keep) {
+            constexpr int KEEP = decltype(keep)::value * HB, GIVE = HB - KEEP;
+#pragma unroll
+            for (int k = 0; k < K4; ++k) {
+                const int give = GIVE + k / 4, mid = KEEP + k / 4, j = k % 4 * 4;
+                mine[k * 64] = f32x4{o[give][j], o[give][j + 1], o[give][j + 2], o[give][j + 3]};
+                acc[k] = f32x4{o[mid][j], o[mid][j + 1], o[mid][j + 2], o[mid][j + 3]};
+            }
+        };
+        if (kg == 0) hand_over(IC<0>{});
+        else hand_over(IC<1>{});
+        ml[(kg * WAVES + wave) * 64 + lane] = f32x2{m_ref, l_tot};
+        __syncthreads();
+        const f32x2 other = ml[((1 - kg) * WAVES + wave) * 64 + lane];
+        float m = fmaxf(m_ref, other[0]);
+        const float ref = m == -INFINITY ? 0.f : m;
+        const float f0 = __builtin_amdgcn_exp2f(m_ref - ref), f1 = __builtin_amdgcn_exp2f(other[0] - ref);
+        // (rounded alike in both groups: the sum that is stored is group 0's, the last arriver's own may be group 1's)
+        float l = kg == 0 ? __builtin_fmaf(l_tot, f0, other[1] * f1) : __builtin_fmaf(other[1], f1, l_tot * f0);
+#pragma unroll
+        for (int k = 0; k < K4; ++k) acc[k] = acc[k] * f0 + theirs[k * 64] * f1;
+
+        if (a.n_splits > 1) {
+            // ---- partial results, in the same register order: as in attention_wave.hip they are written and read
+            // past the caches, and the workgroup that draws the row block's last ticket adds them up, in the order of the
+            // splits whichever it is itself
+            constexpr uint32_t PART_B = BM * (D + 2) * 4;
+            const int blk = (kvh * p.n_items + item) * a.m_tiles + mt;
+            const auto part = part_buffer(a.part, gridDim.x * PART_B);
+            const uint32_t part0 = (uint32_t)(blk * a.n_splits) * PART_B;
+            const uint32_t off_o = part0 + (uint32_t)(((kg * WAVES + wave) * K4) * 64 + lane) * 16u;
+            const uint32_t off_ml = part0 + BM * D * 4 + (uint32_t)(wave * WM + col) * 8u;
+            if (wave_active) {
+#pragma unroll
+                for (int k = 0; k < K4; ++k)
+                    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(buf4, acc[k]), part, off_o + k * 1024, split * PART_B, SC1);
+                if (kg == 0 && hh == 0)
+                    __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(buf2, f32x2{m, l}), part, off_ml, split * PART_B, SC1);
+            }
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this wave's part is at the point of coherence
+            __syncthreads();
+            if (tid == 0) {
+                const uint32_t n = __hip_atomic_fetch_add(a.tickets + blk, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                sh_last = n == (uint32_t)a.n_splits - 1u;
+                if (sh_last) __hip_atomic_store(a.tickets + blk, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
+            __syncthreads();
+            if (!sh_last || !wave_active) return;
+            f32x4 own[K4];
+            const f32x2 own_ml = {m, l};
+#pragma unroll
+            for (int k = 0; k < K4; ++k) {
+                own[k] = acc[k];
+                acc[k] = f32x4{0.f, 0.f, 0.f, 0.f};
+            }
+            m = -INFINITY;
+            l = 0.f;
+            constexpr int U = 4;                         // splits whose loads leave together
+            for (int s0 = 0; s0 < a.n_splits; s0 += U) {
+                f32x2 w[U];
+                f32x4 x[U][K4];
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    const int s = s0 + u;
+                    w[u] = f32x2{-INFINITY, 0.f};
+                    if (s < a.n_splits && s != split) {
+                        w[u] = __builtin_bit_cast(f32x2, __builtin_amdgcn_raw_buffer_load_b64(part, off_ml, s * PART_B, SC1));
+#pragma unroll
+                        for (int k = 0; k < K4; ++k)
+                            x[u][k] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(part, off_o + k * 1024, s * PART_B, SC1));
+                    } else {
+                        if (s == split) w[u] = own_ml;
+#pragma unroll
+                        for (int k = 0; k < K4; ++k) x[u][k] = own[k];
+                    }
                 }
+                float m_new = m;
+#pragma unroll
+                for (int u = 0; u < U; ++u) m_new = fmaxf(m_new, w[u][0]);
+                const float ref = m_new == -INFINITY ? 0.f : m_new, f = __builtin_amdgcn_exp2f(m - ref);
+                l *= f;
+#pragma unroll
+                for (int k = 0; k < K4; ++k) acc[k] *= f;
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    if (s0 + u >= a.n_splits) break;
+                    const float f_u = __builtin_amdgcn_exp2f(w[u][0] - ref);
+                    l += w[u][1] * f_u;
+#pragma unroll
+                    for (int k = 0; k < K4; ++k) acc[k] += x[u][k] * f_u;
+                }
+                m = m_new;
+            }
         }
-        if (hh == 0 && row_ok) {
-            f32x2 ml = {m_ref, l_tot};
-            *reinterpret_cast<f32x2*>(a.part_ml + base * 2) = ml;
+        if (row_ok) {
+            const float inv = 1.f / l;
+#pragma unroll
+            for (int k = 0; k < K4; ++k) write_out(kg * HB + k / 4, k % 4, acc[k] * inv);
         }
     }
 }
@@ -541,31 +650,27 @@ __global__ __launch_bounds__(256) void attn_merge_kernel(KernelArgs a) {
     }
 }
 
-template <int D>
-hipError_t launch(const AttnProblem& p, const AttnPlan& plan, void* workspace, hipStream_t stream) {
+template <int D, int KG>
+hipError_t launch(const AttnProblem& p, const AttnPlan& plan, void* workspace, uint32_t* tickets, hipStream_t stream) {
     KernelArgs a;
     a.p = p;
     a.n_splits = plan.n_splits;
     a.m_tiles = plan.m_tiles;
-    a.part_o = nullptr;
-    a.part_ml = nullptr;
+    a.part = a.part_o = static_cast<float*>(workspace);
+    a.tickets = tickets;
     const int64_t ik = (int64_t)p.n_items * p.n_kv_heads;
-    if (plan.n_splits > 1) {
-        a.part_o = static_cast<float*>(workspace);
-        a.part_ml = a.part_o + ik * plan.n_splits * plan.m_tiles * BM * (int64_t)D;
-    }
-    const int64_t nb = ik * plan.n_splits * plan.m_tiles;
+    a.part_ml = a.part_o ? a.part_o + ik * plan.n_splits * plan.m_tiles * BM * (int64_t)D : nullptr;
+    const dim3 grid((unsigned)((int64_t)p.n_items * p.n_kv_heads * plan.n_splits * plan.m_tiles)), block(KG * WAVES * 64);
     if (p.is_encode)
-        hipLaunchKernelGGL((attn_bf16_kernel<D, true, false, false>), dim3((unsigned)nb), dim3(THREADS), 0, stream, a);
+        hipLaunchKernelGGL((attn_bf16_kernel<D, true, false, false, KG>), grid, block, 0, stream, a);
     else if (p.a_index)
-        hipLaunchKernelGGL((attn_bf16_kernel<D, false, true, false>), dim3((unsigned)nb), dim3(THREADS), 0, stream, a);
+        hipLaunchKernelGGL((attn_bf16_kernel<D, false, true, false, KG>), grid, block, 0, stream, a);
     else if (plan.m_tiles == 1)
-        hipLaunchKernelGGL((attn_bf16_kernel<D, false, false, true>), dim3((unsigned)nb), dim3(THREADS), 0, stream, a);
+        hipLaunchKernelGGL((attn_bf16_kernel<D, false, false, true, KG>), grid, block, 0, stream, a);
     else
-        hipLaunchKernelGGL((attn_bf16_kernel<D, false, false, false>), dim3((unsigned)nb), dim3(THREADS), 0, stream, a);
+        hipLaunchKernelGGL((attn_bf16_kernel<D, false, false, false, KG>), grid, block, 0, stream, a);
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    if (plan.n_splits > 1) {
+    if (e == hipSuccess && KG == 1 && plan.n_splits > 1) {
         const int64_t rows = ik * p.len_q * (p.n_q_heads / p.n_kv_heads);
         hipLaunchKernelGGL(attn_merge_kernel<D>, dim3((unsigned)rows), dim3(256), 0, stream, a);
         e = hipGetLastError();
@@ -575,69 +680,12 @@ hipError_t launch(const AttnProblem& p, const AttnPlan& plan, void* workspace, h
 
 }  // namespace
 
-AttnPlan attn_bf16_plan(const AttnProblem& p) {
-    AttnPlan plan;
-    plan.wave = 0;
-    const int G = p.n_q_heads / p.n_kv_heads;
-    plan.m_tiles = (p.len_q * G + BM - 1) / BM;
-    const int64_t base = (int64_t)p.n_items * p.n_kv_heads * plan.m_tiles;
-    // longest tile list of any item (encode: a full window; QA: all retrieved tokens)
-    const int len_a_max = p.is_encode ? p.l_l : p.len_a;
-    const int n_tiles = (len_a_max + BN - 1) / BN + (p.len_b + BN - 1) / BN;
-    int splits = 1;
-    const int64_t target = 512;              // about two workgroups per CU
-    if (base < target) {
-        // the largest split count that still fits one round of resident workgroups: one more
-        // workgroup than that costs a whole second round
-        splits = (int)(target / base);
-        if (splits < 1) splits = 1;
-        // at least 8 tiles (256 keys) per split; 2 when only one wavefront per workgroup has rows
-        // (a decode step), where latency rather than the pipeline's fill cost decides
-        const int min_tiles = p.len_q * G <= WM ? 2 : 8;
-        const int cap = n_tiles / min_tiles > 1 ? n_tiles / min_tiles : 1;
-        if (splits > cap) splits = cap;
-    }
-    plan.n_splits = splits;
-    plan.workspace_bytes = 0;
-    if (splits > 1)
-        plan.workspace_bytes = (size_t)p.n_items * p.n_kv_heads * splits * plan.m_tiles * BM *
-                               (size_t)(p.head_dim + 2) * sizeof(float);
-    plan.reserve_bytes = plan.workspace_bytes;
-    if (base < target) {
-        // Launches that do not fill the chip by themselves go to attention_wave.hip where that is the
-        // faster one.  Estimate for this kernel, fitted to the same measurements: a 32-key step of
-        // every workgroup 0.74 us (head_dim 64: 0.65); around it 7 us, or with split keys 10 us plus
-        // the partial results' way out and back (0.48 us per MB), in a decode step 9.5 us plus the
-        // merge's walk over the splits (0.04 us each at head_dim 128).
-        // A window counts as far as the stream behind it reaches.
-        const int64_t rows = (int64_t)p.len_q * G < BM ? (int64_t)p.len_q * G : BM;
-        const int64_t ik = (int64_t)p.n_items * p.n_kv_heads;
-        const double part_mb = (double)(ik * splits * p.len_q * G * p.head_dim) * 4e-6;
-        int64_t len_a = len_a_max;
-        if (p.is_encode) {
-            const int64_t past = p.first_token + (int64_t)(p.n_items - 1) * p.len_b;
-            if (past < len_a) len_a = past;
-        }
-        const int64_t kv_tokens = p.is_encode ? len_a + (int64_t)p.n_items * p.len_b : p.n_items * (len_a + p.len_b);
-        AttnLoad load;
-        load.tiles = (len_a + BN - 1) / BN + (p.len_b + BN - 1) / BN;
-        load.kv_mb = (double)(kv_tokens * p.n_kv_heads * p.head_dim) * 4e-6;
-        load.splits = splits;
-        load.workgroups = base * splits;
-        load.us = (double)((load.tiles + splits - 1) / splits) * (p.head_dim == 64 ? 0.65 : 0.74);
-        if (splits == 1) load.us += 7.0;
-        else if (rows <= WM) load.us += 9.5 + 0.04 * splits * p.head_dim / 128;
-        else load.us += 10.0 + 0.48 * part_mb;
-        if (rows > WM) load.us += 0.1 * load.kv_mb;
-        attn_wave_plan(p, load, &plan);
-    }
-    return plan;
-}
-
-hipError_t attn_bf16_launch(const AttnProblem& p, const AttnPlan& plan, void* workspace,
+hipError_t attn_bf16_launch(const AttnProblem& p, const AttnPlan& plan, void* workspace, uint32_t* tickets,
                             hipStream_t stream) {
-    if (p.head_dim == 128) return launch<128>(p, plan, workspace, stream);
-    if (p.head_dim == 64) return launch<64>(p, plan, workspace, stream);
+    if (p.head_dim == 128)
+        return plan.key_groups == 2 ? launch<128, 2>(p, plan, workspace, tickets, stream) : launch<128, 1>(p, plan, workspace, tickets, stream);
+    if (p.head_dim == 64)
+        return plan.key_groups == 2 ? launch<64, 2>(p, plan, workspace, tickets, stream) : launch<64, 1>(p, plan, workspace, tickets, stream);
     return hipErrorInvalidValue;
 }
 

@@ -61,6 +61,17 @@ __device__ inline uint32_t lds_addr_of(const void* p) {
     return (uint32_t)(uintptr_t)(LDS_AS const void*)p;
 }
 
+// Device-scope accesses to the partial results (buffer instructions with the sc1 bit).
+constexpr int SC1 = 16;
+typedef uint32_t buf4 __attribute__((ext_vector_type(4)));
+typedef uint32_t buf2 __attribute__((ext_vector_type(2)));
+__device__ inline __amdgpu_buffer_rsrc_t part_buffer(float* base, uint32_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(base, 0, bytes, 0x00020000);
+}
+
+template <int I>
+using IC = std::integral_constant<int, I>;
+
 // A query's two lanes (lane, lane ^ 32) combine a value without touching LDS:
 // v_permlane32_swap hands every lane both halves' values.
 __device__ inline float pair_max(float v) {

@@ -16,12 +16,12 @@
 // own draw.  The ticket words start at zero and the last arriver sets its word back to zero.
 //
 // What bounds it.  These launches are a chain of latencies: about 2 us to the first tile in LDS, 1 us
-// for the waves' merge, 3 us for ticket and last arriver; between them a step of 32 keys per wave takes
+// for the waves' merge, 2.5 us for ticket and last arriver (whose loads the CU's 64 B/clk path bounds); between them a step of 32 keys per wave takes
 // 1.25 us because eight private K/V tiles (128 KB) come through the CU's 64 B/clk path from L2.
 // Measured against splitting 128-row workgroups over the keys with a merge launch (as replayed from a
-// graph, us; K and V in the caches, then from HBM): 7B-class live frame, 16-frame window 32.4 -> 22.4, 32.1 -> 29.1; 0.5B-class
-// 18.3 -> 12.7, 18.8 -> 13.4; one question over 16 frames 16.2 -> 13.1, 17.1 -> 14.5; a decode step over 64 frames 16.0 ->
-// 13.9, 18.1 -> 15.9.  A software-pipelined step (S of the next tile during the softmax, as in
+// graph, us; K and V in the caches, then from HBM): 7B-class live frame, 16-frame window 31.1 -> 20.3, 31.2 -> 24.1; 0.5B-class
+// 17.9 -> 11.7, 18.3 -> 11.7; one question over 16 frames 16.0 -> 12.1, 16.5 -> 12.4; a decode step over 64 frames 16.0 ->
+// 12.4, 17.4 -> 14.2.  A software-pipelined step (S of the next tile during the softmax, as in
 // attention_bf16.hip) measured no faster here and needs 20 to 30 registers more.
 #include "attention_mfma.h"
 
@@ -31,11 +31,6 @@ namespace {
 constexpr int WAVES = 8;
 constexpr int THREADS = WAVES * 64;
 constexpr int WM = 32;               // query rows per wavefront (one MFMA column block)
-
-// LDS of the tiles, and what the last arriver of a row block of T rows lays over it: a (weight, sum) pair per split and
-// row, then the partial sums of all its thread groups but the first (one group is 64 threads or more).
-constexpr int64_t tile_lds_bytes(int d) { return (int64_t)WAVES * 2 * BN * d * 2; }
-constexpr int64_t merge_lds_bytes(int64_t n_splits, int64_t t) { return n_splits * t * 8 + (THREADS - 64) * 16; }
 
 // Division by a launch constant: n / d for n * d < 2^32 (the quotient of 32-bit division costs about
 // 30 dependent instructions, and a launch this small is mostly its prologue).
@@ -57,23 +52,12 @@ __device__ inline void wait_newest() {           // all vector-memory accesses b
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
-// Device-scope accesses to the partial results (buffer instructions with the sc1 bit).
-constexpr int SC1 = 16;
-typedef uint32_t buf4 __attribute__((ext_vector_type(4)));
-typedef uint32_t buf2 __attribute__((ext_vector_type(2)));
-__device__ inline __amdgpu_buffer_rsrc_t part_buffer(float* base, uint32_t bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(base, 0, bytes, 0x00020000);
-}
-
 // A pointer that is the same in all lanes, in scalar registers.
 __device__ inline const char* uniform(const char* p) {
     const uint64_t v = reinterpret_cast<uint64_t>(p);
     const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v), hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
     return reinterpret_cast<const char*>(((uint64_t)hi << 32) | lo);
 }
-
-template <int I>
-using IC = std::integral_constant<int, I>;
 
 // RW row waves x KG = 8 / RW key groups.  STREAM: every K/V tile is read by this workgroup only
 // (one row block per item).
@@ -92,7 +76,7 @@ __global__ __launch_bounds__(THREADS, 2) void attn_wave_kernel(WaveArgs a) {
     constexpr uint32_t PART_B = T * (D + 2) * 4; // bytes of one partial result
     __shared__ int32_t frame_of_slot[INDEXED ? MAX_INDEXED_FRAMES : 1];
     // per key group and stage: a K tile, a V tile; at the end per key group: its O [T][D] fp32
-    __shared__ __attribute__((aligned(1024))) unsigned char lds[tile_lds_bytes(D)];
+    __shared__ __attribute__((aligned(1024))) unsigned char lds[(int64_t)WAVES * 2 * BN * D * 2];
     __shared__ f32x2 ml[KG][T];
     __shared__ f32x2 ml_all[T];
     __shared__ uint32_t sh_last;
@@ -561,90 +545,7 @@ hipError_t launch(const AttnProblem& p, const AttnPlan& plan, void* workspace, u
     return hipGetLastError();
 }
 
-// head_dim 64 with more than 32 rows, where the estimates of attn_wave_plan are not close enough once K and V come from HBM: the
-// row blocks of a head walk the same tiles together and have little in flight.  There a launch is taken only if a finer
-// estimate of its split (us) also lies below 0.98 of the same for the 128-row kernel.  Both are least-squares fits to times
-// from HBM, replayed from a graph, of 4,100 random shapes (heads from 4/4/64 to 24/8/64; live chunks with windows of 2 to 77
-// frames on young and old streams, questions of 1 to 64 users over 1 to 64 frames).  Of 900 more with over 8 MB of K and V
-// 162 take over 3% longer than on the 128-row kernel without this line, up to 1.6 times as long (16/8/64, 392 tokens, a
-// window of 60 frames: 39 us there, 64 here), and 46 with it, 1.28 at most.  Frames read in place cost the 128-row kernel
-// more: there all are taken.
-// Up to 32 rows a line like this was not worth it: replayed from a graph 14 (K and V warm) and 26 (from HBM) of 170 decode steps
-// are over 3% slower here, by 25% at most, but issued one by one only one of each is, because the 128-row kernel's merge is a
-// second launch (9 us a call here and 11.6 there where both kernels together take 7 to 10).
-struct WaveCost {      // around the steps; a 32-key step, and what it takes more where compute units hold two workgroups; ticket;
-    double fixed, step, step_of_two, ticket, split, split_10kb, kv_mb;    // per partial result; per 10 KB of it; K and V per MB
-};
-struct RowsCost {      // likewise; the merge launch; the partial results' way out and back per MB
-    double fixed, step, step_of_two, merge, part_mb, kv_mb;
-};
-bool wave_pays(const AttnProblem& p, const AttnLoad& other, const AttnPlan& plan) {
-    constexpr RowsCost ROWS[2] = {{3.802, 0.480, 0.152, 2.939, 0.867, 0.073},       // up to 8 MB of K and V
-                                  {5.714, 0.334, 0.206, 1.858, 0.875, 0.052}};      // more than that
-    constexpr WaveCost WAVE[2][2] = {{{4.418, 0.901, 0.734, 3.586, 0.016, 0.0, 0.107}, {5.508, 0.768, 0.371, 1.940, 0.0, 0.346, 0.045}},
-                                     {{4.630, 1.087, 0.775, 3.546, 0.023, 0.0, 0.124}, {5.498, 0.798, 0.349, 4.106, 0.0, 0.125, 0.124}}};
-    const int64_t m_rows = (int64_t)p.len_q * (p.n_q_heads / p.n_kv_heads), ik = (int64_t)p.n_items * p.n_kv_heads;
-    if (p.a_index || p.head_dim != 64 || m_rows <= WM) return true;
-    const int large = other.kv_mb > 8.0;
-    const RowsCost& r = ROWS[large];
-    double rows_us = r.fixed + (double)other.tiles / (double)other.splits * (r.step + (other.workgroups > 256 ? r.step_of_two : 0.0)) + r.kv_mb * other.kv_mb;
-    if (other.splits > 1) rows_us += r.merge + r.part_mb * (double)(ik * other.splits * m_rows * p.head_dim) * 4e-6;
-    const WaveCost& w = WAVE[large][plan.wave - 1];
-    const int64_t s = plan.n_splits, T = plan.wave * WM, rows = m_rows < T ? m_rows : T;
-    double us = w.fixed + (double)other.tiles / (double)(s * (WAVES / plan.wave)) * (w.step + (ik * plan.m_tiles * s > 256 ? w.step_of_two : 0.0)) +
-                w.kv_mb * other.kv_mb;
-    if (s > 1) us += w.ticket + (double)s * (w.split + w.split_10kb * (double)(rows * p.head_dim) * 4e-4);
-    return us < 0.98 * rows_us;
-}
-
 }  // namespace
-
-// The split with the least estimated time, if that beats `other.us`, the estimate for the 128-row
-// kernel.  Fitted to launches of 7B- and 0.5B-class heads (28/4/128, 14/2/64), windows of 2 to 77 frames,
-// 1 to 9 questions: about 8 us before the first tile and after the last, a step of every wave
-// 1.25 us (head_dim 128, eight private tiles through the LDS; with 1.1 a live frame of 205 tokens with a window of 24 frames
-// came here and took 41.3 us with its frame vector, 38.8 there), 1.03 us (four tiles shared by
-// two waves), 0.63 us (head_dim 64; twice that with two workgroups on a CU); a ticket round 3 us plus
-// the last arriver's reading of the partial results, 0.04 us each and 0.07 MB/us.
-// K and V that several row blocks read, from HBM: here 0.36 us per MB on top (0.16 at head_dim 64; the row blocks of a
-// head walk the same tiles together, one step ahead of their use: little in flight), there 0.1.  A
-// question over 64 frames (26 MB): 26.9 us with its KV in the caches and 35.9 without, there 30.8 and 33.2.
-bool attn_wave_plan(const AttnProblem& p, const AttnLoad& other, AttnPlan* plan) {
-    const int G = p.n_q_heads / p.n_kv_heads, D = p.head_dim;
-    const int64_t m_rows = (int64_t)p.len_q * G, ik = (int64_t)p.n_items * p.n_kv_heads, n_tiles = other.tiles;
-    // Beyond what the last-level cache holds a launch is bound by HBM, where the 128-row kernel's three tiles of prefetch
-    // count: 102 shapes of more than 32 rows above this line took 1.0 to 1.13 times its time on average, between 128 and
-    // 256 MB 0.76 to 0.80 with K and V warm and 1.03 cold; 160 (question, head) pairs x 3.2 MB of a decode step 171 us there
-    // and 192 us here.  (Frames read in place are fewer than their count: questions share them.)
-    if ((m_rows <= WM || !p.a_index) && other.kv_mb > 268.0) return false;
-    const int64_t slots = D == 64 ? 512 : 256;   // resident workgroups: LDS holds one (D = 128) or two per CU
-    const double kv_us = m_rows > WM ? (D == 64 ? 0.16 : 0.36) * other.kv_mb : 0.0;
-    double best = 0.98 * other.us;
-    AttnPlan split = *plan;
-    for (int rw = 1; rw <= 2; ++rw) {
-        const int64_t T = rw * WM, kg = WAVES / rw;
-        if (rw > 1 && m_rows <= WM) break;
-        const int64_t m_tiles = (m_rows + T - 1) / T, base = ik * m_tiles, rows = m_rows < T ? m_rows : T;
-        if (base > slots) continue;
-        const double step_us = D == 64 ? 0.63 : (rw == 1 ? 1.25 : 1.03);
-        for (int64_t s = 1; s <= slots / base && (s == 1 || (s - 1) * kg < n_tiles); ++s) {
-            const size_t ws = s > 1 ? (size_t)(base * s) * T * (size_t)(D + 2) * sizeof(float) : 0;
-            if (ws > plan->reserve_bytes || (s > 1 && merge_lds_bytes(s, T) > tile_lds_bytes(D))) break;
-            const int64_t steps = (n_tiles + s * kg - 1) / (s * kg);
-            double us = 8.0 + (double)steps * step_us * (base * s > 256 ? 2.0 : 1.0) + kv_us;
-            if (s > 1) us += 3.0 + (double)s * (0.04 + (double)(rows * D * 4) * 1.4e-5);
-            if (us >= best) continue;
-            best = us;
-            split.wave = rw;
-            split.n_splits = (int32_t)s;
-            split.m_tiles = (int32_t)m_tiles;
-            split.workspace_bytes = ws;
-        }
-    }
-    if (!split.wave || !wave_pays(p, other, split)) return false;
-    *plan = split;
-    return true;
-}
 
 hipError_t attn_wave_launch(const AttnProblem& p, const AttnPlan& plan, void* workspace, uint32_t* tickets,
                             hipStream_t stream) {

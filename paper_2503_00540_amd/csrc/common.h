@@ -76,34 +76,24 @@ __device__ inline ItemSegs item_segments(const AttnProblem& p, int item) {
     return s;
 }
 
-// How a bf16 attention launch is split, and the workspace its partial results need (0 when one split
+// How a bf16 attention launch is split (attention_plan.hip), and the workspace its partial results need (0 when one split
 // suffices).  wave: row waves per workgroup of attention_wave.hip where it takes the launch (m_tiles = blocks of
-// 32 * wave rows), 0: attention_bf16.hip (m_tiles = 128-row blocks).
+// 32 * wave rows), 0: attention_bf16.hip (m_tiles = 128-row blocks) with one or two key groups.
 // reserve_bytes: what the context holds after the call, never less than workspace_bytes: the partial results
-// of attention_bf16.hip for this problem, whichever kernel takes it.  A program may run a prompt and then capture calls it
-// has not run before, relying on the prompt's workspace, so the choice of the kernel must not shrink it.
+// of 128-row workgroups of one key group for this problem, whichever kernel takes it.  A program may run a prompt and then
+// capture calls it has not run before, relying on the prompt's workspace, so the choice of the kernel must not shrink it.
 struct AttnPlan {
     int32_t wave;
     int32_t n_splits;
     int32_t m_tiles;
+    int32_t key_groups;
     size_t workspace_bytes, reserve_bytes;
 };
 AttnPlan attn_bf16_plan(const AttnProblem& p);
-// What the time of a launch is estimated from: the 32-key tiles of the longest item, the MB of K and V of all items, the
-// splits of the 128-row kernel and the workgroups these make, and that kernel's estimate (us).
-struct AttnLoad {
-    int64_t tiles;
-    double kv_mb;
-    int64_t splits, workgroups;
-    double us;
-};
-hipError_t attn_bf16_launch(const AttnProblem& p, const AttnPlan& plan, void* workspace,
-                            hipStream_t stream);
-// attn_wave_plan: true if that kernel takes the problem (other: what it has to beat; plan->reserve_bytes: the most
-// workspace it may ask for).  tickets: WAVE_TICKETS zeroed words that only
-// calls ordered on one stream use.
+// tickets: WAVE_TICKETS zeroed words that only calls ordered on one stream use.
 constexpr int WAVE_TICKETS = 512;
-bool attn_wave_plan(const AttnProblem& p, const AttnLoad& other, AttnPlan* plan);
+hipError_t attn_bf16_launch(const AttnProblem& p, const AttnPlan& plan, void* workspace, uint32_t* tickets,
+                            hipStream_t stream);
 hipError_t attn_wave_launch(const AttnProblem& p, const AttnPlan& plan, void* workspace, uint32_t* tickets,
                             hipStream_t stream);
 hipError_t attn_f32_launch(const AttnProblem& p, hipStream_t stream);
