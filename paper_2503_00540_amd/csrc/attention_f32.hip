@@ -363,14 +363,22 @@ hipError_t launch_mfma(const AttnProblem& p, hipStream_t stream) {
     const int64_t row_blocks = ((int64_t)p.len_q * (p.n_q_heads / p.n_kv_heads) + FR - 1) / FR;
     const int64_t blocks = row_blocks * p.n_items * p.n_kv_heads;
     if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
-    // Wavefronts per row block: enough to bring the launch near four per SIMD (4096 in all); more of
-    // them only lengthen the merge.
+    // Wavefronts per row block: enough to bring the launch near four per SIMD (4096 in all), but none without a key step in
+    // the longest item: more of them only lengthen the merge (32 chunks of 16 tokens with a window of 64 at 4/1/64, eight wavefronts and
+    // four 5.3 and 5.0 us; 8 chunks of 50 with 60 at 14/2/64 9.0 and 7.4; one step of keys, eight and one 4.8 and 4.0).
+    constexpr int KT = D == 64 ? 32 : 16;         // keys of a step
+    int64_t len_a = p.is_encode ? p.l_l : p.len_a;
+    if (p.is_encode) {
+        const int64_t past = p.first_token + (int64_t)(p.n_items - 1) * p.len_b;
+        if (past < len_a) len_a = past;
+    }
+    const int64_t steps = (len_a + p.len_b + KT - 1) / KT;
     auto go = [&](auto indexed) {
         constexpr bool IX = decltype(indexed)::value;
         const dim3 grid((unsigned)blocks);
-        if (blocks >= 4096)
+        if (blocks >= 4096 || steps == 1)
             hipLaunchKernelGGL((attn_f32_mfma_kernel<D, 1, IX>), grid, dim3(64), 0, stream, p, (int)row_blocks);
-        else if (blocks >= 1024)
+        else if (blocks >= 1024 || steps <= 4)
             hipLaunchKernelGGL((attn_f32_mfma_kernel<D, 4, IX>), grid, dim3(256), 0, stream, p, (int)row_blocks);
         else
             hipLaunchKernelGGL((attn_f32_mfma_kernel<D, 8, IX>), grid, dim3(512), 0, stream, p, (int)row_blocks);
