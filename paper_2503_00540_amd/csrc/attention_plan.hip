@@ -10,8 +10,8 @@
 // 14/2/64, 16/8/64, 8/2/128, 28/4/128, 64/8/128; live chunks of 1 to 4 frames with windows of 2 to 77, questions and decode steps of
 // 1 to 32 users over 4 to 64 frames of 33 to 256 tokens.  On all of them, and 600 that read frames in place, the choice takes
 // 1.01 of the best way's time on average (95% of them under 1.08); an estimate of 128-row workgroups of one group against
-// attention_wave.hip alone, as it stood here before, 1.085 (95% under 1.40).  On 900 others, against that: 0.94 of its time replayed from a graph,
-// 0.92 as issued (436 of them faster by 5% or more, 8 slower by as much, 1.1 at most).
+// attention_wave.hip alone, as it stood here before, 1.085 (95% under 1.40).  On 900 others, against that: 0.94 of its time replayed from a graph
+// (331 of them faster by 5% or more, 35 slower by as much, 1.2 at most: decode steps, which as issued pay for the merge launch).
 // Frames read in place are judged like gathered ones, so that both are rounded alike.
 #include "attention_mfma.h"
 
@@ -98,12 +98,15 @@ AttnPlan attn_bf16_plan(const AttnProblem& p) {
         if (blocks > slots || ((few || !in_place) && kv_mb > 268.0)) return best;
         const Cost& c = rw == 1 ? WAVE1[d128][!few] : WAVE2[d128];
         const size_t split_bytes = (size_t)blocks * T * (size_t)(D + 2) * sizeof(float);
-        // the fewest splits for every number of steps; more splits have to gain 3%
+        // K and V that no cache holds, as after a reload, with little in flight.  400 draws of whole reload-and-attention, in-place, decode
+        // and live calls took 0.866 of the time before these estimates with this term (2 of them over 2% longer), 0.867 without it (8)
+        const double cold_us = few || kv_mb <= 8.0 ? 0.0 : (kv_mb - 8.0) * (D == 64 ? 0.06 : 0.15);
+        // the fewest splits for every number of steps; more splits have to gain 2%
         for (int64_t s = 1, steps; s <= slots / blocks; s = up(n_tiles, kg * (steps - 1))) {
             steps = up(n_tiles, s * kg);
             // (more partial results per row block than these were never measured)
             if (s > 1 && ((size_t)s * split_bytes > plan.reserve_bytes || s * T * 8 > WAVES * 2 * BN * D * 2 - 7168)) break;
-            const double us = estimate(c, steps, blocks * s > ONE_PER_CU, s, (double)(s * rows * D) * 4e-4, kv_mb);
+            const double us = estimate(c, steps, blocks * s > ONE_PER_CU, s, (double)(s * rows * D) * 4e-4, kv_mb) + cold_us;
             if (us < SPLIT_GAIN * best.us) best = Way{us, rw, 1, s, row_blocks, (size_t)s * split_bytes};
             if (steps == 1) break;
         }
