@@ -102,14 +102,14 @@ def lib() -> ctypes.CDLL:
     except ImportError as e:
         raise RuntimeError(f"the native binding beside {LIB_PATH} does not load ({e}): build it with "
                            "`python -m paper_2503_00540_amd.build`; there is no fallback path") from e
-    _binding.set_raise(_raise_status)
+
+    def raise_status(status: int, context: int):      # keeps the library it was made with
+        raise RekvError(status, L.rekv_last_error(c_void_p(context)).decode())
+
+    _binding.set_raise(raise_status)
     _native = _binding
     _lib = L
     return L
-
-
-def _raise_status(status: int, context: int):
-    raise RekvError(status, _lib.rekv_last_error(c_void_p(context)).decode())
 
 
 # The current stream's handle without building a torch.cuda.Stream object around it: 0.2 us instead of
