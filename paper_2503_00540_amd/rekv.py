@@ -6,12 +6,14 @@ library has not been built the binding raises; there is no fallback.
 
 An ordinary call (plain device tensors, everything valid) goes through the native half of the binding
 (`csrc/binding.cpp`, _binding.so), which checks and marshals the same arguments for the same C call in a
-fraction of the time; it returns None for any other call, which the method here then serves or refuses.
+fraction of the time; it returns None for any other call, which the method here then serves or refuses. Where
+_binding.so does not load, the methods here serve every call, and the library's loading says so in a warning.
 """
 from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 from ctypes import POINTER, byref, c_char_p, c_float, c_int32, c_int64, c_void_p
 
 import torch
@@ -96,20 +98,32 @@ def lib() -> ctypes.CDLL:
     L.rekv_probe_mfma.argtypes = [c_void_p, c_void_p, c_int32, c_int32, POINTER(ctypes.c_double), c_void_p]
     for name in SYMBOLS[3:]:
         getattr(L, name).restype = c_int32
-    global _native
-    try:
-        from . import _binding
-    except ImportError as e:
-        raise RuntimeError(f"the native binding beside {LIB_PATH} does not load ({e}): build it with "
-                           "`python -m paper_2503_00540_amd.build`; there is no fallback path") from e
 
     def raise_status(status: int, context: int):      # keeps the library it was made with
         raise RekvError(status, L.rekv_last_error(c_void_p(context)).decode())
 
-    _binding.set_raise(raise_status)
-    _native = _binding
+    global _native
+    try:
+        from . import _binding
+        _binding.set_raise(raise_status)
+        _native = _binding
+    except ImportError as e:
+        warnings.warn(f"the native half of the binding beside {LIB_PATH} does not load ({e}); calls are marshalled in Python, "
+                      "which takes longer: build it with `python -m paper_2503_00540_amd.build`", RuntimeWarning, stacklevel=2)
+        _native = _NoNative
     _lib = L
     return L
+
+
+class _NoNative:
+    """In the place of the native half where it does not load: leaves every call to the Python method."""
+
+    @staticmethod
+    def Context(*shape):
+        return _NoNative()
+
+    def __getattr__(self, name):
+        return lambda *args: None
 
 
 # The current stream's handle without building a torch.cuda.Stream object around it: 0.2 us instead of
