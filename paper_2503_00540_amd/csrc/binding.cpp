@@ -130,11 +130,13 @@ PyObject* raise_status(Context* c, rekv_status st) {
     return nullptr;
 }
 
-// Runs the C call without the interpreter lock (a growing workspace waits for the device).
-template <class Call>
-rekv_status outside(Call call) {
+// Runs the C call without the interpreter lock (a growing workspace waits for the device).  The call's arguments are worked
+// out before the lock is given up: a tensor's address can throw (no storage behind it, a lazy copy that finds no memory), and
+// another thread may give the tensor other storage.
+template <class... P, class... A>
+rekv_status outside(rekv_status (*call)(P...), A... args) {
     PyThreadState* s = PyEval_SaveThread();
-    const rekv_status st = call();
+    const rekv_status st = call(args...);
     PyEval_RestoreThread(s);
     return st;
 }
@@ -174,7 +176,7 @@ METHOD(encode_chunk, 8) {        // q, k_cache, v_cache, first_token, l_x, n_chu
     else g.need(g.ok && g.queries(a[7], 3) && out.get().sizes() == q->sizes());
     if (!g.ok) return nullptr;
     void* s = stream();
-    const rekv_status st = outside([&] { return rekv_encode_chunk(g.c->h, ptr(*q), ptr(*k), ptr(*v), first, l_x, n_chunks, l_l, ptr(out.get()), s); });
+    const rekv_status st = outside(rekv_encode_chunk, g.c->h, ptr(*q), ptr(*k), ptr(*v), first, l_x, n_chunks, l_l, ptr(out.get()), s);
     return st ? raise_status(g.c, st) : out.take();
 }
 
@@ -190,7 +192,7 @@ METHOD(frame_keys, 3) {          // k, n_frames, out
     else g.need(g.ok && g.device(a[2], 2, at::kFloat, {dp}) && out.get().size(0) >= n);
     if (!g.ok) return nullptr;
     void* s = stream();
-    const rekv_status st = outside([&] { return rekv_frame_keys(g.c->h, ptr(*k), n, static_cast<float*>(ptr(out.get())), s); });
+    const rekv_status st = outside(rekv_frame_keys, g.c->h, ptr(*k), n, static_cast<float*>(ptr(out.get())), s);
     return st ? raise_status(g.c, st) : out.take();
 }
 
@@ -218,11 +220,9 @@ METHOD(retrieve_topk, 6) {       // frame_keys, n_frames, q_question, k, frame_k
     Tensor scores;
     if (want) scores = at::empty({nq, n_frames}, on(*q, at::kFloat));
     void* s = stream();
-    const rekv_status st = outside([&] {
-        return rekv_retrieve_topk(g.c->h, static_cast<const float*>(ptr(*fk)), stride, n_frames, ptr(*q), (int32_t)nq, (int32_t)nt, k,
-                                  static_cast<int32_t*>(ptr(idx)), static_cast<int32_t*>(ptr(n_sel)),
-                                  want ? static_cast<float*>(ptr(scores)) : nullptr, s);
-    });
+    const rekv_status st = outside(rekv_retrieve_topk, g.c->h, static_cast<const float*>(ptr(*fk)), stride, n_frames, ptr(*q), (int32_t)nq,
+                                   (int32_t)nt, k, static_cast<int32_t*>(ptr(idx)), static_cast<int32_t*>(ptr(n_sel)),
+                                   want ? static_cast<float*>(ptr(scores)) : nullptr, s);
     return st ? raise_status(g.c, st) : selection(idx, n_sel, want ? &scores : nullptr);
 }
 
@@ -240,11 +240,9 @@ METHOD(retrieve_external, 5) {   // frame_emb, q_emb, k, tau, want_scores
     Tensor scores;
     if (want) scores = at::empty({nq, n_frames}, on(*qe, at::kFloat));
     void* s = stream();
-    const rekv_status st = outside([&] {
-        return rekv_retrieve_external(g.c->h, static_cast<const float*>(ptr(*fe)), (int32_t)n_frames, (int32_t)dim,
-                                      static_cast<const float*>(ptr(*qe)), (int32_t)nq, (float)tau, k, static_cast<int32_t*>(ptr(idx)),
-                                      static_cast<int32_t*>(ptr(n_sel)), want ? static_cast<float*>(ptr(scores)) : nullptr, s);
-    });
+    const rekv_status st = outside(rekv_retrieve_external, g.c->h, static_cast<const float*>(ptr(*fe)), (int32_t)n_frames, (int32_t)dim,
+                                   static_cast<const float*>(ptr(*qe)), (int32_t)nq, (float)tau, k, static_cast<int32_t*>(ptr(idx)),
+                                   static_cast<int32_t*>(ptr(n_sel)), want ? static_cast<float*>(ptr(scores)) : nullptr, s);
     return st ? raise_status(g.c, st) : selection(idx, n_sel, want ? &scores : nullptr);
 }
 
@@ -262,9 +260,7 @@ METHOD(block_keys, 4) {          // frame_keys, n_frames, b, out
     else g.need(g.device(a[3], -1, at::kFloat) && out.get().numel() >= n_blocks * dp);
     if (!g.ok) return nullptr;
     void* s = stream();
-    const rekv_status st = outside([&] {
-        return rekv_block_keys(g.c->h, static_cast<const float*>(ptr(*fk)), n_frames, b, static_cast<float*>(ptr(out.get())), s);
-    });
+    const rekv_status st = outside(rekv_block_keys, g.c->h, static_cast<const float*>(ptr(*fk)), n_frames, b, static_cast<float*>(ptr(out.get())), s);
     return st ? raise_status(g.c, st) : out.take();
 }
 
@@ -287,10 +283,8 @@ METHOD(expand_blocks, 3) {       // block_idx, b, n_frames
     idx.made = at::empty({nq, kb * b}, on(*blk, at::kInt));
     n_sel.made = at::empty({nq}, on(*blk, at::kInt));
     void* s = stream();
-    const rekv_status st = outside([&] {
-        return rekv_expand_blocks(g.c->h, static_cast<const int32_t*>(ptr(*blk)), (int32_t)nq, (int32_t)kb, b, n_frames,
-                                  static_cast<int32_t*>(ptr(idx.made)), static_cast<int32_t*>(ptr(n_sel.made)), s);
-    });
+    const rekv_status st = outside(rekv_expand_blocks, g.c->h, static_cast<const int32_t*>(ptr(*blk)), (int32_t)nq, (int32_t)kb, b, n_frames,
+                                   static_cast<int32_t*>(ptr(idx.made)), static_cast<int32_t*>(ptr(n_sel.made)), s);
     return st ? raise_status(g.c, st) : pair(idx, n_sel);
 }
 
@@ -310,10 +304,8 @@ METHOD(gather_kv, 6) {           // src_k, src_v, idx, n_src_frames, dst_k, dst_
     }
     if (!g.ok) return nullptr;
     void* s = stream();
-    const rekv_status st = outside([&] {
-        return rekv_gather_kv(g.c->h, ptr(*k), ptr(*v), 0, n_src, static_cast<const int32_t*>(ptr(*idx)), (int32_t)nq, (int32_t)slots,
-                              ptr(dk.get()), ptr(dv.get()), s);
-    });
+    const rekv_status st = outside(rekv_gather_kv, g.c->h, ptr(*k), ptr(*v), 0, n_src, static_cast<const int32_t*>(ptr(*idx)), (int32_t)nq,
+                                   (int32_t)slots, ptr(dk.get()), ptr(dv.get()), s);
     return st ? raise_status(g.c, st) : pair(dk, dv);
 }
 
@@ -346,10 +338,8 @@ METHOD(gather_kv_layers, 6) {    // src_k, src_v (lists), idx, n_src_frames, dst
         if (!g.ok) return nullptr;
     }
     void* s = stream();
-    const rekv_status st = outside([&] {
-        return rekv_gather_kv_layers(g.c->h, pk, pv, (int32_t)layers, (int32_t)n_src, static_cast<const int32_t*>(ptr(*idx)), (int32_t)nq,
-                                     (int32_t)slots, ptr(dk.get()), ptr(dv.get()), s);
-    });
+    const rekv_status st = outside(rekv_gather_kv_layers, g.c->h, pk, pv, (int32_t)layers, (int32_t)n_src, static_cast<const int32_t*>(ptr(*idx)),
+                                   (int32_t)nq, (int32_t)slots, ptr(dk.get()), ptr(dv.get()), s);
     return st ? raise_status(g.c, st) : pair(dk, dv);
 }
 
@@ -376,10 +366,8 @@ METHOD(gather_kv_rope, 10) {     // src_k, src_v, idx, n_src_frames, then Rope's
     dk.made = at::empty({nq, slots * g.c->nf, g.c->hkv, g.c->d}, on(*idx, g.c->dtype));
     dv.made = at::empty({nq, slots * g.c->nf, g.c->hkv, g.c->d}, on(*idx, g.c->dtype));
     void* s = stream();
-    const rekv_status st = outside([&] {
-        return rekv_gather_kv_rope(g.c->h, ptr(*k), ptr(*v), 0, n_src, static_cast<const int32_t*>(ptr(*idx)), (int32_t)nq, (int32_t)slots,
-                                   ptr(dk.made), ptr(dv.made), r.base, r.layout, r.mode, r.pos, r.rotated, r.src_pos, s);
-    });
+    const rekv_status st = outside(rekv_gather_kv_rope, g.c->h, ptr(*k), ptr(*v), 0, n_src, static_cast<const int32_t*>(ptr(*idx)), (int32_t)nq,
+                                   (int32_t)slots, ptr(dk.made), ptr(dv.made), r.base, r.layout, r.mode, r.pos, r.rotated, r.src_pos, s);
     return st ? raise_status(g.c, st) : pair(dk, dv);
 }
 
@@ -410,11 +398,9 @@ METHOD(attention_indexed, 11) {  // q, k_src, v_src, idx, n_ret_frames, k_text, 
     else g.need(g.queries(a[9], 4) && out.get().sizes() == p.q->sizes());
     if (!g.ok) return nullptr;
     void* s = stream();
-    const rekv_status st = outside([&] {
-        return rekv_attention_indexed(g.c->h, ptr(*p.q), ptr(*p.k), ptr(*p.v), p.n_src, static_cast<const int32_t*>(ptr(*p.idx)), p.idx->size(1),
-                                      n_ret, n_sel, ptr(*p.kt), ptr(*p.vt), p.kt->size(1), n_text, (int32_t)p.nq, (int32_t)p.n_new,
-                                      ptr(out.get()), s);
-    });
+    const rekv_status st = outside(rekv_attention_indexed, g.c->h, ptr(*p.q), ptr(*p.k), ptr(*p.v), p.n_src,
+                                   static_cast<const int32_t*>(ptr(*p.idx)), p.idx->size(1), n_ret, n_sel, ptr(*p.kt), ptr(*p.vt), p.kt->size(1),
+                                   n_text, (int32_t)p.nq, (int32_t)p.n_new, ptr(out.get()), s);
     return st ? raise_status(g.c, st) : out.take();
 }
 
@@ -434,11 +420,10 @@ METHOD(attention_indexed_rope, 17) {   // q, k_src, v_src, idx, k_text, v_text, 
     else g.need(g.queries(a[16], 4) && out.get().sizes() == p.q->sizes());
     if (!g.ok) return nullptr;
     void* s = stream();
-    const rekv_status st = outside([&] {
-        return rekv_attention_indexed_rope(g.c->h, ptr(*p.q), ptr(*p.k), ptr(*p.v), p.n_src, static_cast<const int32_t*>(ptr(*p.idx)), n_ret,
-                                           (int32_t)n_ret, n_sel, ptr(k_pos.get()), r.base, r.layout, r.mode, r.pos, r.rotated, r.src_pos,
-                                           ptr(*p.kt), ptr(*p.vt), p.kt->size(1), n_text, (int32_t)p.nq, (int32_t)p.n_new, ptr(out.get()), s);
-    });
+    const rekv_status st = outside(rekv_attention_indexed_rope, g.c->h, ptr(*p.q), ptr(*p.k), ptr(*p.v), p.n_src,
+                                   static_cast<const int32_t*>(ptr(*p.idx)), n_ret, (int32_t)n_ret, n_sel, ptr(k_pos.get()), r.base, r.layout,
+                                   r.mode, r.pos, r.rotated, r.src_pos, ptr(*p.kt), ptr(*p.vt), p.kt->size(1), n_text, (int32_t)p.nq,
+                                   (int32_t)p.n_new, ptr(out.get()), s);
     return st ? raise_status(g.c, st) : pair(out, k_pos);
 }
 
@@ -456,10 +441,8 @@ METHOD(qa_attention, 7) {        // q, k_ret, v_ret, k_self, v_self, out, n_sel
     else g.need(g.queries(a[5], 4) && out.get().sizes() == q->sizes());
     if (!g.ok) return nullptr;
     void* s = stream();
-    const rekv_status st = outside([&] {
-        return rekv_qa_attention(g.c->h, ptr(*q), ptr(*kr), ptr(*vr), (int32_t)n_ret, n_sel, ptr(*ks), ptr(*vs), (int32_t)nq, (int32_t)nt,
-                                 ptr(out.get()), s);
-    });
+    const rekv_status st = outside(rekv_qa_attention, g.c->h, ptr(*q), ptr(*kr), ptr(*vr), (int32_t)n_ret, n_sel, ptr(*ks), ptr(*vs), (int32_t)nq,
+                                   (int32_t)nt, ptr(out.get()), s);
     return st ? raise_status(g.c, st) : out.take();
 }
 
@@ -479,11 +462,8 @@ METHOD(decode_attention, 9) {    // q, k_ret, v_ret, k_text, v_text, n_text_toke
     else g.need(g.queries(a[6], 4) && out.get().sizes() == q->sizes());
     if (!g.ok) return nullptr;
     void* s = stream();
-    const rekv_status st = outside([&] {
-        return (no_alloc ? rekv_decode_attention_noalloc : rekv_decode_attention)(
-            g.c->h, ptr(*q), ptr(*kr), ptr(*vr), (int32_t)n_ret, n_sel, ptr(*kt), ptr(*vt), kt->size(1), n_text, (int32_t)nq, (int32_t)n_new,
-            ptr(out.get()), s);
-    });
+    const rekv_status st = outside(no_alloc ? rekv_decode_attention_noalloc : rekv_decode_attention, g.c->h, ptr(*q), ptr(*kr), ptr(*vr),
+                                   (int32_t)n_ret, n_sel, ptr(*kt), ptr(*vt), kt->size(1), n_text, (int32_t)nq, (int32_t)n_new, ptr(out.get()), s);
     return st ? raise_status(g.c, st) : out.take();
 }
 

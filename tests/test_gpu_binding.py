@@ -4,6 +4,7 @@ import numpy as np
 import pytest
 import torch
 
+from paper_2503_00540_amd import rekv
 from paper_2503_00540_amd.rekv import Rekv
 
 pytestmark = pytest.mark.gpu
@@ -163,3 +164,29 @@ def test_unusual_and_refused_calls_end_as_without_it():
     r._fast = native
     r.close()
     assert outcome(lambda: r.frame_keys(t["k"], 1))[0] == "RekvError"
+
+
+def test_a_tensor_that_gives_no_address_is_refused():
+    """Its address throws: the native half leaves the call, with the interpreter as it was, to the Python method."""
+    t, r = setup(), Rekv(HQ, HKV, D, NF)
+    want = r.frame_keys(t["k"], F)
+    sealed = t["k"].clone()
+    torch._C._set_throw_on_mutable_data_ptr(sealed)
+    for call in (lambda: r.frame_keys(sealed, F), lambda: r.encode_chunk(t["q"], sealed, t["v"], 30, 7, 2, 25),
+                 lambda: r.gather_kv(sealed, t["v"], t["idx"]), lambda: r.gather_kv_layers([t["k"], sealed], [t["v"], t["k"]], t["idx"].view(2, 1, 3))):
+        with pytest.raises(RuntimeError):
+            call()
+    assert torch.equal(r.frame_keys(t["k"], F), want)
+
+
+def test_calls_without_the_native_half_end_alike(monkeypatch):
+    """Where _binding.so does not load, the Python methods serve every ordinary call."""
+    t, r = setup(), Rekv(HQ, HKV, D, NF)
+    want = {name: call() for name, call in calls(t, r).items()}
+    monkeypatch.setattr(rekv, "_native", rekv._NoNative)
+    plain = Rekv(HQ, HKV, D, NF)
+    for name, call in calls(t, plain).items():
+        got, ref = call(), want[name]
+        if name == "frame_keys out":
+            got, ref = got[:3], ref[:3]
+        assert same(got, ref), name
