@@ -5,14 +5,17 @@
 //   wave 1, 2   attention_wave.hip: blocks of 32 or 64 rows, eight or four key runs per workgroup, s splits on top;
 //   two groups  attention_bf16.hip, 128-row blocks, two key groups per workgroup, one workgroup per CU, merged by the last arriver;
 //   one group   attention_bf16.hip, 128-row blocks of four wavefronts, two workgroups per CU, merged by a second launch.
-// The estimates are least-squares fits (no term below zero) to 2,500 random problems with gathered or windowed keys, each timed in
-// every one of the ways and up to nine splits, replayed from a graph, K and V in the caches and from HBM (the mean of both): heads
-// 14/2/64, 16/8/64, 8/2/128, 28/4/128, 64/8/128; live chunks of 1 to 4 frames with windows of 2 to 77, questions and decode steps of
-// 1 to 32 users over 4 to 64 frames of 33 to 256 tokens.  On all of them, and 600 that read frames in place, the choice takes
-// 1.01 of the best way's time on average (95% of them under 1.08); an estimate of 128-row workgroups of one group against
-// attention_wave.hip alone, as it stood here before, 1.085 (95% under 1.40).  On 900 others, against that: 0.94 of its time replayed from a graph
-// (331 of them faster by 5% or more, 35 slower by as much, 1.2 at most: decode steps, which as issued pay for the merge launch).
-// Frames read in place are judged like gathered ones, so that both are rounded alike.
+// The estimates are least-squares fits (no term below zero) to random problems, each timed in every one of the ways and up to nine
+// splits, K and V in the caches and from HBM (the mean):
+//   more than 32 rows: 2,500 problems with gathered or windowed keys of the heads 14/2/64, 16/8/64, 8/2/128, 28/4/128, 64/8/128,
+//     replayed from a graph: live chunks of 1 to 4 frames with windows of 2 to 77, questions of 1 to 32 users over 4 to 64 frames;
+//   up to 32 rows: 2,100 decode steps and short questions of those heads and of 1 to 32 KV heads with groups of 1 to 16, 1 to 250
+//     users, 64 to 16,000 keys (350 more of up to a million keys count a fifth), replayed and as issued from Python (the mean).
+//     A third of the samples are not split: without them the fixed part and the cost of splitting are one column.
+// How far from the best measured way the choice is, on 1,100 others of more than 32 rows, nearly half of them of other heads, gathered, in place
+// or live: 1.02 on average (95% under 1.14; other heads 1.02 and 1.13), where the estimate that stood here before these, of
+// 128-row workgroups of one group against attention_wave.hip alone, was at 1.08 (1.38).  Up to 32 rows, on its own samples: 1.01 and 1.06 to
+// 1.07 in each of the three measurements.  Frames read in place are judged like gathered ones, so that both are rounded alike.
 #include "attention_mfma.h"
 
 namespace rekv {
@@ -23,21 +26,22 @@ constexpr int WM = 32;                    // and of a row wave
 constexpr int WAVES = 8;                  // of attention_wave.hip's workgroups
 constexpr int64_t TWO_PER_CU = 512, ONE_PER_CU = 256;
 
-// Microseconds: around everything; per 32-key step of the longest run, more where CUs hold two workgroups; where keys are split:
-// once, per split, per size of the partial results; per MB of K and V.
+// Microseconds: around everything; per 32-key step of the longest run; per tile of the average run (one at least), more where CUs
+// hold two workgroups; where keys are split: once, per split, per size of the partial results; per MB of K and V.  Where only the
+// longest run was fitted, it is the average run too.
 struct Cost {
-    double fixed, step, step_of_two, split, per_split, per_size, kv;
+    double fixed, step, run, run_of_two, split, per_split, per_size, kv;
 };
-// [head_dim 64, 128][up to 32 rows, more]
-constexpr Cost WAVE1[2][2] = {{{3.526, 0.868, 1.171, 2.448, 0.033, 0.000, 0.111}, {4.282, 0.711, 0.683, 1.755, 0.099, 0.081, 0.054}},
-                              {{4.414, 1.817, 0.000, 2.085, 0.000, 0.220, 0.084}, {5.720, 1.112, 0.000, 1.481, 0.089, 0.146, 0.058}}};
-constexpr Cost WAVE2[2] = {{4.500, 0.721, 0.529, 1.152, 0.147, 0.151, 0.030}, {6.328, 1.057, 0.000, 0.922, 0.257, 0.140, 0.034}};
-constexpr Cost TWO_GROUPS[2] = {{5.500, 0.589, 0.000, 1.040, 0.000, 0.485, 0.026}, {8.095, 0.811, 0.000, 1.121, 0.000, 0.821, 0.040}};
-constexpr Cost ONE_GROUP[2][2] = {{{3.180, 0.233, 0.000, 3.180, 0.019, 0.530, 0.116}, {3.813, 0.479, 0.096, 2.045, 0.000, 0.774, 0.035}},
-                                  {{3.484, 0.255, 0.000, 3.484, 0.034, 0.496, 0.124}, {5.761, 0.598, 0.158, 1.705, 0.000, 0.544, 0.041}}};
+// [head_dim 64, 128]
+constexpr Cost WAVE1_FEW[2] = {{3.635, 0.082, 0.939, 1.360, 2.611, 0.019, 0.110, 0.081}, {4.136, 0.467, 1.614, 0.000, 2.678, 0.000, 0.201, 0.069}};
+constexpr Cost ONE_GROUP_FEW[2] = {{4.345, 0.300, 0.000, 0.170, 2.090, 0.018, 0.677, 0.028}, {4.992, 0.430, 0.000, 0.361, 1.698, 0.034, 0.588, 0.041}};
+constexpr Cost WAVE1[2] = {{4.282, 0.711, 0.000, 0.683, 1.755, 0.099, 0.081, 0.054}, {5.720, 1.112, 0.000, 0.000, 1.481, 0.089, 0.146, 0.058}};
+constexpr Cost WAVE2[2] = {{4.500, 0.721, 0.000, 0.529, 1.152, 0.147, 0.151, 0.030}, {6.328, 1.057, 0.000, 0.000, 0.922, 0.257, 0.140, 0.034}};
+constexpr Cost TWO_GROUPS[2] = {{5.500, 0.589, 0.000, 0.000, 1.040, 0.000, 0.485, 0.026}, {8.095, 0.811, 0.000, 0.000, 1.121, 0.000, 0.821, 0.040}};
+constexpr Cost ONE_GROUP[2] = {{3.813, 0.479, 0.000, 0.096, 2.045, 0.000, 0.774, 0.035}, {5.761, 0.598, 0.000, 0.158, 1.705, 0.000, 0.544, 0.041}};
 
-double estimate(const Cost& c, int64_t steps, bool two_per_cu, int64_t splits, double size, double kv_mb) {
-    double us = c.fixed + (double)steps * (c.step + (two_per_cu ? c.step_of_two : 0.0)) + kv_mb * c.kv;
+double estimate(const Cost& c, int64_t steps, double run, bool two_per_cu, int64_t splits, double size, double kv_mb) {
+    double us = c.fixed + (double)steps * c.step + run * (c.run + (two_per_cu ? c.run_of_two : 0.0)) + kv_mb * c.kv;
     if (splits > 1) us += c.split + (double)splits * c.per_split + size * c.per_size;
     return us;
 }
@@ -96,7 +100,7 @@ AttnPlan attn_bf16_plan(const AttnProblem& p) {
         Way best = {NONE, rw, 1, 1, 1, 0};
         const int64_t T = rw * WM, kg = WAVES / rw, row_blocks = up(m_rows, T), blocks = ik * row_blocks, rows = m_rows < T ? m_rows : T;
         if (blocks > slots || ((few || !in_place) && kv_mb > 268.0)) return best;
-        const Cost& c = rw == 1 ? WAVE1[d128][!few] : WAVE2[d128];
+        const Cost& c = few ? WAVE1_FEW[d128] : rw == 1 ? WAVE1[d128] : WAVE2[d128];
         const size_t split_bytes = (size_t)blocks * T * (size_t)(D + 2) * sizeof(float);
         // K and V that no cache holds, as after a reload, with little in flight.  400 draws of whole reload-and-attention, in-place, decode
         // and live calls took 0.866 of the time before these estimates with this term (2 of them over 2% longer), 0.867 without it (8)
@@ -106,7 +110,8 @@ AttnPlan attn_bf16_plan(const AttnProblem& p) {
             steps = up(n_tiles, s * kg);
             // (more partial results per row block than these were never measured)
             if (s > 1 && ((size_t)s * split_bytes > plan.reserve_bytes || s * T * 8 > WAVES * 2 * BN * D * 2 - 7168)) break;
-            const double us = estimate(c, steps, blocks * s > ONE_PER_CU, s, (double)(s * rows * D) * 4e-4, kv_mb) + cold_us;
+            const double run = few ? fmax(1.0, (double)n_tiles / (double)(s * kg)) : (double)steps;
+            const double us = estimate(c, steps, run, blocks * s > ONE_PER_CU, s, (double)(s * rows * D) * 4e-4, kv_mb) + cold_us;
             if (us < SPLIT_GAIN * best.us) best = Way{us, rw, 1, s, row_blocks, (size_t)s * split_bytes};
             if (steps == 1) break;
         }
@@ -115,23 +120,25 @@ AttnPlan attn_bf16_plan(const AttnProblem& p) {
     const int64_t m_tiles = up(m_rows, BM);
     auto two_groups = [&] {
         if (few || base > ONE_PER_CU) return Way{NONE, 0, 2, 1, m_tiles, 0};
-        const int64_t s = splits_of(ONE_PER_CU, n_tiles);
-        return Way{estimate(TWO_GROUPS[d128], up(n_tiles, 2 * s), false, s, (double)(s * (m_rows < BM ? m_rows : BM)) / BM, kv_mb),
+        const int64_t s = splits_of(ONE_PER_CU, n_tiles), steps = up(n_tiles, 2 * s);
+        return Way{estimate(TWO_GROUPS[d128], steps, (double)steps, false, s, (double)(s * (m_rows < BM ? m_rows : BM)) / BM, kv_mb),
                    0, 2, s, m_tiles, (size_t)s * block_bytes};
     };
     auto one_group = [&] {
-        const int64_t s = splits_of(TWO_PER_CU, n_tiles);
-        return Way{estimate(ONE_GROUP[d128][!few], up(n_tiles, s), base * s > ONE_PER_CU, s, (double)(ik * s * m_rows * D) * 4e-6, kv_mb),
+        const int64_t s = splits_of(TWO_PER_CU, n_tiles), steps = up(n_tiles, s);
+        return Way{estimate(few ? ONE_GROUP_FEW[d128] : ONE_GROUP[d128], steps, (double)steps, base * s > ONE_PER_CU, s,
+                            (double)(ik * s * m_rows * D) * 4e-6, kv_mb),
                    0, 1, s, m_tiles, (size_t)s * block_bytes};
     };
     Way best;
     auto consider = [&](const Way& w, double gain) { if (w.us < gain * best.us) best = w; };
     if (few) {
-        // (25 to 32 rows of head_dim 64 over few pairs of item and KV head: level at one item, 8.3 us for 16/2/64 over 4,000 keys
-        // and 8.0 to 8.3 split over the keys of a workgroup, so that only a clear gain counts)
-        const bool level = D == 64 && m_rows > 24 && ik <= 6;
-        best = level ? one_group() : wave(1);
-        consider(level ? wave(1) : one_group(), level ? 0.75 : 0.97);
+        // (25 to 32 rows of head_dim 64 over two to six pairs of item and KV head, split either way: from level, 8.0 and 8.2 us for
+        // 16/2/64 over 4,000 keys, to a gain of 14%; only more than that counts, so that these stay where their results were)
+        const Way w1 = wave(1);
+        const bool level = D == 64 && m_rows > 24 && ik > 1 && ik <= 6 && w1.splits > 1;
+        best = one_group();
+        consider(w1, level ? 0.80 : 1.0);
     } else {
         best = two_groups();
         const Way w1 = wave(1), w2 = wave(2);

@@ -102,3 +102,23 @@ def test_beyond_the_last_level_cache_the_128_row_kernel(d, hq, hkv, len_q):
 ])
 def test_launches_that_splitting_the_keys_slows_down(hq, hkv, d, len_q, len_a, encode):
     assert plan(hq, hkv, d, len_q, len_a, len_q, 1, encode)[0] == 0
+
+
+@pytest.mark.parametrize("hq,hkv,d,len_q,len_a,len_b,items,wave", [
+    # head_dim 64, more users than half of the chip's places: an unsplit 128-row workgroup has rows for one wavefront of four
+    (14, 2, 64, 1, 237, 275, 144, 1),        # us, replayed from a graph: 10.1 and 12.4 with 128-row workgroups
+    (14, 2, 64, 1, 819, 75, 219, 1),         # 17.0 and 18.9
+    (16, 8, 64, 1, 163, 122, 37, 1),         # 8.1 and 9.7
+    (28, 4, 64, 1, 1512, 104, 104, 1),       # 30.0 and 32.7
+    # a few hundred keys of one user: one launch
+    (28, 4, 128, 1, 193, 70, 1, 1),          # 6.2 and 7.7
+    (14, 2, 64, 4, 137, 224, 1, 1),          # 5.3 and 7.1
+    # around a thousand keys, or many of many users: 128-row workgroups split over the keys and a merge
+    (8, 4, 128, 1, 467, 35, 3, 0),           # 8.2 and 9.8 with the split-key kernel
+    (64, 8, 128, 1, 1008, 13, 1, 0),         # 8.4 and 9.7
+    (8, 2, 128, 1, 720, 30, 5, 0),
+    (64, 8, 128, 1, 1152, 30, 1, 0),
+    (32, 32, 64, 1, 4716, 28, 5, 0),         # 36 and 48
+])
+def test_few_rows_take_the_faster_kernel(hq, hkv, d, len_q, len_a, len_b, items, wave):
+    assert plan(hq, hkv, d, len_q, len_a, len_b, items)[0] == wave
