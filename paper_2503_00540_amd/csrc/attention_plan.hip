@@ -15,7 +15,8 @@
 // How far from the best measured way the choice is, on 1,100 others of more than 32 rows, nearly half of them of other heads, gathered, in place
 // or live: 1.02 on average (95% under 1.14; other heads 1.02 and 1.13), where the estimate that stood here before these, of
 // 128-row workgroups of one group against attention_wave.hip alone, was at 1.08 (1.38).  Up to 32 rows, on its own samples: 1.01 and 1.06 to
-// 1.07 in each of the three measurements.  Frames read in place are judged like gathered ones, so that both are rounded alike.
+// 1.07 in each of the three measurements.
+// Frames read in place are judged like gathered ones, except where more than 268 MB of them are listed (see there).
 #include "attention_mfma.h"
 
 namespace rekv {
@@ -93,8 +94,10 @@ AttnPlan attn_bf16_plan(const AttnProblem& p) {
     };
     constexpr double NONE = 1e30;
     // attention_wave.hip.  Beyond what the last-level cache holds a launch is bound by HBM, where the 128-row kernel's three
-    // tiles of prefetch count (102 shapes of more than 32 rows above this line took 1.0 to 1.13 times its time on average; frames
-    // read in place are fewer than their count: questions share them).  Resident workgroups: LDS holds one (D = 128) or two per CU.
+    // tiles of prefetch count (102 shapes of more than 32 rows above this line took 1.0 to 1.13 times its time on average).  Frames
+    // read in place are fewer than their count, questions share them: on 80 such calls of head_dim 64 and more than 32 rows the choice
+    // without the line takes 1.005 of the best way's time, with it 1.09 and up to 1.6 (at head_dim 128 the line changes nothing).
+    // Resident workgroups: LDS holds one (D = 128) or two per CU.
     const int64_t slots = D == 64 ? TWO_PER_CU : ONE_PER_CU;
     auto wave = [&](int rw) {
         Way best = {NONE, rw, 1, 1, 1, 0};
@@ -102,8 +105,9 @@ AttnPlan attn_bf16_plan(const AttnProblem& p) {
         if (blocks > slots || ((few || !in_place) && kv_mb > 268.0)) return best;
         const Cost& c = few ? WAVE1_FEW[d128] : rw == 1 ? WAVE1[d128] : WAVE2[d128];
         const size_t split_bytes = (size_t)blocks * T * (size_t)(D + 2) * sizeof(float);
-        // K and V that no cache holds, as after a reload, with little in flight.  400 draws of whole reload-and-attention, in-place, decode
-        // and live calls took 0.866 of the time before these estimates with this term (2 of them over 2% longer), 0.867 without it (8)
+        // K and V that no cache holds, as after a reload, come with little in flight.  372 gathered calls from HBM that the term was not
+        // chosen on: 0.952 of the time of the estimate before these with it, 0.962 without (14 of them over 10% longer, 2 with it);
+        // with K and V in the caches 0.953 with it and 0.940 without.
         const double cold_us = few || kv_mb <= 8.0 ? 0.0 : (kv_mb - 8.0) * (D == 64 ? 0.06 : 0.15);
         // the fewest splits for every number of steps; more splits have to gain 2%
         for (int64_t s = 1, steps; s <= slots / blocks; s = up(n_tiles, kg * (steps - 1))) {

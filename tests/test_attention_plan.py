@@ -122,3 +122,17 @@ def test_launches_that_splitting_the_keys_slows_down(hq, hkv, d, len_q, len_a, e
 ])
 def test_few_rows_take_the_faster_kernel(hq, hkv, d, len_q, len_a, len_b, items, wave):
     assert plan(hq, hkv, d, len_q, len_a, len_b, items)[0] == wave
+
+
+def test_frames_in_place_are_judged_like_gathered_ones():
+    """Except beyond 268 MB of listed K and V at head_dim 64 with more than 32 rows, where questions share what they list."""
+    rng, beyond = random.Random(11), 0
+    log_int = lambda lo, hi: int(round(math.exp(rng.uniform(math.log(lo), math.log(hi)))))
+    for _ in range(60_000):
+        hkv, d, len_q, items, frames = rng.choice([1, 2, 4, 8, 16]), rng.choice([64, 128]), log_int(1, 300), log_int(1, 300), log_int(1, 1024)
+        hq, len_a, len_b = hkv * rng.choice([1, 2, 3, 7, 8]), frames * rng.choice([33, 144, 196, 256]), len_q + rng.choice([0, log_int(1, 300)])
+        both = [plan(hq, hkv, d, len_q, len_a, len_b, items, in_place=x) for x in (False, True)]
+        large = d == 64 and len_q * (hq // hkv) > 32 and items * (len_a + len_b) * hkv * d * 4 > 268_000_000
+        assert both[0] == both[1] or large, (hq, hkv, d, len_q, len_a, len_b, items)
+        beyond += both[0] != both[1]
+    assert beyond > 100
