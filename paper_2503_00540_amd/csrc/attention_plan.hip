@@ -48,6 +48,9 @@ double estimate(const Cost& c, int64_t steps, double run, bool two_per_cu, int64
 }
 
 constexpr double SPLIT_GAIN = 0.98;
+// The most rows of partial results per row block of attention_wave.hip (228 splits of 32 rows, 484 at head_dim 128): more were
+// never measured.
+constexpr int64_t MOST_SPLIT_ROWS[2] = {7296, 15488};
 int64_t up(int64_t n, int64_t d) { return (n + d - 1) / d; }
 
 }  // namespace
@@ -112,8 +115,7 @@ AttnPlan attn_bf16_plan(const AttnProblem& p) {
         // the fewest splits for every number of steps; more splits have to gain 2%
         for (int64_t s = 1, steps; s <= slots / blocks; s = up(n_tiles, kg * (steps - 1))) {
             steps = up(n_tiles, s * kg);
-            // (more partial results per row block than these were never measured)
-            if (s > 1 && ((size_t)s * split_bytes > plan.reserve_bytes || s * T * 8 > WAVES * 2 * BN * D * 2 - 7168)) break;
+            if (s > 1 && ((size_t)s * split_bytes > plan.reserve_bytes || s * T > MOST_SPLIT_ROWS[d128])) break;
             const double run = few ? fmax(1.0, (double)n_tiles / (double)(s * kg)) : (double)steps;
             const double us = estimate(c, steps, run, blocks * s > ONE_PER_CU, s, (double)(s * rows * D) * 4e-4, kv_mb) + cold_us;
             if (us < SPLIT_GAIN * best.us) best = Way{us, rw, 1, s, row_blocks, (size_t)s * split_bytes};

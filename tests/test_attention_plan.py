@@ -19,13 +19,20 @@ def plan(hq, hkv, d, len_q, len_a, len_b, items=1, encode=False, first=1 << 40, 
     return tuple(out)
 
 
-def last_arriver_lds(wave, splits, rows, d):
-    """Bytes the merge of a row block of so many rows lays over the tiles: a weight pair per split and row, then the
-    partial sums of all thread groups but the first."""
-    n_chunks = rows * d // 4
-    per = -(-n_chunks // 64) * 64
+def key_groups(hq, hkv, d, len_q, len_a, len_b, items=1, encode=False, first=1 << 40, in_place=False):
+    f = rekv.lib().rekv_internal_attention_key_groups
+    f.restype = ctypes.c_int32
+    f.argtypes = [ctypes.c_int32] * 4 + [ctypes.c_int64] + [ctypes.c_int32] * 5
+    return f(hq, hkv, d, int(encode), first, items, len_q, len_a, len_b, int(in_place))
+
+
+def last_arriver_lds(rows, d):
+    """Bytes that the merge of a row block of so many rows lays over the tiles: of all thread groups but the first, the partial
+    sums from the front, their maxima and sums behind the room that the most of those can take."""
+    per = -(-(rows * d // 4) // 64) * 64
     groups = 512 // per if per * 2 <= 512 else 1
-    return splits * 32 * wave * 8 + (groups - 1) * per * 16
+    assert (groups - 1) * per <= 512 - 64
+    return (512 - 64) * 16 + (groups - 1) * per * 8 if groups > 1 else 0
 
 
 def workspace_of_128_row_blocks(hq, hkv, d, len_q, len_a, len_b, items):
@@ -55,7 +62,7 @@ def shapes():
 
 
 def test_split_launches_fit_their_kernel():
-    n_split = 0
+    n_split = n_two = 0
     for hq, hkv, d, len_q, len_a, len_b, items, encode in shapes():
         wave, splits, row_blocks, ws, reserved = plan(hq, hkv, d, len_q, len_a, len_b, items, encode)
         where = (hq, hkv, d, len_q, len_a, len_b, items, encode)
@@ -63,7 +70,15 @@ def test_split_launches_fit_their_kernel():
         assert ws <= 33 << 20, where                              # the allocation-free entry point's scratch
         assert reserved == workspace_of_128_row_blocks(hq, hkv, d, len_q, len_a, len_b, items), where
         assert ws <= reserved, where
+        groups = key_groups(hq, hkv, d, len_q, len_a, len_b, items, encode)
+        assert groups in (1, 2) and (groups == 1 or not wave), where
         if not wave:
+            blocks = items * hkv * row_blocks
+            assert row_blocks == -(-len_q * (hq // hkv) // 128), where
+            assert ws == (blocks * splits * 128 * (d + 2) * 4 if splits > 1 else 0), where
+            if groups == 2:                                       # arrival counters, one resident workgroup per CU
+                n_two += 1
+                assert blocks * splits <= 256 and len_q * (hq // hkv) > 32, where
             continue
         m_rows, t = len_q * (hq // hkv), 32 * wave
         assert row_blocks == -(-m_rows // t), where
@@ -74,8 +89,9 @@ def test_split_launches_fit_their_kernel():
         n_split += 1
         assert ws >= items * hkv * row_blocks * splits * t * (d + 2) * 4, where
         last = m_rows - (row_blocks - 1) * t
-        assert max(last_arriver_lds(wave, splits, rows, d) for rows in {last, min(m_rows, t)}) <= 8 * 2 * 32 * d * 2, where
-    assert n_split > 1000
+        assert max(last_arriver_lds(rows, d) for rows in {last, min(m_rows, t)}) <= 8 * 2 * 32 * d * 2, where
+        assert splits * t <= (7296 if d == 64 else 15488), where      # the most that were ever measured
+    assert n_split > 1000 and n_two > 1000
 
 
 @pytest.mark.parametrize("hq,hkv,d,l_x,items", [(8, 2, 128, 66, 1), (28, 4, 128, 196, 1), (14, 2, 64, 144, 2), (16, 8, 64, 392, 1)])
