@@ -40,7 +40,7 @@ __device__ inline float wave_sum(float v) {
 // or two batches per thread (mean_rows_launch).  The last frame may be short (n_rows in all; a stream's last block of
 // frames).  Many frames are bound by HBM.  Measured with whole rows per workgroup and a loop over the left-over rows, then
 // so (us, replayed from a graph; keys in the caches / from HBM): one frame of 196 x 512 4.4 / 6.6 -> 2.4 / 2.4, of 196 x 128 2.7 / 4.3 ->
-// 2.2 / 2.6, 64 frames of 196 x 512 7.5 / 8.3 -> 3.4 / 4.7, 256 of them 8.9 / 11.0 -> 7.8 / 10.0 (5.3 TB/s).
+// 2.2 / 2.6, 64 frames of 196 x 512 7.5 / 8.3 -> 3.4 / 4.7, 256 of them 8.9 / 11.0 -> 7.8 / 10.0 (5.2 TB/s).
 // ---------------------------------------------------------------------------------------
 // ONE: a frame has no more rows than there are row groups (block vectors, tiny frames): less code to fetch.
 template <bool BF16, bool ONE>
@@ -917,18 +917,20 @@ namespace {
 // One vector per `per` rows, n_rows in all.  Lanes per workgroup: a whole row's (up to 256), narrowed to 128 bytes while the
 // frames have two rows or more for each row group and the narrow slabs are at most 4,096 workgroups.  Beyond that the chip is
 // full either way and whole rows are level or ahead: 1,024 frames of 256 x 512 39.8 us and 41.3 us in slabs (fp32: 450 blocks of 8 x 512 2.8
-// and 6.1), 2,048 of 33 x 256 5.3 and 9.0.
+// and 6.1), 2,048 of 33 x 256 5.3 and 9.0.  The lanes decide the order of a sum, so a frame's vector may differ in its last bits between
+// a call with few frames and one with many.
 constexpr int MIN_LPR_LOG2 = 3, MAX_SLABS = 4096;
 hipError_t mean_rows_launch(const void* k, int64_t n_rows, int per, int d_prime, int dtype, float* out, hipStream_t stream) {
     const int vec = dtype == REKV_BF16 ? 8 : 4;
     const int lanes = (d_prime + vec - 1) / vec;          // 16-byte lanes per key row
     const int64_t frames = (n_rows + per - 1) / per;
+    const int64_t most = n_rows < per ? n_rows : per;     // rows of the longest frame (a single short block of frames: 2.1 -> 1.8 us)
     int lpr_log2 = 0;
     while ((1 << lpr_log2) < lanes && lpr_log2 < 8) ++lpr_log2;
     if (frames * ((lanes + (1 << MIN_LPR_LOG2) - 1) >> MIN_LPR_LOG2) <= MAX_SLABS)
-        while (lpr_log2 > MIN_LPR_LOG2 && (1024 >> lpr_log2) <= per) --lpr_log2;
+        while (lpr_log2 > MIN_LPR_LOG2 && (1024 >> lpr_log2) <= most) --lpr_log2;
     dim3 grid((unsigned)frames, (unsigned)((lanes + (1 << lpr_log2) - 1) >> lpr_log2));
-    const bool bf16 = dtype == REKV_BF16, one = per <= 256 >> lpr_log2;
+    const bool bf16 = dtype == REKV_BF16, one = most <= 256 >> lpr_log2;
     auto kern = bf16 ? (one ? frame_keys_kernel<true, true> : frame_keys_kernel<true, false>)
                      : (one ? frame_keys_kernel<false, true> : frame_keys_kernel<false, false>);
     hipLaunchKernelGGL(kern, grid, dim3(256), 0, stream, k, per, n_rows, d_prime, lpr_log2, out);
