@@ -363,9 +363,10 @@ hipError_t launch_mfma(const AttnProblem& p, hipStream_t stream) {
     const int64_t row_blocks = ((int64_t)p.len_q * (p.n_q_heads / p.n_kv_heads) + FR - 1) / FR;
     const int64_t blocks = row_blocks * p.n_items * p.n_kv_heads;
     if (blocks > 0x7FFFFFFF) return hipErrorInvalidValue;
-    // Wavefronts per row block: enough to bring the launch near four per SIMD (4096 in all), but none without a key step in
-    // the longest item: more of them only lengthen the merge (32 chunks of 16 tokens with a window of 64 at 4/1/64, eight wavefronts and
-    // four 5.3 and 5.0 us; 8 chunks of 50 with 60 at 14/2/64 9.0 and 7.4; one step of keys, eight and one 4.8 and 4.0).
+    // Wavefronts per row block: enough to bring the launch near four per SIMD (4096 in all), but one where the longest item has a
+    // single step of keys and four where it has up to four: more of them only lengthen the merge (32 chunks of 16 tokens with a window
+    // of 64 at 4/1/64, eight wavefronts and four 5.3 and 5.0 us; 8 chunks of 50 with 60 at 14/2/64 9.0 and 7.4; one step, eight and one 4.8
+    // and 4.0).
     constexpr int KT = D == 64 ? 32 : 16;         // keys of a step
     int64_t len_a = p.is_encode ? p.l_l : p.len_a;
     if (p.is_encode) {

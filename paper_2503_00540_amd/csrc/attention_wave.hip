@@ -16,12 +16,12 @@
 // own draw.  The ticket words start at zero and the last arriver sets its word back to zero.
 //
 // What bounds it.  These launches are a chain of latencies: about 2 us to the first tile in LDS, 1 us
-// for the waves' merge, 2.5 us for ticket and last arriver (whose loads the CU's 64 B/clk path bounds); between them a step of 32 keys per wave takes
-// 1.25 us because eight private K/V tiles (128 KB) come through the CU's 64 B/clk path from L2.
+// for the waves' merge, 1 us for the ticket and about 3 for the last arriver, whose loads leave together; between them a step of 32
+// keys per wave takes 1.25 us because eight private K/V tiles (128 KB) come through the CU's 64 B/clk path from L2.
 // Measured against splitting 128-row workgroups over the keys with a merge launch (as replayed from a
-// graph, us; K and V in the caches, then from HBM): 7B-class live frame, 16-frame window 31.1 -> 20.3, 31.2 -> 24.1; 0.5B-class
-// 17.9 -> 11.7, 18.3 -> 11.7; one question over 16 frames 16.0 -> 12.1, 16.5 -> 12.4; a decode step over 64 frames 16.0 ->
-// 12.4, 17.4 -> 14.2.  A software-pipelined step (S of the next tile during the softmax, as in
+// graph, us; K and V in the caches, then from HBM): 7B-class live frame, 16-frame window 31.2 -> 21.2, 31.2 -> 24.0; 0.5B-class
+// 18.0 -> 11.7, 18.8 -> 12.5; one question over 16 frames 15.8 -> 12.3, 16.7 -> 13.5; a decode step over 64 frames 15.0 ->
+// 12.5, 17.5 -> 14.4.  A software-pipelined step (S of the next tile during the softmax, as in
 // attention_bf16.hip) measured no faster here and needs 20 to 30 registers more.
 #include "attention_mfma.h"
 

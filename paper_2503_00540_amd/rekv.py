@@ -1,4 +1,4 @@
-"""Thin ctypes binding over librekv.so: same names as the C ABI, argument marshalling only.
+"""Python binding over librekv.so: same names as the C ABI, argument checks and marshalling only.
 
 Every step of the path runs in the HIP kernels behind the C ABI (`include/rekv.h`).  PyTorch
 appears here only as the owner of device / pinned memory and of the current stream.  If the
