@@ -16,7 +16,8 @@
 // or live: 1.02 on average (95% under 1.14; other heads 1.02 and 1.13), where the estimate that stood here before these, of
 // 128-row workgroups of one group against attention_wave.hip alone, was at 1.08 (1.38).  Up to 32 rows, on its own samples: 1.01 and 1.06 to
 // 1.07 in each of the three measurements.
-// Frames read in place are judged like gathered ones, except where more than 268 MB of them are listed (see there).
+// Frames read in place are judged like gathered ones, except at up to 32 rows and where more than 268 MB of them are listed at
+// head_dim 64 (see below).
 #include "attention_mfma.h"
 
 namespace rekv {
@@ -143,8 +144,10 @@ AttnPlan attn_bf16_plan(const AttnProblem& p) {
         // 16/2/64 over 4,000 keys, to a gain of 14%; only more than that counts, so that these stay where their results were)
         const Way w1 = wave(1);
         const bool level = D == 64 && m_rows > 24 && ik > 1 && ik <= 6 && w1.splits > 1;
+        // (in place every lane of a 128-row workgroup looks up its frame: 1.09 to 1.10 of the estimate on 1,500 such calls, the split-key
+        // kernel 0.99 to 1.04.  With the factor the choice takes 1.004 to 1.008 of the best way's time on them, without 1.011 to 1.021)
         best = one_group();
-        consider(w1, level ? 0.80 : 1.0);
+        consider(w1, (level ? 0.80 : 1.0) * (in_place ? 1.1 : 1.0));
     } else {
         best = two_groups();
         const Way w1 = wave(1), w2 = wave(2);
